@@ -878,6 +878,17 @@ static rt_status trace_impl(rt_ctx *c, const rt_camera *cam, const rt_step_rule 
     a.h_max = r->kind == RT_STEP_RK45 ? r->h_max : r->h;
     a.t_max = r->t_max;
     a.max_steps = max_steps;
+    // the first k with (float)k h >= t_max, in the kernel's own arithmetic
+    // (nondecreasing in k), or max_steps
+    {
+        int lo = 0, hi = max_steps;
+        while (lo < hi) {
+            const int mid = lo + (hi - lo) / 2;
+            if ((float)mid * r->h >= r->t_max) hi = mid;
+            else lo = mid + 1;
+        }
+        a.n_end = std::max(lo, 1);
+    }
     a.K = r->cull_every;
     a.S = r->pass_steps;
     a.bisect_iters = r->bisect_iters;

@@ -90,6 +90,7 @@ struct TraceArgs {
     int step_kind;
     float h, rtol, atol, h_min, h_max, t_max;
     int max_steps, K, S, bisect_iters;
+    int n_end;          // RK4/Euler: accepted steps after which a ray is a miss (max_steps, or t_max reached)
     float cull_margin;  // < 0: no culling
     float cull_base;    // composed deformations: window motion without displacement, (K+1) h_max 1.02 + 1e-4
     float cull_disp;    // composed deformations: bound on |Phi(x) - x| over all x

@@ -147,6 +147,20 @@ __device__ __forceinline__ void two_sum_add(float &hi, float &lo, float d) {
     hi = s;
 }
 
+// One RK4 or Euler step where the acceleration is zero at every stage: the
+// velocity stays and the position increment is the steppers' own sum of
+// stage velocities, so the bits are those of the full step.
+template <int STEP> __device__ __forceinline__ V3<float> free_step(V3<float> y, float h) {
+    if constexpr (STEP == STEP_RK4) {
+        V3<float> sx = axpy(2.0f, y, y);
+        sx = axpy(2.0f, y, sx);
+        sx = axpy(1.0f, y, sx);
+        return (h * (float)(1.0 / 6.0)) * sx;
+    } else {
+        return h * y;
+    }
+}
+
 __device__ __forceinline__ float box_dist2(float cx, float cy, float cz, const float lo[3], const float hi[3]) {
     float dx = fmaxf(fmaxf(lo[0] - cx, cx - hi[0]), 0.0f);
     float dy = fmaxf(fmaxf(lo[1] - cy, cy - hi[1]), 0.0f);

@@ -55,6 +55,21 @@ __device__ __forceinline__ void write_out(const TraceArgs &A, unsigned oi, V3<fl
     if (A.out_steps) A.out_steps[oi] = steps;
 }
 
+// Checkpoint c of ray id on the adjoint tape.
+__device__ __forceinline__ void write_ckpt(const TraceArgs &A, int id, int c, V3<float> xh, V3<float> xl,
+                                           V3<float> y) {
+    float *ck = A.tape_ck + ((((int64_t)(id >> 6) * A.n_ckpt + c) * 9) * 64 + (id & 63));
+    ck[0 * 64] = xh.x;
+    ck[1 * 64] = xh.y;
+    ck[2 * 64] = xh.z;
+    ck[3 * 64] = xl.x;
+    ck[4 * 64] = xl.y;
+    ck[5 * 64] = xl.z;
+    ck[6 * 64] = y.x;
+    ck[7 * 64] = y.y;
+    ck[8 * 64] = y.z;
+}
+
 // Refine record of a chord hit: 4 float4 (64 B) where t is steps * h and
 // the hit step is h (RK4 and Euler without learned crossings), else 5
 // (80 B: also t as two floats and the step size).
@@ -82,6 +97,52 @@ __device__ __forceinline__ V3<float> initial_velocity(const TraceArgs &A, const 
 __device__ __forceinline__ float4 *batch_save() {
     __shared__ float4 save[3 * 256];
     return save;
+}
+
+// ============================================================ free flight
+// Kinds whose acceleration is exactly zero outside the bumps or deformations
+// the wave has listed (the graph of a sum of bumps and a composition of local
+// deformations are flat there).
+constexpr bool flat_outside(int kind) {
+    return kind == KIND_EUCLID || kind == KIND_GRAPH || kind == KIND_GANISO || is_deform(kind);
+}
+// Distance from the box [mn, mx] of the wave's positions to the nearest cut
+// region or object, rounded down; called by the whole wave.  Cut regions and
+// tori are taken as balls about their centres.
+template <int KIND>
+__device__ __forceinline__ float free_distance(const TraceArgs &A, const float4 *__restrict__ Bs,
+                                               const float4 *__restrict__ SPH, const float4 *__restrict__ PLN,
+                                               const float *__restrict__ TOR, int lane, const float mn[3],
+                                               const float mx[3]) {
+    float gap = __builtin_huge_valf();
+    if (KIND != KIND_EUCLID && lane < A.n_bumps) {
+        const float4 *__restrict__ q = Bs + (is_deform(KIND) ? DEFORM_F4 : 2) * lane;
+        const float4 b0 = q[0], b1 = q[1];
+        float R;
+        if constexpr (KIND == KIND_GRAPH) {
+            R = sqrt_(b1.z);
+        } else {
+            // spread-scaled cut radius times the largest spread
+            const float cut2 = is_deform(KIND) ? q[2].w : b1.w;
+            R = sqrt_(cut2) * rsqrt_(fminf(fminf(b1.x, b1.y), b1.z));
+        }
+        gap = sqrt_(box_dist2(b0.x, b0.y, b0.z, mn, mx)) - R * 1.0001f;
+    }
+    for (int i = lane; i < A.n_spheres; i += 64) {
+        const float4 s = SPH[i];
+        gap = fminf(gap, sqrt_(box_dist2(s.x, s.y, s.z, mn, mx)) - s.w);
+    }
+    if (lane < A.n_planes) {
+        const float4 pl = PLN[lane];
+        const float c = pl.x * (mn[0] + mx[0]) + pl.y * (mn[1] + mx[1]) + pl.z * (mn[2] + mx[2]) - 2.f * pl.w;
+        const float r = fabsf(pl.x) * (mx[0] - mn[0]) + fabsf(pl.y) * (mx[1] - mn[1]) + fabsf(pl.z) * (mx[2] - mn[2]);
+        gap = fminf(gap, 0.5f * (fabsf(c) - r));
+    }
+    if (lane < A.n_tori) {
+        const float *tp = TOR + 8 * lane;
+        gap = fminf(gap, sqrt_(box_dist2(tp[0], tp[1], tp[2], mn, mx)) - (tp[6] + tp[7]));
+    }
+    return wave_min(gap) * 0.999f;
 }
 
 // ================================================================ the pass
@@ -126,6 +187,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STEP == STE
     // under DP5(4) and learned crossings; fixed-step traces derive t from the
     // step count and neither read nor keep them
     constexpr bool CARRY_T = STEP == STEP_RK45 || SURR;
+    constexpr bool FREE = flat_outside(KIND) && !COUNT && !SURR && !BATCH;
     const int lane = lane_id();
     const int xcd0 = blockIdx.x % N_XCD;
     int *pass_ctr = A.ctr + rti::CTR_PASS0 + pass * rti::CTR_PASS_WORDS;
@@ -254,6 +316,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STEP == STE
                 }
 
                 // ---- per-wave culling window
+                int n_free = 0;  // steps that can be flown free from here
                 if (BATCH ? (!replay && wi == 0) : it % A.K == 0) {
                     // the lane id taken afresh: the table offsets derived from it
                     // are then formed in this block, once per window, instead of
@@ -367,6 +430,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STEP == STE
                             }
                             emask = ballot(en);
                         }
+                        if constexpr (FREE) {
+                            // Nothing in reach of this window: the steps are free flight,
+                            // and so are those of the further windows that end before the
+                            // nearest cut region or object.  There a g-unit velocity has
+                            // Euclidean speed 1 (2% margin), the step's stages included.
+                            if (((KIND == KIND_EUCLID ? 0ull : bmask) | sm[0] | sm[1] | sm[2] | sm[3] | omask) == 0) {
+                                const float D = free_distance<KIND>(A, Bs, SPH, PLN, TOR, lane, pmn, pmx);
+                                const float q = fminf((D - 2e-4f) * rcp_(1.02f * A.h_max), 1e6f);
+                                n_free = max((int)q - 2, A.K) / A.K * A.K;
+                            }
+                        }
                     }
                     if (COUNT && act) {
                         // objects inside this lane's own window (what one ray alone would need)
@@ -400,6 +474,80 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STEP == STE
                         st_bw++;
                     }
                 }
+                if constexpr (FREE) {
+                    // Free flight: a constant velocity, so a step is the three
+                    // two-float additions of a constant increment (fixed steps; 12
+                    // instructions) and its bookkeeping; no acceleration, no chord
+                    // test, no culling until the flight ends.  The bits are those of
+                    // the full steps.
+                    if (n_free > 0) {
+                        y = y + mk(0.f, 0.f, 0.f);
+                        if constexpr (STEP != STEP_RK45) {
+                            const V3<float> dx = free_step<STEP>(y, A.h);
+                            // every active ray of a pass has taken the same number of steps
+                            const int k0 = pass * A.S + it;
+                            if (ballot(act && !finite6(dx, mk(0.f, 0.f, 0.f))) == 0) {
+                                const int n = min(n_free, min(A.S - it, A.n_end - k0));
+                                if (act) {
+                                    for (int j = 0; j < n;) {
+                                        int m = n - j;
+                                        if constexpr (TAPE) {
+                                            const int c = (k0 + j) / A.ckpt_every, o = (k0 + j) - c * A.ckpt_every;
+                                            if (o == 0) write_ckpt(A, id, c, xh, xl, y);
+                                            m = min(m, A.ckpt_every - o);
+                                        }
+                                        j += m;
+#pragma unroll 4
+                                        for (; m > 0; --m) {
+                                            two_sum_add(xh.x, xl.x, dx.x);
+                                            two_sum_add(xh.y, xl.y, dx.y);
+                                            two_sum_add(xh.z, xl.z, dx.z);
+                                        }
+                                    }
+                                    steps += n;
+                                    acc_pass += n;
+                                    if (k0 + n >= A.n_end) {
+                                        write_out(A, qbase + pix, xh + xl, (float)steps * A.h, y, -1, steps);
+                                        if (TAPE) A.tape_hit[(int64_t)(qbase + pix) * rti::TAPE_REC + 11] = __int_as_float(-1);
+                                        alive = false;
+                                    }
+                                }
+                                it += n;
+                                continue;
+                            }
+                        } else {
+                            // adaptive steps: a zero error estimate, so every trial is
+                            // accepted and the step grows by the largest factor
+                            A0 = mk(0.f, 0.f, 0.f);
+                            need_a0 = false;
+                            if (ballot(act && !finite6(A.h_max * y, mk(0.f, 0.f, 0.f))) == 0) {
+                                for (int j = 0; j < n_free; ++j) {
+                                    const bool on = alive && acc_pass < A.S;
+                                    const uint64_t om = ballot(on);
+                                    if (om == 0) break;
+                                    st_lane += __popcll(om);
+                                    if (on) {
+                                        const float hs = fminf(hc, A.t_max - (th + tl));
+                                        att++;
+                                        hc = fminf(hs * 5.0f, A.h_max);
+                                        two_sum_add(xh.x, xl.x, hs * y.x);
+                                        two_sum_add(xh.y, xl.y, hs * y.y);
+                                        two_sum_add(xh.z, xl.z, hs * y.z);
+                                        two_sum_add(th, tl, hs);
+                                        steps++;
+                                        acc_pass++;
+                                        if (steps >= A.max_steps || th + tl >= A.t_max * (1.0f - 1e-6f)) {
+                                            write_out(A, qbase + pix, xh + xl, th + tl, y, -1, steps);
+                                            alive = false;
+                                        }
+                                    }
+                                }
+                                it += n_free;
+                                continue;
+                            }
+                        }
+                    }
+                }
                 // wave statistics (work counting only; the lane count is also DP5's attempt count)
                 if (COUNT || STEP == STEP_RK45) st_lane += __popcll(am);
                 if (COUNT) {
@@ -408,18 +556,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STEP == STE
                     st_ol += __popcll(sm[0]) + __popcll(sm[1]) + __popcll(sm[2]) + __popcll(sm[3]) + __popcll(omask);
                 }
 
-                if (TAPE && act && steps % A.ckpt_every == 0) {
-                    float *ck = A.tape_ck + ((((int64_t)(id >> 6) * A.n_ckpt + steps / A.ckpt_every) * 9) * 64 + (id & 63));
-                    ck[0 * 64] = xh.x;
-                    ck[1 * 64] = xh.y;
-                    ck[2 * 64] = xh.z;
-                    ck[3 * 64] = xl.x;
-                    ck[4 * 64] = xl.y;
-                    ck[5 * 64] = xl.z;
-                    ck[6 * 64] = y.x;
-                    ck[7 * 64] = y.y;
-                    ck[8 * 64] = y.z;
-                }
+                if (TAPE && act && steps % A.ckpt_every == 0) write_ckpt(A, id, steps / A.ckpt_every, xh, xl, y);
                 Acc32<KIND, COUNT, true> acc{Bs, bmask, A.twist_amp, A.twist_theta0, &c_eval, &c_bump};
                 // The step is computed, its chord tested against the scene on
                 // the state before the step, and only then committed: a hit
@@ -472,7 +609,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STEP == STE
                             const float rem = t_lim - ((float)steps * A.h + (th + tl));
                             hstep = rem < A.h * (1.0f - 1e-5f) ? fmaxf(rem, 0.f) : A.h;
                         }
-                        ok = step_rk4<float>(acc, p, y, hstep, dx, dv);
+                        if (FREE && KIND != KIND_EUCLID && bmask == 0) {
+                            // objects but no bump in the window: the same free step
+                            dx = free_step<STEP>(y, A.h);
+                            dv = mk(0.f, 0.f, 0.f);
+                            ok = true;
+                        } else {
+                            ok = step_rk4<float>(acc, p, y, hstep, dx, dv);
+                        }
                     } else {
                         ok = step_euler<float>(acc, p, y, A.h, dx, dv);
                     }
@@ -585,7 +729,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STEP == STE
                             // RK45 lands on t_max up to float rounding of the clipped last step
                             float t = (STEP == STEP_RK45) ? th + tl : (float)steps * A.h + (SURR ? th + tl : 0.f);
                             float t_end = (STEP == STEP_RK45) ? A.t_max * (1.0f - 1e-6f) : A.t_max;
-                            done_miss = steps >= A.max_steps || t >= t_end || clipped;
+                            if constexpr (CARRY_T) done_miss = steps >= A.max_steps || t >= t_end || clipped;
+                            else done_miss = steps >= A.n_end;
                             if constexpr (BATCH) {
                                 if (!replay) {
                                     const V3<float> q = xh + xl;
