@@ -154,9 +154,10 @@ __device__ __forceinline__ V3<float> graph_finish(const GraphAccum &A) {
 // work.  COUNT adds the number of bumps inside their cut sphere at p to
 // *n_in.
 __device__ __forceinline__ void bump_at(const float4 *__restrict__ B, int b, float4 &b0, float4 &b1) {
-    const float4 *q = (const float4 *)((const char *)B + ((unsigned)b << 5));
-    b0 = q[0];
-    b1 = q[1];
+    typedef float f32x8 __attribute__((ext_vector_type(8)));
+    const f32x8 q = *(const f32x8 *)((const char *)B + ((unsigned)b << 5));
+    b0 = make_float4(q[0], q[1], q[2], q[3]);
+    b1 = make_float4(q[4], q[5], q[6], q[7]);
 }
 
 // SREG: the caller's mask is held in scalar registers; a fresh scalar copy
@@ -211,6 +212,56 @@ __device__ __forceinline__ V3<float> graph_accel_f32(const float4 *__restrict__ 
     return graph_finish(A);
 }
 
+// The walk of a window whose points are known to lie inside the cut spheres
+// of the bumps not in cutm: those bumps skip the cut's comparison and select.
+struct GraphWalk {
+    const float4 *__restrict__ B;
+    uint64_t mask, cutm;
+    template <bool FIRST> __device__ __forceinline__ void bump(int b, V3<float> p, V3<float> y, float yy, GraphAccum &A) const {
+        float4 b0, b1;
+        bump_at(B, b, b0, b1);
+        const float dx = p.x - b0.x, dy = p.y - b0.y, dz = p.z - b0.z;
+        const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+        float w = b1.x * exp2_(b0.w * r2);
+        if ((cutm >> b) & 1ull) {
+            __asm__ volatile("" : "+v"(w));  // a branch, not a select of the select
+            w = r2 <= b1.z ? w : 0.0f;
+        }
+        const float dv = fmaf(dz, y.z, fmaf(dy, y.y, dx * y.x));
+        if constexpr (FIRST) {
+            A.gx = -w * dx;
+            A.gy = -w * dy;
+            A.gz = -w * dz;
+            A.q = w * fmaf(b1.y, dv * dv, -yy);
+        } else {
+            A.gx = fmaf(-w, dx, A.gx);
+            A.gy = fmaf(-w, dy, A.gy);
+            A.gz = fmaf(-w, dz, A.gz);
+            A.q = fmaf(w, fmaf(b1.y, dv * dv, -yy), A.q);
+        }
+    }
+    __device__ __forceinline__ bool operator()(V3<float> p, V3<float> y, V3<float> &a) const {
+        uint64_t m = mask;
+        __asm__("" : "+s"(m));
+        if (!m) {
+            a = mk(0.f, 0.f, 0.f);
+            return true;
+        }
+        GraphAccum A;
+        const float yy = dot(y, y);
+        int b = __builtin_ctzll(m);
+        m &= ~(1ull << b);
+        bump<true>(b, p, y, yy, A);
+        while (m) {
+            b = __builtin_ctzll(m);
+            m &= ~(1ull << b);
+            bump<false>(b, p, y, yy, A);
+        }
+        a = graph_finish(A);
+        return true;
+    }
+};
+
 // Graph metric of a sum of anisotropic Gaussians (Eq. 6.1 with three
 // spreads): with d = x - c, S = diag(1/s^2) and w = a exp(-d^T S d / 2),
 //   grad f = -sum_b w_b S d_b,   y^T H y = sum_b w_b ((S d_b . y)^2 - y^T S_b y)
@@ -232,32 +283,137 @@ __device__ __forceinline__ ABump<double> abump_at(const double *__restrict__ B, 
     return {mk(q[0], q[1], q[2]), mk(q[4], q[5], q[6]), q[3], q[7]};
 }
 
+template <class T> struct AnisoAccum {
+    T gx, gy, gz, q;
+};
+// WAVE: a bump no active lane is inside of is left out by the whole wave.
+// Returns whether this lane is inside the bump's cut.
+template <class T, bool WAVE = false>
+__device__ __forceinline__ bool aniso_term(const ABump<T> &P, V3<T> p, V3<T> y, AnisoAccum<T> &A) {
+    const V3<T> d = mk(p.x - P.c.x, p.y - P.c.y, p.z - P.c.z);
+    const V3<T> Sd = mk(P.s.x * d.x, P.s.y * d.y, P.s.z * d.z);
+    const T r2 = dot(d, Sd);
+    if (WAVE && ballot(r2 <= P.cut2) == 0) return false;
+    const T w = r2 <= P.cut2 ? P.a * exp2_(T(-0.5) * log2e_<T>() * r2) : T(0);
+    A.gx -= w * Sd.x;
+    A.gy -= w * Sd.y;
+    A.gz -= w * Sd.z;
+    const T u = dot(Sd, y);
+    const T ySy = P.s.x * y.x * y.x + P.s.y * y.y * y.y + P.s.z * y.z * y.z;
+    A.q += w * (u * u - ySy);
+    return r2 <= P.cut2;
+}
+template <class T> __device__ __forceinline__ V3<T> aniso_finish(const AnisoAccum<T> &A) {
+    const T den = T(1) + A.gx * A.gx + A.gy * A.gy + A.gz * A.gz;
+    const T c = -A.q * rcp_(den);
+    return mk(c * A.gx, c * A.gy, c * A.gz);
+}
+
 template <class T, bool COUNT = false, bool WAVE = false, class PB>
 __device__ __forceinline__ V3<T> graph_aniso_accel(PB B, uint64_t mask, V3<T> p, V3<T> y, unsigned *n_in = nullptr) {
-    T gx = T(0), gy = T(0), gz = T(0), q = T(0);
+    AnisoAccum<T> A{T(0), T(0), T(0), T(0)};
     unsigned n = 0;
     while (mask) {
         const int b = __builtin_ctzll(mask);
         mask &= ~(1ull << b);
-        const auto P = abump_at(B, b);
-        const V3<T> d = mk(p.x - P.c.x, p.y - P.c.y, p.z - P.c.z);
-        const V3<T> Sd = mk(P.s.x * d.x, P.s.y * d.y, P.s.z * d.z);
-        const T r2 = dot(d, Sd);
-        if (WAVE && ballot(r2 <= P.cut2) == 0) continue;
-        const T w = r2 <= P.cut2 ? P.a * exp2_(T(-0.5) * log2e_<T>() * r2) : T(0);
-        if (COUNT) n += r2 <= P.cut2 ? 1u : 0u;
-        gx -= w * Sd.x;
-        gy -= w * Sd.y;
-        gz -= w * Sd.z;
-        const T u = dot(Sd, y);
-        const T ySy = P.s.x * y.x * y.x + P.s.y * y.y * y.y + P.s.z * y.z * y.z;
-        q += w * (u * u - ySy);
+        const bool in = aniso_term<T, WAVE>(abump_at(B, b), p, y, A);
+        if (COUNT) n += in ? 1u : 0u;
     }
     if (COUNT) *n_in += n;
-    const T den = T(1) + gx * gx + gy * gy + gz * gz;
-    const T c = -q * rcp_(den);
-    return mk(c * gx, c * gy, c * gz);
+    return aniso_finish(A);
 }
+
+// ------------------------------------------------ a wave's own bump list
+// For launches too small to hide the latency of the scalar-load walk: a
+// culling window's listed bumps are copied, in index order, to a list in LDS
+// that the wave reads back four at a time.  Four bumps' terms are
+// independent until their sums, the next four are read while these are
+// computed, and the parameters arrive in vector registers.  The list is
+// padded to whole groups with bumps of zero weight.  Same terms, same order
+// of sums as the walks above.
+constexpr int LIST_GROUP = 4;
+constexpr int LIST_F4 = 2 * (MAX_BUMPS + 2 * LIST_GROUP);
+// Lane i brings bump i (b0, b1) if need; returns the number of groups.
+// Called by the whole wave.
+template <bool ANISO>
+__device__ __forceinline__ int list_fill(float4 *list, uint64_t mask, bool need, float4 b0, float4 b1) {
+    __builtin_amdgcn_wave_barrier();
+    if (need) {
+        const int slot = mbcnt64(mask);
+        list[2 * slot] = b0;
+        list[2 * slot + 1] = b1;
+    }
+    const int n = __popcll(mask), lane = lane_id();
+    if (lane < 2 * LIST_GROUP) {
+        // zero amplitude, and a cut below every squared distance
+        list[2 * (n + lane)] = make_float4(0.f, 0.f, 0.f, 0.f);
+        list[2 * (n + lane) + 1] = ANISO ? make_float4(0.f, 0.f, 0.f, -1.0f) : make_float4(0.f, 0.f, -1.0f, 0.f);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    return (n + LIST_GROUP - 1) / LIST_GROUP;
+}
+template <bool ANISO> struct ListSum {
+    GraphAccum G{0.f, 0.f, 0.f, 0.f};
+    AnisoAccum<float> N{0.f, 0.f, 0.f, 0.f};
+    __device__ __forceinline__ void add(float4 b0, float4 b1, V3<float> p, V3<float> y, float yy) {
+        if constexpr (ANISO) {
+            const ABump<float> P{mk(b0.x, b0.y, b0.z), mk(b1.x, b1.y, b1.z), b0.w, b1.w};
+            aniso_term<float>(P, p, y, N);
+        } else {
+            graph_bump_f32(b0, b1, p, y, yy, G);
+        }
+    }
+    __device__ __forceinline__ V3<float> finish() const {
+        if constexpr (ANISO) return aniso_finish(N);
+        else return graph_finish(G);
+    }
+};
+// NB listed bumps held in registers for a whole window.
+template <bool ANISO, int NB> struct HeldAcc {
+    float4 b0[NB], b1[NB];
+    __device__ __forceinline__ HeldAcc(const float4 *__restrict__ B, uint64_t mask) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int b = __builtin_ctzll(mask);
+            mask &= ~(1ull << b);
+            bump_at(B, b, b0[i], b1[i]);
+        }
+    }
+    __device__ __forceinline__ bool operator()(V3<float> p, V3<float> y, V3<float> &a) const {
+        ListSum<ANISO> S;
+        const float yy = dot(y, y);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) S.add(b0[i], b1[i], p, y, yy);
+        a = S.finish();
+        return true;
+    }
+};
+template <bool ANISO> struct ListAcc {
+    const float4 *list;
+    int groups;
+    __device__ __forceinline__ bool operator()(V3<float> p, V3<float> y, V3<float> &a) const {
+        float4 c[2 * LIST_GROUP];
+#pragma unroll
+        for (int i = 0; i < 2 * LIST_GROUP; ++i) c[i] = list[i];
+        ListSum<ANISO> S;
+        const float yy = dot(y, y);
+        const float4 *q = list;
+#pragma unroll 1
+        for (int g = 0; g < groups; ++g) {
+            float4 d[2 * LIST_GROUP];
+            q += 2 * LIST_GROUP;  // (the list is padded by one more group)
+#pragma unroll
+            for (int i = 0; i < 2 * LIST_GROUP; ++i) d[i] = q[i];
+#pragma unroll
+            for (int i = 0; i < LIST_GROUP; ++i) S.add(c[2 * i], c[2 * i + 1], p, y, yy);
+#pragma unroll
+            for (int i = 0; i < 2 * LIST_GROUP; ++i) c[i] = d[i];
+        }
+        a = S.finish();
+        return true;
+    }
+};
 
 // Graph metric of the quadratic f = qx x^2 + qy y^2 + qz z^2 (the example of
 // Sec. 5.1 is (1, 1, -1)): grad f = 2 q x, y^T H y = 2 sum_j q_j y_j^2.

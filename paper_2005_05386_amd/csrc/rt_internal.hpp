@@ -95,6 +95,7 @@ struct TraceArgs {
     float cull_base;    // composed deformations: window motion without displacement, (K+1) h_max 1.02 + 1e-4
     float cull_disp;    // composed deformations: bound on |Phi(x) - x| over all x
     int count;          // instrumented variant
+    int lat_chunks;     // passes of at most this many chunks run the small-launch variant (0: none)
     int batch;          // batched multi-segment intersection
     // buffers
     float *st;             // ray state, Q_NFIELDS x cap

@@ -48,7 +48,7 @@ constexpr double dp_ea(int l) {
 // Each stepper returns the increments (dx, dv) of one step of size h from
 // (p, y); acc(p, y, a) evaluates the acceleration and reports failure.
 template <class T, class F>
-__device__ __forceinline__ bool step_euler(F &acc, V3<T> p, V3<T> y, T h, V3<T> &dx, V3<T> &dv,
+__device__ __forceinline__ bool step_euler(const F &acc, V3<T> p, V3<T> y, T h, V3<T> &dx, V3<T> &dv,
                                            const V3<T> *k1 = nullptr) {
     V3<T> a;
     bool ok = true;
@@ -62,7 +62,7 @@ __device__ __forceinline__ bool step_euler(F &acc, V3<T> p, V3<T> y, T h, V3<T> 
 }
 
 template <class T, class F>
-__device__ __forceinline__ bool step_rk4(F &acc, V3<T> p, V3<T> y, T h, V3<T> &dx, V3<T> &dv,
+__device__ __forceinline__ bool step_rk4(const F &acc, V3<T> p, V3<T> y, T h, V3<T> &dx, V3<T> &dv,
                                          const V3<T> *k1 = nullptr) {
     // Classical RK4 on (x, y): stage s evaluates k_s = a(P_s, Y_s) with
     // (P_0, Y_0) = (p, y) and (P_s, Y_s) = (p + c_s Y_{s-1}, y + c_s k_{s-1}),
@@ -147,6 +147,12 @@ __device__ __forceinline__ void two_sum_add(float &hi, float &lo, float d) {
     hi = s;
 }
 
+template <int STEP, class F>
+__device__ __forceinline__ bool fixed_step(const F &acc, V3<float> p, V3<float> y, float h, V3<float> &dx, V3<float> &dv) {
+    if constexpr (STEP == STEP_RK4) return step_rk4<float>(acc, p, y, h, dx, dv);
+    else return step_euler<float>(acc, p, y, h, dx, dv);
+}
+
 // One RK4 or Euler step where the acceleration is zero at every stage: the
 // velocity stays and the position increment is the steppers' own sum of
 // stage velocities, so the bits are those of the full step.
@@ -165,6 +171,14 @@ __device__ __forceinline__ float box_dist2(float cx, float cy, float cz, const f
     float dx = fmaxf(fmaxf(lo[0] - cx, cx - hi[0]), 0.0f);
     float dy = fmaxf(fmaxf(lo[1] - cy, cy - hi[1]), 0.0f);
     float dz = fmaxf(fmaxf(lo[2] - cz, cz - hi[2]), 0.0f);
+    return dx * dx + dy * dy + dz * dz;
+}
+
+// Squared distance from c to the farthest point of the box.
+__device__ __forceinline__ float box_far2(float cx, float cy, float cz, const float lo[3], const float hi[3]) {
+    const float dx = fmaxf(cx - lo[0], hi[0] - cx);
+    const float dy = fmaxf(cy - lo[1], hi[1] - cy);
+    const float dz = fmaxf(cz - lo[2], hi[2] - cz);
     return dx * dx + dy * dy + dz * dz;
 }
 

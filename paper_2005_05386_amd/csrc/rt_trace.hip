@@ -8,6 +8,9 @@
 //            steps; rays that neither hit nor terminated are compacted into
 //            the other ray queue (per parameter set) for pass p+1, so every
 //            pass starts with full waves;
+//            A window that reaches no bump and no object is flown in closed
+//            form (free flight), the others are marched in a loop of their
+//            own that stops where some lane hits or fails;
 //   refine   one lane per chord hit, in double precision: bisection of the
 //            step fraction on the sign of the hit object's implicit function
 //            along the partial step of the same integrator, then the output.
@@ -145,6 +148,58 @@ __device__ __forceinline__ float free_distance(const TraceArgs &A, const float4 
     return wave_min(gap) * 0.999f;
 }
 
+// ===================================================== segment versus scene
+// First crossing of the chord [x, x + dx] with the listed objects (spheres
+// sm, planes and tori om); p = xh + xl.  Updates (hit_s, hit_id) where a
+// crossing comes before hit_s.
+__device__ __forceinline__ void chord_scan(const uint64_t sm[4], uint64_t om, int ns, int np,
+                                           const float4 *__restrict__ SPH, const float4 *__restrict__ PLN,
+                                           const float *__restrict__ TOR, V3<float> xh, V3<float> xl, V3<float> p,
+                                           V3<float> dx, float &hit_s, int &hit_id) {
+    const float DD = dot(dx, dx);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        uint64_t m = sm[w];
+        while (m) {
+            int b = __builtin_ctzll(m);
+            m &= m - 1;
+            int idx = 64 * w + b;
+            float4 s = SPH[idx];
+            V3<float> o = mk((xh.x - s.x) + xl.x, (xh.y - s.y) + xl.y, (xh.z - s.z) + xl.z);
+            float sc = sphere_chord(s, o, dx, DD);
+            if (sc < hit_s) {
+                hit_s = sc;
+                hit_id = idx;
+            }
+        }
+    }
+    uint64_t m = om;
+    while (m) {
+        int b = __builtin_ctzll(m);
+        m &= m - 1;
+        float F0, F1;
+        int oid;
+        if (b < 8) {
+            float4 pl = PLN[b];
+            F0 = pl.x * p.x + pl.y * p.y + pl.z * p.z - pl.w;
+            F1 = F0 + (pl.x * dx.x + pl.y * dx.y + pl.z * dx.z);
+            oid = ns + b;
+        } else {
+            const float *tp = TOR + 8 * (b - 8);
+            F0 = torus_sdf<float>(tp, p);
+            F1 = torus_sdf<float>(tp, p + dx);
+            oid = ns + np + (b - 8);
+        }
+        if ((F0 > 0.f) != (F1 > 0.f)) {
+            float sc = fminf(fmaxf(F0 / (F0 - F1), 0.f), 1.f);
+            if (sc < hit_s) {
+                hit_s = sc;
+                hit_id = oid;
+            }
+        }
+    }
+}
+
 // ================================================================ the pass
 // Occupancy: 7 waves per SIMD (at most 72 VGPRs) measured fastest for the
 // RK4 graph and twist kernels, 6 for DP5(4) and for rotating deformations
@@ -166,6 +221,20 @@ __device__ __forceinline__ float free_distance(const TraceArgs &A, const float4 
 #ifndef RT_BATCH_WAVES
 #define RT_BATCH_WAVES 6  // the same for the batched-segment variant
 #endif
+#ifndef RT_LAT_WAVES
+#define RT_LAT_WAVES 4  // the same for the small-launch variant
+#endif
+// LAT: the variant for passes of few chunks (graph metrics of bumps, fixed
+// steps; at most lat_chunks, four waves per SIMD).  A wave alone on its SIMD
+// issues a vector instruction every 5 to 6 cycles and waits out every scalar
+// load, so what counts is the length of its own instruction stream: one or two
+// listed bumps stay in registers for the whole window, more are read from the
+// wave's list in LDS four at a time.  128 registers, no spills.  Against the
+// walk (start of this design, then with free flight and the march below, then
+// this): 64x64, one bump 1.25 / 1.09 / 0.91 ms; 86x84, 61 bumps 16.1 / 17.4 /
+// 11.3 ms; 721x403, 12 anisotropic bumps 20.3 / 19.2 / 18.4 ms.  In launches
+// that fill the SIMDs the walk is faster (the list's padding and register
+// copies are issue slots), so those keep it.
 // BATCH: batched multi-segment intersection (Sec. 4.1 proposes testing many
 // segments of the polygon at once).  A culling window's K steps are first
 // marched with no scene test while each lane keeps the bounding box of its
@@ -176,8 +245,8 @@ __device__ __forceinline__ float free_distance(const TraceArgs &A, const float4 
 // A lane that ends by a miss or a failure while marching writes its output
 // only once its box is cleared.  Windows and object lists only bound the
 // work, so the outputs equal the plain kernel's bit for bit.
-template <int KIND, int STEP, bool COUNT, bool SURR = false, bool TAPE = false, bool BATCH = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STEP == STEP_RK45 || KIND == KIND_DEFORM_ROT ? 6 : (BATCH ? RT_BATCH_WAVES : (KIND == KIND_GRAPH && !SURR ? RT_GRAPH_WAVES : RT_PASS_WAVES)), 8))) void k_trace_pass(TraceArgs A, int pass, const float4 *__restrict__ BF,
+template <int KIND, int STEP, bool COUNT, bool SURR = false, bool TAPE = false, bool BATCH = false, bool LAT = false>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LAT ? RT_LAT_WAVES : STEP == STEP_RK45 || KIND == KIND_DEFORM_ROT ? 6 : (BATCH ? RT_BATCH_WAVES : (KIND == KIND_GRAPH && !SURR ? RT_GRAPH_WAVES : RT_PASS_WAVES)), 8))) void k_trace_pass(TraceArgs A, int pass, const float4 *__restrict__ BF,
                                                     const float4 *__restrict__ SPH,
                                                     const float4 *__restrict__ PLN,
                                                     const float *__restrict__ TOR) {
@@ -187,6 +256,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STEP == STE
     // under DP5(4) and learned crossings; fixed-step traces derive t from the
     // step count and neither read nor keep them
     constexpr bool CARRY_T = STEP == STEP_RK45 || SURR;
+    static_assert(!LAT || ((KIND == KIND_GRAPH || KIND == KIND_GANISO) && STEP != STEP_RK45 && !COUNT && !SURR && !BATCH),
+                  "small-launch variant: graph metrics of bumps, fixed steps");
+    float4 *list = nullptr;  // LAT: this wave's bump list
+    if constexpr (LAT) {
+        __shared__ float4 lists[4 * LIST_F4];
+        list = lists + (threadIdx.x >> 6) * LIST_F4;
+    }
+    int groups = 0;  // LAT: groups of the list
+    constexpr bool TIGHT = STEP != STEP_RK45 && !COUNT && !SURR && !BATCH;
     constexpr bool FREE = flat_outside(KIND) && !COUNT && !SURR && !BATCH;
     const int lane = lane_id();
     const int xcd0 = blockIdx.x % N_XCD;
@@ -207,6 +285,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STEP == STE
         pre = wave_incl_scan((cnt + 63) >> 6);
         total_chunks = uniform_i(__shfl(pre, 63));
     }
+    // of the two variants of a later pass one takes it, by its chunk count
+    if (A.lat_chunks > 0 && pass > 0 && (total_chunks <= A.lat_chunks) != LAT) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) pass_ctr[rti::CTR_NCH] = total_chunks;
     // no survivors (the late passes of a surrogate trace): nothing to pull,
     // count or write
@@ -286,6 +366,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STEP == STE
             int acc_pass = 0;
             int it = 0;
             uint64_t bmask = 0, omask = 0, emask = 0;
+            uint64_t cutm = ~0ull;  // TIGHT: listed bumps whose cut some point of the window may be beyond
+            int wend = 0;           // TIGHT: the iteration at which the window ends
             uint64_t sm[4] = {0, 0, 0, 0};
             V3<float> A0 = mk(0.f, 0.f, 0.f);
             bool need_a0 = true;
@@ -296,6 +378,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STEP == STE
             bool replay = false, hold = false, inb = false;
             int wi = 0, wlen = 0, fin = 0, it_m = 0;
             V3<float> bmin = mk(0.f, 0.f, 0.f), bmax = bmin;
+
+            // push chord hits to the refine queue (wave-aggregated); the lane's
+            // registers still hold the state before the step
+            auto push_hits = [&](bool hit, float hit_s, int hit_id, float hstep) {
+                uint64_t hm = ballot(hit);
+                if (hm) {
+                    int base = 0;
+                    if (lane == 0) base = atomicAdd(A.ctr + rti::CTR_REFINE, __popcll(hm));
+                    base = uniform_i(__shfl(base, 0));
+                    if (hit) {
+                        int64_t r = base + mbcnt64(hm);
+                        if constexpr (compact_record(STEP, SURR)) {
+                            // t = steps h and the step is h: 4 float4
+                            float4 *rec = A.rec + 4 * r;
+                            rec[0] = make_float4(xh.x, xh.y, xh.z, xl.x);
+                            rec[1] = make_float4(xl.y, xl.z, y.x, y.y);
+                            rec[2] = make_float4(y.z, hit_s, __int_as_float(hit_id), __int_as_float((int)(qbase + pix)));
+                            rec[3] = make_float4(__int_as_float(steps), __int_as_float((int)(uint32_t)bmask),
+                                                 __int_as_float((int)(bmask >> 32)), 0.f);
+                        } else {
+                            float4 *rec = A.rec + rti::REC_F4 * r;
+                            rec[0] = make_float4(xh.x, xh.y, xh.z, xl.x);
+                            rec[1] = make_float4(xl.y, xl.z, y.x, y.y);
+                            rec[2] = make_float4(y.z, th, hstep, hit_s);
+                            rec[3] = make_float4(__int_as_float(hit_id), __int_as_float((int)(qbase + pix)),
+                                                 __int_as_float(steps), tl);
+                            rec[4] = make_float4(__int_as_float((int)(uint32_t)bmask),
+                                                 __int_as_float((int)(bmask >> 32)), 0.f, 0.f);
+                        }
+                    }
+                }
+            };
 
             for (;;) {
                 bool act = alive && (STEP == STEP_RK45 ? acc_pass < A.S : it < A.S) && !(SURR && parked);
@@ -317,7 +431,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STEP == STE
 
                 // ---- per-wave culling window
                 int n_free = 0;  // steps that can be flown free from here
-                if (BATCH ? (!replay && wi == 0) : it % A.K == 0) {
+                if (BATCH ? (!replay && wi == 0) : (TIGHT ? it >= wend : it % A.K == 0)) {
+                    if constexpr (TIGHT) wend = it + A.K;
                     // the lane id taken afresh: the table offsets derived from it
                     // are then formed in this block, once per window, instead of
                     // being hoisted out of the step loop and spilled (not in the
@@ -382,12 +497,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STEP == STE
                         hi[0] = pmx[0] + m;
                         hi[1] = pmx[1] + m;
                         hi[2] = pmx[2] + m;
-                        bool need = false;
+                        bool need = false, beyond = true;
+                        float4 b0 = make_float4(0.f, 0.f, 0.f, 0.f), b1 = b0;
                         if (KIND == KIND_GRAPH && lane < n_bumps) {
-                            float4 b0 = Bs[2 * lane], b1 = Bs[2 * lane + 1];
+                            b0 = Bs[2 * lane], b1 = Bs[2 * lane + 1];
                             need = box_dist2(b0.x, b0.y, b0.z, lo, hi) <= b1.z;
+                            if constexpr (TIGHT) beyond = box_far2(b0.x, b0.y, b0.z, lo, hi) > b1.z * 0.9999f;
                         } else if (KIND == KIND_GANISO && lane < n_bumps) {
-                            const float4 b0 = Bs[2 * lane], b1 = Bs[2 * lane + 1];
+                            b0 = Bs[2 * lane], b1 = Bs[2 * lane + 1];
                             const float rho = aniso_box_rho(b0, b1, lo, hi);
                             need = rho * rho <= b1.w * 1.00001f;
                         } else if (is_deform(KIND) && lane < n_bumps) {
@@ -396,6 +513,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STEP == STE
                             need = rho * rho <= Bs[DEFORM_F4 * lane + 2].w * 1.00001f;
                         }
                         bmask = ballot(need);
+                        if constexpr (LAT) groups = list_fill<KIND == KIND_GANISO>(list, bmask, need, b0, b1);
+                        else if constexpr (TIGHT && KIND == KIND_GRAPH) cutm = ballot(beyond);
 #pragma unroll
                         for (int w = 0; w < 4; ++w) {
                             bool ns_need = false;
@@ -548,6 +667,118 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STEP == STE
                         }
                     }
                 }
+                if constexpr (TIGHT) {
+                    // ---- the march: steps of this window are computed, tested against the listed
+                    // objects and committed in a loop with one wave-wide question per
+                    // step, until some lane's step is an event (a chord hit, a failed
+                    // acceleration or a non-finite increment).  That step stays
+                    // uncommitted and is finished below.  Every active ray of a pass
+                    // has taken the same number of steps, so the end of the ray is
+                    // the end of the march for all of them.
+                    const int k0 = pass * A.S + it;
+                    const int n = min(wend - it, min(A.S - it, A.n_end - k0));
+                    const bool objs = (sm[0] | sm[1] | sm[2] | sm[3] | omask) != 0;
+                    int j = 0;
+                    bool event = false, fail = false;
+                    float hit_s = 2.f;
+                    int hit_id = -1;
+                    if (act) {
+                        int ck = 0, ck_j = 0;  // TAPE: the next checkpoint and the step before which it is due
+                        if constexpr (TAPE) {
+                            ck = (k0 + A.ckpt_every - 1) / A.ckpt_every;
+                            ck_j = ck * A.ckpt_every - k0;
+                        }
+                        auto checkpoint = [&]() {
+                            if constexpr (TAPE) {
+                                if (j == ck_j) {
+                                    write_ckpt(A, id, ck, xh, xl, y);
+                                    ck++;
+                                    ck_j += A.ckpt_every;
+                                }
+                            }
+                        };
+                        V3<float> dx, dv;
+                        auto march = [&](const auto &accel) {
+                            auto step = [&](V3<float> p, V3<float> &dx, V3<float> &dv) {
+                                const bool ok = fixed_step<STEP>(accel, p, y, A.h, dx, dv);
+                                return ok && finite6(dx, dv);
+                            };
+                            // most windows list no object: a lean loop of their own
+                            if (!objs) {
+#pragma unroll 1
+                                for (; j < n; ++j) {
+                                    checkpoint();
+                                    V3<float> dx, dv;
+                                    if (ballot(!step(xh + xl, dx, dv))) break;
+                                    two_sum_add(xh.x, xl.x, dx.x);
+                                    two_sum_add(xh.y, xl.y, dx.y);
+                                    two_sum_add(xh.z, xl.z, dx.z);
+                                    y = y + dv;
+                                }
+                            }
+#pragma unroll 1
+                            for (; j < n; ++j) {
+                                checkpoint();
+                                const V3<float> p = xh + xl;
+                                if (FREE && KIND != KIND_EUCLID && bmask == 0) {
+                                    // objects but no bump in the window
+                                    dx = free_step<STEP>(y, A.h);
+                                    dv = mk(0.f, 0.f, 0.f);
+                                    fail = !finite6(dx, dv);
+                                } else {
+                                    fail = !step(p, dx, dv);
+                                }
+                                if (!fail) chord_scan(sm, omask, ns, np, SPH, PLN, TOR, xh, xl, p, dx, hit_s, hit_id);
+                                event = ballot(fail || hit_id >= 0) != 0;
+                                if (event) break;
+                                two_sum_add(xh.x, xl.x, dx.x);
+                                two_sum_add(xh.y, xl.y, dx.y);
+                                two_sum_add(xh.z, xl.z, dx.z);
+                                y = y + dv;
+                            }
+                        };
+                        if constexpr (LAT) {
+                            constexpr bool AN = KIND == KIND_GANISO;
+                            const int nb = __popcll(bmask);
+                            if (nb == 1) march(HeldAcc<AN, 1>(Bs, bmask));
+                            else if (nb == 2) march(HeldAcc<AN, 2>(Bs, bmask));
+                            else march(ListAcc<AN>{list, groups});
+                        } else if constexpr (KIND == KIND_GRAPH) {
+                            march(GraphWalk{Bs, bmask, cutm});
+                        } else {
+                            march(Acc32<KIND, false, true>{Bs, bmask, A.twist_amp, A.twist_theta0, nullptr, nullptr});
+                        }
+                        steps += j;
+                        acc_pass += j;
+                        if (event) {
+                            if (fail) {
+                                write_out(A, qbase + pix, xh + xl, (float)steps * A.h, y, -2, steps);
+                                if (TAPE) A.tape_hit[(int64_t)(qbase + pix) * rti::TAPE_REC + 11] = __int_as_float(-1);
+                                alive = false;
+                            } else {
+                                acc_pass++;  // a hit step was integrated: count it
+                                if (hit_id >= 0) {
+                                    alive = false;
+                                } else {
+                                    two_sum_add(xh.x, xl.x, dx.x);
+                                    two_sum_add(xh.y, xl.y, dx.y);
+                                    two_sum_add(xh.z, xl.z, dx.z);
+                                    y = y + dv;
+                                    steps++;
+                                }
+                            }
+                        }
+                        if (alive && steps >= A.n_end) {
+                            write_out(A, qbase + pix, xh + xl, (float)steps * A.h, y, -1, steps);
+                            if (TAPE) A.tape_hit[(int64_t)(qbase + pix) * rti::TAPE_REC + 11] = __int_as_float(-1);
+                            alive = false;
+                        }
+                    }
+                    // (the same for every active lane)
+                    it += __builtin_amdgcn_readlane(j + (event ? 1 : 0), __builtin_ctzll(am));
+                    push_hits(act && hit_id >= 0, hit_s, hit_id, A.h);
+                    continue;
+                }
                 // wave statistics (work counting only; the lane count is also DP5's attempt count)
                 if (COUNT || STEP == STEP_RK45) st_lane += __popcll(am);
                 if (COUNT) {
@@ -627,48 +858,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STEP == STE
                         // ---- segment versus scene, chord [x, x + dx] (a scalar branch:
                         // most wave iterations list no object)
                         if ((!BATCH || replay) && (sm[0] | sm[1] | sm[2] | sm[3] | omask) != 0) {
-                            const float DD = dot(dx, dx);
-#pragma unroll
-                            for (int w = 0; w < 4; ++w) {
-                                uint64_t m = sm[w];
-                                while (m) {
-                                    int b = __builtin_ctzll(m);
-                                    m &= m - 1;
-                                    int idx = 64 * w + b;
-                                    float4 s = SPH[idx];
-                                    V3<float> o = mk((xh.x - s.x) + xl.x, (xh.y - s.y) + xl.y, (xh.z - s.z) + xl.z);
-                                    float sc = sphere_chord(s, o, dx, DD);
-                                    if (sc < hit_s) {
-                                        hit_s = sc;
-                                        hit_id = idx;
-                                    }
-                                }
-                            }
-                            uint64_t m = omask;
-                            while (m) {
-                                int b = __builtin_ctzll(m);
-                                m &= m - 1;
-                                float F0, F1;
-                                int oid;
-                                if (b < 8) {
-                                    float4 pl = PLN[b];
-                                    F0 = pl.x * p.x + pl.y * p.y + pl.z * p.z - pl.w;
-                                    F1 = F0 + (pl.x * dx.x + pl.y * dx.y + pl.z * dx.z);
-                                    oid = ns + b;
-                                } else {
-                                    const float *tp = TOR + 8 * (b - 8);
-                                    F0 = torus_sdf<float>(tp, p);
-                                    F1 = torus_sdf<float>(tp, p + dx);
-                                    oid = ns + np + (b - 8);
-                                }
-                                if ((F0 > 0.f) != (F1 > 0.f)) {
-                                    float sc = fminf(fmaxf(F0 / (F0 - F1), 0.f), 1.f);
-                                    if (sc < hit_s) {
-                                        hit_s = sc;
-                                        hit_id = oid;
-                                    }
-                                }
-                            }
+                            chord_scan(sm, omask, ns, np, SPH, PLN, TOR, xh, xl, p, dx, hit_s, hit_id);
                         }
                         // ---- chord entering an eligible support sphere (SURR)
                         float ent_s = 2.f;
@@ -751,35 +941,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STEP == STE
                     }
                     if (done_fail || done_miss || hit) alive = false;
                 }
-                // ---- push chord hits to the refine queue (wave-aggregated);
-                // the lane's registers still hold the state before the step
-                uint64_t hm = ballot(hit);
-                if (hm) {
-                    int base = 0;
-                    if (lane == 0) base = atomicAdd(A.ctr + rti::CTR_REFINE, __popcll(hm));
-                    base = uniform_i(__shfl(base, 0));
-                    if (hit) {
-                        int64_t r = base + mbcnt64(hm);
-                        if constexpr (compact_record(STEP, SURR)) {
-                            // t = steps h and the step is h: 4 float4
-                            float4 *rec = A.rec + 4 * r;
-                            rec[0] = make_float4(xh.x, xh.y, xh.z, xl.x);
-                            rec[1] = make_float4(xl.y, xl.z, y.x, y.y);
-                            rec[2] = make_float4(y.z, hit_s, __int_as_float(hit_id), __int_as_float((int)(qbase + pix)));
-                            rec[3] = make_float4(__int_as_float(steps), __int_as_float((int)(uint32_t)bmask),
-                                                 __int_as_float((int)(bmask >> 32)), 0.f);
-                        } else {
-                            float4 *rec = A.rec + rti::REC_F4 * r;
-                            rec[0] = make_float4(xh.x, xh.y, xh.z, xl.x);
-                            rec[1] = make_float4(xl.y, xl.z, y.x, y.y);
-                            rec[2] = make_float4(y.z, th, hstep, hit_s);
-                            rec[3] = make_float4(__int_as_float(hit_id), __int_as_float((int)(qbase + pix)),
-                                                 __int_as_float(steps), tl);
-                            rec[4] = make_float4(__int_as_float((int)(uint32_t)bmask),
-                                                 __int_as_float((int)(bmask >> 32)), 0.f, 0.f);
-                        }
-                    }
-                }
+                push_hits(hit, hit_s, hit_id, hstep);
                 if constexpr (SURR) {
                     // ---- queue the rays that parked on a support sphere in this step
                     const bool now = park_b >= 0;
@@ -1223,6 +1385,17 @@ hipError_t launch_pass(const TraceArgs &a, const rti::DeviceData &d, int p, int 
                                p, d.bump_f, d.sph_f, d.pln_f, d.tor_f);
             return hipGetLastError();
         }
+    }
+    if constexpr ((KIND == KIND_GRAPH || KIND == KIND_GANISO) && STEP != STEP_RK45 && !SURR) {
+        // the small-launch variant: the first pass by its known chunk count, a
+        // later pass by the survivors (each variant reads the count and only
+        // one proceeds; frames that are small to begin with need one launch)
+        const int chunks = a.n_sets * a.tiles_x * a.tiles_y;
+        if (!a.count && a.lat_chunks > 0 && (p > 0 || chunks <= a.lat_chunks))
+            hipLaunchKernelGGL((k_trace_pass<KIND, STEP, false, false, TAPE, false, true>),
+                               dim3(std::min(grid, (a.lat_chunks + 3) / 4)), dim3(256), 0, s, a, p, d.bump_f, d.sph_f,
+                               d.pln_f, d.tor_f);
+        if (!a.count && a.lat_chunks > 0 && chunks <= a.lat_chunks) return hipGetLastError();
     }
     if (a.count)
         hipLaunchKernelGGL((k_trace_pass<KIND, STEP, true, SURR, TAPE>), dim3(grid), dim3(256), 0, s, a, p,

@@ -1,0 +1,132 @@
+"""The pass kernel's fast forms against its work-counting variant
+(RT_FLAG_COUNT_WORK), which takes every step in full, tests every window and
+runs none of them: free flight through windows that reach nothing, the march,
+and the small-launch variant with its per-wave bump lists.  The outputs must
+be equal bit for bit.  Every test names its case on stdout before touching
+the GPU."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+FIELDS = ("hit", "t", "id", "dir", "steps")
+
+
+@pytest.fixture(scope="module")
+def rt():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2005_05386_amd import rt as _rt
+    return _rt
+
+
+def trace(rt, wl, rule):
+    tr = rt.Tracer(0)
+    tr.set_metric(wl["metric"])
+    tr.set_scene(wl["scene"])
+    out = tr.trace(wl["camera"], rule, rule["max_steps"])
+    tr.sync()
+    return rt.to_numpy(out), tr.stats()
+
+
+def same(rt, wl, rule):
+    g, s = trace(rt, wl, rule)
+    c, sc = trace(rt, wl, dict(rule, flags=rt.FLAG_COUNT_WORK))
+    for k in FIELDS:
+        assert np.array_equal(g[k], c[k]), k
+    for k in ("rays", "ray_steps", "attempts", "refined"):
+        assert s[k] == sc[k], k
+    return g
+
+
+def few(n):
+    """The headline frame with its first n bumps (list lengths 0, 1, 2, whole
+    groups of four and remainders)."""
+    wl = W.get("bumps16_1080p")
+    wl["metric"] = dict(wl["metric"], bumps=wl["metric"]["bumps"][:, :n])
+    return wl
+
+
+def aniso(n):
+    wl = W.get("abumps16_1080p")
+    wl["metric"] = dict(wl["metric"], abumps=wl["metric"]["abumps"][:, :n])
+    return wl
+
+
+CASES = {
+    "bumps16": (lambda: W.get("bumps16_1080p"), {}),
+    "euler": (lambda: W.get("bumps16_1080p"), {"kind": W.EULER}),
+    "rk45": (lambda: W.get("bumps16_1080p_rk45"), {}),
+    "rk45_passes": (lambda: W.get("bumps16_1080p_rk45"), {"pass_steps": 100, "cull_every": 3}),
+    "passes": (lambda: W.get("bumps16_1080p"), {"pass_steps": 50}),
+    "window1": (lambda: W.get("bumps16_1080p"), {"cull_every": 1}),
+    "window256": (lambda: W.get("bumps16_1080p"), {"cull_every": 256, "pass_steps": 300}),
+    "t_max": (lambda: W.get("bumps16_1080p"), {"t_max": 7.003}),
+    "no_bumps": (lambda: few(0), {}),
+    "bump1": (lambda: few(1), {}),
+    "bumps2": (lambda: few(2), {}),
+    "bumps5": (lambda: few(5), {}),
+    "bumps64": (lambda: W.get("surrogate_64_4k"), {}),
+    "aniso": (lambda: W.get("abumps16_1080p"), {}),
+    "aniso3": (lambda: aniso(3), {"kind": W.EULER}),
+    "deform": (lambda: W.get("deform16_1080p"), {}),
+    "rdeform": (lambda: W.get("rdeform16_1080p"), {"pass_steps": 256}),
+    "twist": (lambda: W.get("twist_4k"), {}),
+    "quadric": (lambda: W.get("quadric_1080p"), {}),
+    "isolated": (lambda: W.get("surrogate_isolated_4k"), {}),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+@pytest.mark.parametrize("size", [(61, 43), (200, 113)])
+def test_equals_counted_trace(rt, name, size):
+    print("[gpu-case] fast forms == counted variant:", name, size, flush=True)
+    make, rule = CASES[name]
+    wl = W.with_size(make(), *size)
+    same(rt, wl, dict(wl["rule"], **rule))
+
+
+@pytest.mark.parametrize("size", [(512, 512), (520, 512)])
+def test_both_sides_of_the_small_launch_line(rt, size):
+    """4096 chunks run the small-launch variant from the first pass on; 4160
+    start in the other and hand the later passes over as rays end."""
+    print("[gpu-case] small-launch line", size, flush=True)
+    wl = W.with_size(W.get("bumps16_1080p"), *size)
+    same(rt, wl, dict(wl["rule"], pass_steps=128, h=0.02, max_steps=1000))
+
+
+def test_empty_world(rt):
+    """Nothing to reach at all: every ray flies free to the end."""
+    print("[gpu-case] empty world", flush=True)
+    wl = W.with_size(few(0), 40, 24)
+    wl["scene"] = W.scene()
+    for kind in (W.RK4, W.EULER, W.RK45):
+        g = same(rt, wl, dict(wl["rule"], kind=kind, h_max=0.02))
+        assert (g["id"] == -1).all()
+
+
+def test_taped_trace_equals_plain(rt):
+    """Checkpoints inside free flights and marches leave the trace as it is,
+    and the tape does not depend on the window or pass length."""
+    import torch
+    print("[gpu-case] taped trace", flush=True)
+    wl = W.with_size(W.get("bumps16_1080p"), 72, 45)
+    rule = dict(wl["rule"], h=0.02, max_steps=1000)
+    tr = rt.Tracer(0)
+    tr.set_metric(wl["metric"])
+    tr.set_scene(wl["scene"])
+    ref = rt.to_numpy(tr.trace(wl["camera"], rule, 1000))
+    tapes = []
+    for K, S in ((16, 1000), (5, 64), (256, 333)):
+        nbytes = tr.tape_bytes(wl["camera"], 1000, 7)
+        tape = torch.zeros(nbytes // 4 + 1, dtype=torch.float32, device="cuda")
+        out, tape = tr.trace_fwd_ckpt(wl["camera"], dict(rule, cull_every=K, pass_steps=S), 1000, 7, tape=tape)
+        tr.sync()
+        out = rt.to_numpy(out)
+        for k in FIELDS:
+            assert np.array_equal(out[k], ref[k]), k
+        tapes.append(tape.cpu().numpy())
+    assert np.array_equal(tapes[0], tapes[1], equal_nan=True) and np.array_equal(tapes[0], tapes[2], equal_nan=True)
