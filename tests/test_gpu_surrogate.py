@@ -69,6 +69,20 @@ def test_crossing_data_random_mode(env):
     assert np.all(aux[..., 1] >= 0)                        # every ray left the sphere
 
 
+@pytest.mark.parametrize("n_per", [1, 63, 64, 65, 255, 257, 1000])
+def test_crossing_samples_do_not_depend_on_the_count(env, n_per):
+    """Every sample of every shape is generated, whatever the remainders of
+    the launch: unstratified draws are the same samples in a larger batch."""
+    rt, surrogate, torch, tr = env
+    say("crossing data, %d per shape" % n_per)
+    kappa, scale = [0.4, 1.1, 2.0, 2.9, 0.7], [1.0, 0.5, 0.3, 0.2, 0.1]
+    big = tr.surrogate_gen(kappa, scale, 1100, 0.02, seed=9, mode=0)
+    part = tr.surrogate_gen(kappa, scale, n_per, 0.02, seed=9, mode=0)
+    tr.sync()
+    for b, a in zip(big, part):
+        assert torch.equal(b[:, :n_per], a)
+
+
 @pytest.mark.parametrize("mode", [4, 6])
 def test_crossing_data_stratified_mode(env, mode):
     """Stratified draws (the training loop's): sample i of n takes its
