@@ -81,10 +81,6 @@ struct rt_ctx {
     size_t surr_sb_bytes = 0;
     bool surr_sb_dirty = true;
     int surr_eligible = 0;
-    void *d_grp_ctl = nullptr;         // control block of rt_mlp_fwd_grouped
-    size_t grp_ctl_bytes = 0;
-    void *d_grp_w = nullptr;           // its aligned copy of the networks
-    size_t grp_w_bytes = 0;
     void *d_xbuf = nullptr;            // crossing queues, sized for xbuf_cap rays
     int64_t xbuf_cap = 0;
     void *d_ibuf = nullptr;            // illumination workspace, sized for ibuf_cap pixels
@@ -188,8 +184,6 @@ void rt_destroy(rt_ctx *c) {
         (void)hipFree(c->d_surr_sb);
         (void)hipFree(c->d_xbuf);
         (void)hipFree(c->d_ibuf);
-        (void)hipFree(c->d_grp_ctl);
-        (void)hipFree(c->d_grp_w);
         for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
     }
     delete c;
@@ -1214,7 +1208,7 @@ rt_status rt_mlp_fwd(rt_ctx *c, int n_nets, int batch, const uint16_t *w_bf16, c
     if (st != RT_OK) return st;
     rti::MlpWork w;
     rti::mlp_work_carve(work, n_nets, batch, w);
-    hipError_t e = rti::mlp_forward(n_nets, batch, (const __bf16 *)w_bf16, params, x, y, w, true, (hipStream_t)stream);
+    hipError_t e = rti::mlp_forward(n_nets, batch, params, x, y, w, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(c, e, "kernel launch (mlp forward)");
     return RT_OK;
 }
@@ -1224,53 +1218,33 @@ rt_status rt_mlp_fwd_grouped(rt_ctx *c, int n_nets, const int32_t *rows, const u
     if (!c) return RT_EINVAL;
     if (n_nets < 1 || n_nets > rti::MAX_NETS) return fail(c, RT_EINVAL, "rt_mlp_fwd_grouped: n_nets must be in 1..64");
     if (!rows || !w_bf16 || !params || !x || !y) return fail(c, RT_EINVAL, "rt_mlp_fwd_grouped: NULL argument");
-    std::vector<int> ctl(rti::CTR_SURR_WORDS, 0);
+    rti::GroupCtl ctl{};
     int64_t tot = 0, tiles = 0;
     for (int g = 0; g < n_nets; ++g) {
         if (rows[g] < 0) return fail(c, RT_EINVAL, "rt_mlp_fwd_grouped: negative row count");
-        ctl[rti::XC_ROW + g] = (int)tot;
-        ctl[rti::XC_TILE + g] = (int)tiles;
+        ctl.w[rti::XC_ROW + g] = (int)tot;
+        ctl.w[rti::XC_TILE + g] = (int)tiles;
         tot += rows[g];
         tiles += (rows[g] + 63) / 64;
         if (tot > (1LL << 30)) return fail(c, RT_EINVAL, "rt_mlp_fwd_grouped: too many rows");
     }
     for (int g = n_nets; g <= 64; ++g) {
-        ctl[rti::XC_ROW + g] = (int)tot;
-        ctl[rti::XC_TILE + g] = (int)tiles;
+        ctl.w[rti::XC_ROW + g] = (int)tot;
+        ctl.w[rti::XC_TILE + g] = (int)tiles;
     }
     if (c->host_only) return fail(c, RT_ESTATE, "rt_mlp_fwd_grouped: host-only context");
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return hip_fail(c, e, "hipSetDevice");
-    rt_status st = sync_last(c);
-    if (st != RT_OK) return st;
-    if ((st = upload(c, &c->d_grp_ctl, &c->grp_ctl_bytes, ctl.data(), ctl.size() * sizeof(int))) != RT_OK) return st;
     if (tiles == 0) return RT_OK;
-    // the kernel reads weight rows with 128-bit loads: copy them to 16-byte
-    // aligned rows of MLP_P_PAD values
-    const size_t P = RT_MLP_PARAMS, PP = rti::MLP_P_PAD;
-    const size_t need = (size_t)n_nets * PP * 6;
-    if (c->grp_w_bytes < need) {
-        (void)hipFree(c->d_grp_w);
-        c->d_grp_w = nullptr;
-        c->grp_w_bytes = 0;
-        if ((e = hipMalloc(&c->d_grp_w, need)) != hipSuccess) return hip_fail(c, e, "hipMalloc (grouped mlp)");
-        c->grp_w_bytes = need;
-    }
-    char *gw = (char *)c->d_grp_w;
-    hipStream_t hs = (hipStream_t)stream;
-    if ((e = hipMemcpy2DAsync(gw, PP * 2, w_bf16, P * 2, P * 2, n_nets, hipMemcpyDeviceToDevice, hs)) != hipSuccess ||
-        (e = hipMemcpy2DAsync(gw + (size_t)n_nets * PP * 2, PP * 4, params, P * 4, P * 4, n_nets,
-                              hipMemcpyDeviceToDevice, hs)) != hipSuccess)
-        return hip_fail(c, e, "hipMemcpy2DAsync (grouped mlp)");
     rti::SurrArgs S{};
     S.n_nets = n_nets;
-    S.stride = (int64_t)PP;
-    S.wb = (const __bf16 *)gw;
-    S.params = (const float *)(gw + (size_t)n_nets * PP * 2);
+    S.stride = RT_MLP_PARAMS;
+    S.wb = (const __bf16 *)w_bf16;
+    S.params = params;
     S.xin = (float *)x;
     S.xout = y;
     int blocks = (int)std::min<int64_t>(tiles, 2 * (int64_t)c->n_cu);
-    e = rti::launch_mlp_grouped((const int *)c->d_grp_ctl, S, blocks, (hipStream_t)stream);
+    e = rti::launch_mlp_rows(ctl, S, blocks, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(c, e, "kernel launch (grouped mlp)");
     c->last_stream = (hipStream_t)stream;
     c->traced = true;
@@ -1431,7 +1405,7 @@ rt_status rt_surrogate_train(rt_ctx *c, int n_nets, const float *kappa, const fl
                 return hip_fail(c, e, "kernel launch (surrogate training data)");
         }
         const float *Xs = X + (size_t)j * nb * 6, *Ys = Y + (size_t)j * nb * 6;
-        if ((e = rti::mlp_forward(n_nets, batch, (const __bf16 *)w_bf16, params, Xs, PRED, w, true, s)) !=
+        if ((e = rti::mlp_forward(n_nets, batch, params, Xs, PRED, w, s)) !=
                 hipSuccess ||
             (e = rti::launch_mse_grad(PRED, Ys, DY, (int64_t)nb * 6, batch, part, 64, s)) != hipSuccess ||
             (e = rti::mlp_backward(n_nets, batch, (const __bf16 *)w_bf16, params, DY, G, w, s)) != hipSuccess ||

@@ -217,61 +217,32 @@ constexpr int ILLUM_RETRY_ROUNDS = 3;
 constexpr int ILLUM_CONT_STAGES = 8;
 hipError_t launch_illum(const IllumArgs &a, const DeviceData &d, int grid, hipStream_t s);
 // ------------------------------------------------------------- MLP (BF16)
-enum Epi { EPI_NONE = 0, EPI_HIDDEN = 1, EPI_BIAS = 2, EPI_DSILU = 3 };
-
-// Grouped GEMM C = A B (see rt_mlp.hip).  Group g offsets every operand by
-// its group stride; with rows != NULL group g has rows[g] rows starting at
-// row row_off[g] of A and C (A's group stride is then normally 0).
-struct GemmArgs {
-    const __bf16 *A;
-    int64_t a_g;
-    int64_t sam, sak;
-    const __bf16 *B;
-    int64_t b_g;
-    int64_t sbk, sbn;
-    int M, N, K;
-    const int *rows;
-    const int *row_off;
-    int epi;
-    const float *bias;
-    int64_t bias_g;
-    float *Cf;
-    int64_t cf_g, ldcf;
-    __bf16 *Cb;
-    int64_t cb_g, ldcb;
-    const float *Z;
-    int64_t z_g, ldz;
-};
-
 // Per-network parameter layout (floats / bf16 values).
 constexpr int64_t MLP_H = 256, MLP_IN = 6, MLP_OUT = 6;
 constexpr int64_t OFF_W1 = 0, OFF_B1 = OFF_W1 + MLP_H * MLP_IN, OFF_W2 = OFF_B1 + MLP_H, OFF_B2 = OFF_W2 + MLP_H * MLP_H,
                   OFF_W3 = OFF_B2 + MLP_H, OFF_B3 = OFF_W3 + MLP_H * MLP_H, OFF_W4 = OFF_B3 + MLP_H,
                   OFF_B4 = OFF_W4 + MLP_OUT * MLP_H, MLP_P = OFF_B4 + MLP_OUT;
 
-// Activation workspace of a forward pass kept for the backward.
+// Workspace of a forward pass kept for the backward: rows in whole tiles of
+// 64, T = tiles per network, Bp = 64 T.
 struct MlpWork {
-    float *xf;        // [n][B][6] inputs (FP32 first layer)
-    float *z[3];      // [n][B][256] pre-activations
-    __bf16 *h[3];     // [n][B][256] activations (bf16, high part)
-    __bf16 *hl[3];    // [n][B][256] low parts: h - hi, rounded to bf16
-    __bf16 *dyb;      // [n][B][6]
-    float *dzf[2];    // [n][B][256]
-    __bf16 *dzb[2];   // [n][B][256]
-    float *part;      // colsum partials [n][ceil(B/256)][256]
+    float *xf;             // [n][Bp][6] inputs
+    float *z2;             // [n][T] tiles of pre-activations of layer 2, accumulator order
+    float *z3;             // [n][Bp][256] pre-activations of layer 3
+    __bf16 *h1t, *h2t;     // [n][T][256][64] activations (bf16, high part)
+    __bf16 *dz2t, *dz3t;   // [n][T][256][64] back-propagated signals
+    __bf16 *wt;            // [n][2][256 * 256] W2, W3 in the backward products' fragment order
+    float *part1, *part4;  // [n][ceil(B/32)][7][256] partial gradients of the FP32 layers
+    float *cs2, *cs3;      // [n][T][256] partial bias gradients
 };
 size_t mlp_work_bytes(int n_nets, int batch);
 void mlp_work_carve(void *base, int n_nets, int batch, MlpWork &w);
-hipError_t mlp_forward(int n_nets, int batch, const __bf16 *wb, const float *params, const float *x, float *y,
-                       const MlpWork &w, bool keep, hipStream_t s);
+hipError_t mlp_forward(int n_nets, int batch, const float *params, const float *x, float *y, const MlpWork &w,
+                       hipStream_t s);
 hipError_t mlp_backward(int n_nets, int batch, const __bf16 *wb, const float *params, const float *dy, float *grad,
                         const MlpWork &w, hipStream_t s);
-hipError_t launch_gemm(const GemmArgs &G, int groups, int max_rows, hipStream_t s);
-hipError_t launch_colsum(const float *X, int64_t xg, int rows, int N, int groups, float *part, float *out,
-                         int64_t out_g, hipStream_t s);
 hipError_t launch_adamw(float *p, __bf16 *pb, float *m, float *v, const float *g, int64_t n, float lr, float b1,
                         float b2, float eps, float wd, int step, hipStream_t s);
-hipError_t launch_to_bf16(const float *x, __bf16 *y, int64_t n, hipStream_t s);
 hipError_t launch_mse_grad(const float *y, const float *t, float *dy, int64_t n, int batch, float *part, int nblk,
                            hipStream_t s);
 
@@ -287,6 +258,10 @@ hipError_t launch_cross_cal(const float *X, const float *P, const float *Y, cons
 // Fused grouped MLP forward: ctl holds per-network row offsets at XC_ROW
 // and tile offsets at XC_TILE; uses S.wb, S.params, S.stride, S.n_nets,
 // S.xin, S.xout.
+struct GroupCtl {
+    int w[XC_TILE + 65];
+};
+hipError_t launch_mlp_rows(const GroupCtl &C, const SurrArgs &S, int blocks, hipStream_t s);
 hipError_t launch_mlp_grouped(const int *ctl, const SurrArgs &S, int blocks, hipStream_t s);
 hipError_t launch_surr_stage(const TraceArgs &a, const SurrArgs &S, const float4 *bump_f, int pass, int mlp_blocks,
                              hipStream_t s);

@@ -1,26 +1,28 @@
 // Kernels of the surrogate MLP (6 -> 256 -> 256 -> 256 -> 6, SiLU): the
 // first layer (K = 6) and the output layer (N = 6) in FP32 on the vector
 // units (1% of the FLOPs), the two 256x256 products on the BF16 matrix
-// cores with FP32 accumulation, column sums for bias gradients, and the
-// AdamW update.
+// cores with FP32 accumulation, and the AdamW update.
 //
 // Forward products use three-term split bf16: a value v is carried as
 // hi = bf16(v) and lo = bf16(v - hi), and A B is accumulated as
-// Ah Bh + Ah Bl + Al Bh (the dropped Al Bl is ~2^-16 relative), which gives
+// Al Bh + Ah Bl + Ah Bh (the dropped Al Bl is ~2^-16 relative), which gives
 // the network near-FP32 accuracy; plain bf16 forward products leave a
 // relative error floor of about 1e-3 in the learned map.  The backward
 // products (signals and weight gradients) stay single bf16.
 //
-// GEMM: for every group g (one network), C[m][n] = sum_k A(m,k) B(k,n) with
-// A(m,k) = A[a_off(g) + m*sam + k*sak], B(k,n) = B[b_off(g) + k*sbk + n*sbn]
-// (bf16), arbitrary strides so that transposed operands need no copies.
-// A 256-thread workgroup computes a 64x64 tile of C: the 64x32 A slice and
-// 32x64 B slice of each K step are staged in LDS (zero-filled outside the
-// matrix; the next slice is read into registers during the products), then
-// each wave accumulates a 32x32 block with four v_mfma_f32_16x16x32_bf16
-// per step.  Lane l of a 16x16x32 MFMA supplies
-// A[l%16][8(l/16) .. 8(l/16)+7] and B[8(l/16) .. +7][l%16] and receives
-// D[4(l/16) + j][l%16], j = 0..3.
+// A training step is four launches around the update: the forward and the
+// backward pass each take a 64-row tile of one network through all layers
+// in one workgroup, with the tile's activations or signals in LDS, then the
+// weight gradients of both 256x256 layers, then the sums of the FP32
+// layers' and biases' row partials.  What crosses memory between them is what
+// the weight gradients and the backward pass need: z2, z3 (FP32) and, as
+// tiles with the row running fastest, h1, h2, dz2, dz3 (bf16), which is
+// the order in which a lane of the weight-gradient product takes them.
+// 64 networks x 1024 rows, per training step without the data generator:
+// 680 us with one launch per layer and reduction, @STEP@ us with these.
+//
+// Lane l of a 16x16x32 MFMA supplies A[l%16][8(l/16) .. 8(l/16)+7] and
+// B[8(l/16) .. +7][l%16] and receives D[4(l/16) + j][l%16], j = 0..3.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -31,15 +33,27 @@
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+// The networks are MLP_P values apart, an even but not a multiple of four:
+// 16-byte accesses at the alignment of the element.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef __bf16 bf16x8u __attribute__((ext_vector_type(8), aligned(2)));
+
+constexpr int TM = 64;         // rows of a tile
+constexpr int H = rti::MLP_H;  // 256
+constexpr int AROW = 264;      // bf16 row of an activation tile in LDS (528 bytes: fragment reads spread over the banks)
+constexpr int NT = 512;        // threads of a tile's workgroup: eight waves of 32 output columns each
+constexpr int FROW = 260;      // FP32 row of a tile in LDS
+// Rows per partial sum of the FP32 layers' weight gradients.
+constexpr int GRAD_ROWS = 32;
 
 // XCD-aware tile order.  Workgroups go to the 8 XCDs round-robin by their
-// linear id, and each XCD has its own L2.  Tiles are numbered with the
-// column tile fastest, then the row tile, then the group (network), and
-// XCD k takes the k-th contiguous eighth of that order: the column tiles of
-// one row tile run one after another on the same XCD (the row slice of A
-// is fetched from memory once), and a network's weights are read by one
-// XCD only.  The grid is 1-D, 8 * ceil(tiles / 8) workgroups; returns false
-// for the padding.
+// linear id, and each XCD has its own L2.  Tiles are numbered with x
+// fastest, then y, then z, and XCD k takes the k-th contiguous eighth of that
+// order, so that one network's weights and operands are read by one XCD.
+// The grid is 1-D, 8 * ceil(tiles / 8) workgroups; returns false for the
+// padding.
 __device__ __forceinline__ bool xcd_tile(int nx, int ny, int nz, int &x, int &y, int &z) {
     const int T = nx * ny * nz;
     const int per = (T + 7) / 8;
@@ -52,634 +66,553 @@ __device__ __forceinline__ bool xcd_tile(int nx, int ny, int nz, int &x, int &y,
     return true;
 }
 inline unsigned xcd_grid(int nx, int ny, int nz) { return 8u * (unsigned)(((int64_t)nx * ny * nz + 7) / 8); }
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ float silu(float z) { return z / (1.0f + __expf(-z)); }
+// 1 / (1 + exp(-z)): the hardware reciprocal with one Newton step (the tiles
+// are bound by vector issue, and a full division is twice the instructions).
+// The exponent stops at 2^120, where the result is below any float that z
+// could still lift to a normal product.
+__device__ __forceinline__ float sigmoid(float z) {
+    const float d = 1.0f + __builtin_amdgcn_exp2f(fminf(-1.4426950408889634f * z, 120.0f));
+    const float r = __builtin_amdgcn_rcpf(d);
+    return fmaf(r, fmaf(-d, r, 1.0f), r);
+}
+__device__ __forceinline__ float silu(float z) { return z * sigmoid(z); }
 __device__ __forceinline__ float dsilu(float z) {
-    float s = 1.0f / (1.0f + __expf(-z));
+    const float s = sigmoid(z);
     return s * (1.0f + z * (1.0f - s));
 }
 
-// Operand staging layouts of the backward GEMM: L_GEN reads element by
-// element through both strides (any shape); L_KC has unit stride along k
-// (16-byte loads of 8 consecutive k); L_MC has unit stride along the row
-// index m (or n for B): 16-byte loads of 8 consecutive rows at one k,
-// written transposed into LDS; L_MC4 is L_MC with four 4-byte loads for
-// operands whose group stride is only even.  The vector layouts need
-// 8 | M, N, K and the other stride, 8 | the group stride and 16-byte
-// aligned bases (2 | and 4-byte aligned for L_MC4).
-enum { L_GEN = 0, L_KC = 1, L_MC = 2, L_MC4 = 3 };
-
-// Stage a 64 x 32 (row, k) slice of X(row, k) = X[row*srow + k*sk] into
-// S[row][k]; rows >= R and k >= K are zero.
-template <int L>
-__device__ __forceinline__ void stage_load(const __bf16 *__restrict__ X, int64_t srow, int64_t sk, int r0, int R,
-                                           int k0, int K, int tid, bf16x8 &v) {
-    if constexpr (L == L_KC) {
-        const int r = r0 + (tid >> 2), k = k0 + (tid & 3) * 8;
-        if (r < R && k < K) {
-            v = *(const bf16x8 *)(X + (int64_t)r * srow + k);
-        } else {
+__device__ __forceinline__ void split8(const float *v, bf16x8 &hi, bf16x8 &lo) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = (__bf16)0.0f;
-        }
-    } else if constexpr (L == L_MC || L == L_MC4) {
-        const int k = k0 + (tid >> 3), r = r0 + (tid & 7) * 8;
-        if (r < R && k < K) {
-            if constexpr (L == L_MC) {
-                v = *(const bf16x8 *)(X + (int64_t)k * sk + r);
-            } else {
-                const uint32_t *w = (const uint32_t *)(X + (int64_t)k * sk + r);
-                typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-                const u32x4 u = {w[0], w[1], w[2], w[3]};
-                v = __builtin_bit_cast(bf16x8, u);
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = (__bf16)0.0f;
-        }
-    } else {
-        const int r = r0 + (tid >> 2), kc = k0 + (tid & 3) * 8;
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            v[e] = (r < R && kc + e < K) ? X[(int64_t)r * srow + (int64_t)(kc + e) * sk] : (__bf16)0.0f;
+    for (int e = 0; e < 8; ++e) {
+        const __bf16 h = (__bf16)v[e];
+        hi[e] = h;
+        lo[e] = (__bf16)(v[e] - (float)h);
     }
 }
 
-template <int L>
-__device__ __forceinline__ void stage_store(__bf16 (*S)[40], int tid, const bf16x8 &v) {
-    if constexpr (L == L_MC || L == L_MC4) {
-        const int k = tid >> 3, r = (tid & 7) * 8;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) S[r + e][k] = v[e];
-    } else {
-        *(bf16x8 *)&S[tid >> 2][(tid & 3) * 8] = v;
-    }
+// Sum over the wave by the butterfly l ^ 32, 16, 8, 4, 2, 1, without LDS: half
+// and row swaps, then rotations within rows of 16 (after the l ^ 8 step the
+// rotation by 4 meets the same values as l ^ 4).
+template <int CTRL> __device__ __forceinline__ float dpp_add(float v) {
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float wave_sum(float v) {
+    const unsigned u = __float_as_uint(v);
+    const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const unsigned w = __float_as_uint(v);
+    const auto b = __builtin_amdgcn_permlane16_swap(w, w, false, false);
+    v = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+    v = dpp_add<0x128>(v);  // row rotation by 8
+    v = dpp_add<0x124>(v);  // row rotation by 4
+    v = dpp_add<0x4E>(v);   // quad permutation l ^ 2
+    return dpp_add<0xB1>(v);  // l ^ 1
 }
 
-// VEC: every tile is whole and the outputs (and Z) are 16-byte aligned with
-// row strides a multiple of 8 elements; the epilogue then goes through LDS
-// and every thread stores 16 consecutive values of one row with 16-byte
-// stores (EPI_NONE and EPI_DSILU).
-template <int LA, int LB, bool VEC = false>
-__global__ __launch_bounds__(256) void k_gemm(rti::GemmArgs G, int ntx, int nty, int ntz) {
-    // one LDS block: the two staging arrays, reused for the output tile
-    __shared__ __attribute__((aligned(16))) float smem[VEC ? 64 * 68 : 64 * 40];
-    static_assert(sizeof(smem) >= 2 * 64 * 40 * sizeof(__bf16), "staging exceeds the LDS block");
-    __bf16(*As)[40] = reinterpret_cast<__bf16(*)[40]>(&smem[0]);
-    __bf16(*Bs)[40] = reinterpret_cast<__bf16(*)[40]>(&smem[0]) + 64;  // transposed: Bs[n][k]
-    int tx, ty, g;
-    if (!xcd_tile(ntx, nty, ntz, tx, ty, g)) return;
-    int M = G.M;
-    int64_t row0 = 0;
-    if (G.rows) {
-        M = G.rows[g];
-        row0 = G.row_off[g];
-    }
-    const int m0 = ty * 64, n0 = tx * 64;
-    if (m0 >= M) return;
-    const __bf16 *__restrict__ A = G.A + g * G.a_g + row0 * G.sam;
-    const __bf16 *__restrict__ B = G.B + g * G.b_g;
+// ================================================================= forward
+// Where a tile's results go for a backward pass.
+struct KeepTile {
+    float *x;          // [64][6] inputs
+    float *z2;         // pre-activations of layer 2 in accumulator order: [wave][i][j][lane][4]
+    float *z3;         // [64][256]
+    __bf16 *h1t, *h2t; // [256][64]
+};
+
+// One 64-row tile (M valid rows, the rest zero inputs) of the network at Pg.
+// Eight waves, wave w owning output columns [32 w, 32 w + 32) of the two
+// products; the tile's activations sit in LDS as the two bf16 parts, the FP32
+// master weights stream through L2 and are split as they arrive, the next
+// slice of 32 k on its way while the current one is multiplied.  Bound by
+// the matrix cores' 3 x 16.8 MFLOP per tile next to the vector work of the
+// splits and SiLUs; 68 KB of LDS and at most 128 registers keep two workgroups,
+// four waves per SIMD, on a CU, so one's vector work runs under the other's
+// products (four waves of 64 columns, two per SIMD, took @4W@).
+template <bool KEEP>
+__device__ __forceinline__ void forward_tile(char *smem, float (*Xs)[6], const float *__restrict__ Pg,
+                                             const float *__restrict__ X, float *__restrict__ Y, int M,
+                                             const KeepTile &K) {
+    __bf16(*Ah)[AROW] = reinterpret_cast<__bf16(*)[AROW]>(smem);
+    __bf16(*Al)[AROW] = Ah + TM;
+    float(*Hf)[FROW] = reinterpret_cast<float(*)[FROW]>(smem);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-    f32x4 acc[2][2];
+    const int col = lane & 15, grp = lane >> 4, kq = grp * 8;
+    for (int e = tid; e < TM * 6; e += NT) {
+        const float v = e < 6 * M ? X[e] : 0.f;
+        Xs[e / 6][e % 6] = v;
+        if constexpr (KEEP) K.x[e] = v;
+    }
+    __syncthreads();
+    {   // layer 1, FP32: thread = unit and half of the rows
+        const int o = tid & (H - 1);
+        const float *W = Pg + rti::OFF_W1 + o * 6;
+        const float w0 = W[0], w1 = W[1], w2 = W[2], w3 = W[3], w4 = W[4], w5 = W[5];
+        const float b = Pg[rti::OFF_B1 + o];
+        const int rh = (tid >> 8) * (TM / 2);
+#pragma unroll 1
+        for (int r0 = rh; r0 < rh + TM / 2; r0 += 8) {
+            bf16x8 hi;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+            for (int u = 0; u < 8; ++u) {
+                const int r = r0 + u;
+                float z = b;
+                z = fmaf(w0, Xs[r][0], z);
+                z = fmaf(w1, Xs[r][1], z);
+                z = fmaf(w2, Xs[r][2], z);
+                z = fmaf(w3, Xs[r][3], z);
+                z = fmaf(w4, Xs[r][4], z);
+                z = fmaf(w5, Xs[r][5], z);
+                const float h = silu(z);
+                hi[u] = (__bf16)h;
+                Ah[r][o] = hi[u];
+                Al[r][o] = (__bf16)(h - (float)hi[u]);
+            }
+            if constexpr (KEEP) *(bf16x8 *)(K.h1t + o * TM + r0) = hi;
+        }
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int l = 0; l < 2; ++l) {
+        const float *__restrict__ W = Pg + (l == 0 ? rti::OFF_W2 : rti::OFF_W3) + (wave * 32 + col) * H + kq;
+        const float *__restrict__ bias = Pg + (l == 0 ? rti::OFF_B2 : rti::OFF_B3) + wave * 32 + col;
+        f32x4 acc[4][2];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        f32x4u raw[2][2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            raw[j][0] = *(const f32x4u *)(W + 16 * j * H);
+            raw[j][1] = *(const f32x4u *)(W + 16 * j * H + 4);
+        }
+#pragma unroll 1
+        for (int k0 = 0; k0 < H; k0 += 32) {
+            bf16x8 bh[2], bl[2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const float v[8] = {raw[j][0][0], raw[j][0][1], raw[j][0][2], raw[j][0][3],
+                                    raw[j][1][0], raw[j][1][1], raw[j][1][2], raw[j][1][3]};
+                split8(v, bh[j], bl[j]);
+            }
+            const int kn = k0 + 32 < H ? k0 + 32 : k0;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                raw[j][0] = *(const f32x4u *)(W + 16 * j * H + kn);
+                raw[j][1] = *(const f32x4u *)(W + 16 * j * H + kn + 4);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const bf16x8 ah = *(const bf16x8 *)&Ah[16 * i + col][k0 + kq];
+                const bf16x8 al = *(const bf16x8 *)&Al[16 * i + col][k0 + kq];
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[j], acc[i][j], 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[j], acc[i][j], 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[j], acc[i][j], 0, 0, 0);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int n = wave * 32 + 16 * j + col;
+            const float bn = bias[16 * j];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int r = 16 * i + 4 * grp;
+                f32x4 z;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) z[e] = acc[i][j][e] + bn;
+                if (l == 0) {
+                    if constexpr (KEEP) *(f32x4 *)(K.z2 + (((wave * 4 + i) * 2 + j) * 64 + lane) * 4) = z;
+                    bf16x4 hi;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float h = silu(z[e]);
+                        hi[e] = (__bf16)h;
+                        Ah[r + e][n] = hi[e];
+                        Al[r + e][n] = (__bf16)(h - (float)hi[e]);
+                    }
+                    if constexpr (KEEP) *(bf16x4 *)(K.h2t + n * TM + r) = hi;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        if constexpr (KEEP) K.z3[(r + e) * H + n] = z[e];
+                        Hf[r + e][n] = silu(z[e]);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+    }
+    // output layer, FP32: one wave per row, lane l taking k = l + 64 q in order
+    // of q, then the butterfly sum over the lanes, then the bias
+    {
+        float w4[6][4];
+#pragma unroll
+        for (int o = 0; o < 6; ++o)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) w4[o][q] = Pg[rti::OFF_W4 + o * H + lane + 64 * q];
+        const float b4 = lane < 6 ? Pg[rti::OFF_B4 + lane] : 0.f;
+        for (int m = wave; m < M; m += NT / 64) {
+            float h[4], a[6];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) h[q] = Hf[m][lane + 64 * q];
+#pragma unroll
+            for (int o = 0; o < 6; ++o) {
+                float t = w4[o][0] * h[0];
+#pragma unroll
+                for (int q = 1; q < 4; ++q) t = fmaf(w4[o][q], h[q], t);
+                a[o] = wave_sum(t);
+            }
+            if (lane < 6) {
+                float v = a[0];
+#pragma unroll
+                for (int o = 1; o < 6; ++o) v = lane == o ? a[o] : v;
+                Y[6 * m + lane] = b4 + v;
+            }
+        }
+    }
+    __syncthreads();
+}
+
+constexpr int TILE_LDS = 2 * TM * AROW * 2;  // both bf16 parts, or one FP32 tile
+static_assert(TILE_LDS >= TM * FROW * 4, "FP32 tile exceeds the LDS block");
+
+// y = MLP(x) for n networks of B rows each, keeping what the backward needs.
+__global__ __launch_bounds__(NT, 4) void k_mlp_fwd(const float *__restrict__ params, const float *__restrict__ X,
+                                                    float *__restrict__ Y, int n, int B, rti::MlpWork w) {
+    __shared__ __attribute__((aligned(16))) char smem[TILE_LDS];
+    __shared__ float Xs[TM][6];
+    const int tiles = (B + TM - 1) / TM;
+    int t, one, g;
+    if (!xcd_tile(tiles, 1, n, t, one, g)) return;
+    const int m0 = t * TM;
+    const int64_t T = (int64_t)g * tiles + t;
+    const KeepTile K{w.xf + T * TM * 6, w.z2 + T * TM * H, w.z3 + T * TM * H, w.h1t + T * TM * H, w.h2t + T * TM * H};
+    forward_tile<true>(smem, Xs, params + g * rti::MLP_P, X + ((int64_t)g * B + m0) * 6, Y + ((int64_t)g * B + m0) * 6,
+                       min(TM, B - m0), K);
+}
+
+// Rows grouped by network (ctl: row and tile offsets): persistent workgroups
+// over the tile list.
+__device__ __forceinline__ void infer_tiles(const int *__restrict__ ctl, const rti::SurrArgs &S) {
+    __shared__ __attribute__((aligned(16))) char smem[TILE_LDS];
+    __shared__ float Xs[TM][6];
+    const int total_tiles = ctl[rti::XC_TILE + 64];
+    const int lane = threadIdx.x & 63;
+    for (int t = blockIdx.x; t < total_tiles; t += gridDim.x) {
+        // network of tile t: the last one whose first tile is <= t
+        const int toff = lane < S.n_nets ? ctl[rti::XC_TILE + lane] : 0x7fffffff;
+        const int g = __builtin_amdgcn_readfirstlane(__popcll(__ballot(toff <= t)) - 1);
+        const int off = ctl[rti::XC_ROW + g], cnt = ctl[rti::XC_ROW + g + 1] - off;
+        const int m0 = (t - ctl[rti::XC_TILE + g]) * TM;
+        forward_tile<false>(smem, Xs, S.params + (int64_t)g * S.stride, S.xin + 6 * (int64_t)(off + m0),
+                            S.xout + 6 * (int64_t)(off + m0), min(TM, cnt - m0), KeepTile{});
+    }
+}
+
+// The tracer's crossings (offsets made on the device) and a caller's rows
+// (offsets by value: nothing to upload or wait for).
+__global__ __launch_bounds__(NT, 4) void k_mlp_infer(const int *__restrict__ ctl, const rti::SurrArgs S) {
+    infer_tiles(ctl, S);
+}
+__global__ __launch_bounds__(NT, 4) void k_mlp_infer_rows(const rti::GroupCtl C, const rti::SurrArgs S) {
+    infer_tiles(C.w, S);
+}
+
+// ================================================================ backward
+// W2 and W3 of the bf16 copy in the order a wave reads them as the B operand
+// of dz W (B(k, n) = W[k][n]): fragment (n/16, k/32), lane, 8 consecutive k.
+// A thread takes 8 k x 8 n.
+__global__ __launch_bounds__(256) void k_mlp_wfrag(const __bf16 *__restrict__ wb, __bf16 *__restrict__ wt) {
+    const int g = blockIdx.y, t = blockIdx.x * 256 + threadIdx.x;  // 2 layers x 32 x 32
+    const int l = t >> 10, k8 = (t >> 5) & 31, n8 = t & 31;
+    const __bf16 *src = wb + (int64_t)g * rti::MLP_P + (l == 0 ? rti::OFF_W2 : rti::OFF_W3) + k8 * 8 * H + n8 * 8;
+    bf16x8 v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = *(const bf16x8u *)(src + k * H);
+    __bf16 *dst = wt + ((int64_t)g * 2 + l) * H * H;
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+        bf16x8 o;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) o[k] = v[k][n];
+        const int nn = n8 * 8 + n, lane = (k8 & 3) * 16 + (nn & 15);
+        *(bf16x8 *)(dst + (((nn >> 4) * 8 + (k8 >> 2)) * 64 + lane) * 8) = o;
+    }
+}
+
+// acc = A W for the 64 rows of A in LDS and this wave's 32 columns.
+__device__ __forceinline__ void signal_product(const __bf16 (*A)[AROW], const __bf16 *__restrict__ frag, int wave,
+                                               int lane, f32x4 acc[4][2]) {
+    const int col = lane & 15, kq = (lane >> 4) * 8;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // the next slice is loaded into registers while the current one is
-    // multiplied
-    bf16x8 va, vb;
-    stage_load<LA>(A, G.sam, G.sak, m0, M, 0, G.K, tid, va);
-    stage_load<LB>(B, G.sbn, G.sbk, n0, G.N, 0, G.K, tid, vb);
-    const int kq = (lane >> 4) * 8;
-    for (int k0 = 0; k0 < G.K; k0 += 32) {
-        stage_store<LA>(As, tid, va);
-        stage_store<LB>(Bs, tid, vb);
-        __syncthreads();
-        if (k0 + 32 < G.K) {
-            stage_load<LA>(A, G.sam, G.sak, m0, M, k0 + 32, G.K, tid, va);
-            stage_load<LB>(B, G.sbn, G.sbk, n0, G.N, k0 + 32, G.K, tid, vb);
+    const __bf16 *__restrict__ W = frag + ((wave * 2) * 8 * 64 + lane) * 8;
+#pragma unroll 2
+    for (int k = 0; k < 8; ++k) {
+        bf16x8 b[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) b[j] = *(const bf16x8 *)(W + (j * 8 + k) * 64 * 8);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bf16x8 a = *(const bf16x8 *)&A[16 * i + col][32 * k + kq];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[j], acc[i][j], 0, 0, 0);
         }
-        bf16x8 a[2], b[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            a[i] = *(const bf16x8 *)&As[wm + 16 * i + (lane & 15)][kq];
-            b[i] = *(const bf16x8 *)&Bs[wn + 16 * i + (lane & 15)][kq];
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-        __syncthreads();
     }
-    if constexpr (VEC) {
-        // the staging arrays are free after the loop's last barrier
-        float(*Zs)[68] = reinterpret_cast<float(*)[68]>(&smem[0]);
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    Zs[wm + 16 * i + (lane >> 4) * 4 + e][wn + 16 * j + (lane & 15)] = acc[i][j][e];
-        __syncthreads();
-        const int rr = tid >> 2, c0 = (tid & 3) * 16;
-        const int64_t gm = row0 + m0 + rr;
-        float v[16];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float4 t = *reinterpret_cast<const float4 *>(&Zs[rr][c0 + 4 * q]);
-            v[4 * q] = t.x;
-            v[4 * q + 1] = t.y;
-            v[4 * q + 2] = t.z;
-            v[4 * q + 3] = t.w;
-        }
-        if (G.epi == rti::EPI_DSILU) {
-            const float *zp = G.Z + g * G.z_g + gm * G.ldz + n0 + c0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4 z = *reinterpret_cast<const float4 *>(zp + 4 * q);
-                v[4 * q] *= dsilu(z.x);
-                v[4 * q + 1] *= dsilu(z.y);
-                v[4 * q + 2] *= dsilu(z.z);
-                v[4 * q + 3] *= dsilu(z.w);
-            }
-            __bf16 *cb = G.Cb + g * G.cb_g + gm * G.ldcb + n0 + c0;
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                bf16x8 b;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) b[e] = (__bf16)v[8 * q + e];
-                *reinterpret_cast<bf16x8 *>(cb + 8 * q) = b;
-            }
-        }
-        float *cf = G.Cf + g * G.cf_g + gm * G.ldcf + n0 + c0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            *reinterpret_cast<float4 *>(cf + 4 * q) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-        return;
-    }
-    // epilogue
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int m = m0 + wm + 16 * i + (lane >> 4) * 4 + e;
-                const int n = n0 + wn + 16 * j + (lane & 15);
-                if (m >= M || n >= G.N) continue;
-                const int64_t gm = row0 + m;
-                float v = acc[i][j][e];
-                switch (G.epi) {
-                case rti::EPI_HIDDEN: {
-                    const float z = v + G.bias[g * G.bias_g + n];
-                    if (G.Cf) G.Cf[g * G.cf_g + gm * G.ldcf + n] = z;
-                    G.Cb[g * G.cb_g + gm * G.ldcb + n] = (__bf16)silu(z);
-                    break;
-                }
-                case rti::EPI_BIAS:
-                    G.Cf[g * G.cf_g + gm * G.ldcf + n] = v + G.bias[g * G.bias_g + n];
-                    break;
-                case rti::EPI_DSILU: {
-                    const float d = v * dsilu(G.Z[g * G.z_g + gm * G.ldz + n]);
-                    G.Cf[g * G.cf_g + gm * G.ldcf + n] = d;
-                    G.Cb[g * G.cb_g + gm * G.ldcb + n] = (__bf16)d;
-                    break;
-                }
-                default:
-                    G.Cf[g * G.cf_g + gm * G.ldcf + n] = v;
-                    break;
-                }
-            }
 }
 
-// Weight-gradient product: both operands have unit stride along m (or n)
-// and the long K (the batch) strided, C = sum_k A(m, k) B(k, n) with
-// A(m, k) = A[k sak + m], B(k, n) = B[k sbk + n], EPI_NONE.  A 64x64 tile
-// per block; the four waves split K in four contiguous quarters, each wave
-// accumulating the whole tile for its quarter (4x4 16x16x32 MFMA tiles)
-// with its own LDS staging, so the K loop has no block barrier.  A lane
-// loads four k rows of eight consecutive m and writes each m's four k values
-// as one 8-byte LDS store ([m][k] rows of 40).  The partial tiles are added
-// in a fixed order, (w0 + w2) + (w1 + w3), through LDS.  Needs K % 128 == 0,
-// M % 64 == 0, N % 64 == 0, 8 | the strides and 16-byte aligned bases.
-__global__ __launch_bounds__(256) void k_gemm_wgrad(rti::GemmArgs G, int ntx, int nty, int ntz) {
-    __shared__ __attribute__((aligned(16))) float smem[4 * 2 * 64 * 40 / 2];
-    static_assert(sizeof(smem) >= 2 * 64 * 64 * sizeof(float), "reduction exceeds the LDS block");
-    int tx, ty, g;
-    if (!xcd_tile(ntx, nty, ntz, tx, ty, g)) return;
+// A 64-row tile of one network from dy back to the first layer's gradient:
+//   dz3 = (dy W4) silu'(z3), dz2 = (dz3 W3) silu'(z2), dz1 = (dz2 W2) silu'(z1),
+// the signals rounded to bf16 for the products and the weight gradients,
+// z1 formed again from the inputs.  Between the products the tile goes
+// through LDS in FP32, and a thread walks down its column: the bias sums and
+// the FP32 layers' weight-gradient partials in row order, and the column's
+// bf16 values, which are contiguous in the transposed signal matrices.
+// Bound by the 0.3 MB that a tile reads and writes and by the column walks.
+__global__ __launch_bounds__(NT, 4) void k_mlp_bwd(const float *__restrict__ params, const float *__restrict__ DY, int n,
+                                                   int B, rti::MlpWork w) {
+    __shared__ __attribute__((aligned(16))) char smem[TILE_LDS];
+    __shared__ float Xs[TM][6], Ds[TM][6], S0[H];
+    __bf16(*A)[AROW] = reinterpret_cast<__bf16(*)[AROW]>(smem);
+    float(*F)[FROW] = reinterpret_cast<float(*)[FROW]>(smem);
+    const int tiles = (B + TM - 1) / TM, nch = (B + GRAD_ROWS - 1) / GRAD_ROWS;
+    int t, one, g;
+    if (!xcd_tile(tiles, 1, n, t, one, g)) return;
+    const int m0 = t * TM, M = min(TM, B - m0);
+    const int64_t T = (int64_t)g * tiles + t;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int col = lane & 15, grp = lane >> 4;
+    // the column walks: column c, rows [32 half, 32 half + 32)
+    const int c = tid & (H - 1), half = tid >> 8, rh = half * GRAD_ROWS;
+    const float *__restrict__ Pg = params + g * rti::MLP_P;
+    const float *__restrict__ dy = DY + ((int64_t)g * B + m0) * 6;
+    for (int e = tid; e < TM * 6; e += NT) {
+        Xs[e / 6][e % 6] = w.xf[T * TM * 6 + e];
+        Ds[e / 6][e % 6] = e < 6 * M ? dy[e] : 0.f;
+    }
+    __syncthreads();
+    auto write_part = [&](float *part, const float a[7]) {
+        const int ch = 2 * t + half;
+        if (ch < nch) {
+            float *dst = part + ((int64_t)g * nch + ch) * 7 * H + c;
+#pragma unroll
+            for (int i = 0; i < 7; ++i) dst[i * H] = a[i];
+        }
+    };
+    // a column's sum from its two halves (called by all threads)
+    auto column_sum = [&](float s, float *out) {
+        if (half == 0) S0[c] = s;
+        __syncthreads();
+        if (half == 1) out[T * H + c] = S0[c] + s;
+    };
+    {   // output layer
+        float w4[6], a[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, s = 0.f;
+#pragma unroll
+        for (int o = 0; o < 6; ++o) w4[o] = Pg[rti::OFF_W4 + o * H + c];
+        const float *__restrict__ z3 = w.z3 + (T * TM + rh) * H + c;
+        __bf16 *__restrict__ dzt = w.dz3t + (T * H + c) * TM + rh;
+#pragma unroll 1
+        for (int r0 = 0; r0 < GRAD_ROWS; r0 += 8) {
+            float z[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) z[u] = z3[(r0 + u) * H];
+            bf16x8 pk;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int m = rh + r0 + u;
+                const float sg = sigmoid(z[u]), h = z[u] * sg;
+                float dh = 0.f;
+#pragma unroll
+                for (int o = 0; o < 6; ++o) {
+                    const float d = Ds[m][o];
+                    dh = fmaf(d, w4[o], dh);
+                    a[o] = fmaf(d, h, a[o]);
+                }
+                if (c < 6) a[6] += Ds[m][c];
+                const float dz = dh * (sg * (1.0f + z[u] * (1.0f - sg)));
+                s += dz;
+                pk[u] = (__bf16)dz;
+                A[m][c] = pk[u];
+            }
+            *(bf16x8 *)(dzt + r0) = pk;
+        }
+        write_part(w.part4, a);
+        column_sum(s, w.cs3);
+    }
+    // (column_sum's barrier: the tile of signals is complete)
+    f32x4 acc[4][2];
+    signal_product(A, w.wt + ((int64_t)g * 2 + 1) * H * H, wave, lane, acc);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const f32x4 z = *(const f32x4 *)(w.z2 + T * TM * H + (((wave * 4 + i) * 2 + j) * 64 + lane) * 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) F[16 * i + 4 * grp + e][wave * 32 + 16 * j + col] = acc[i][j][e] * dsilu(z[e]);
+            __builtin_amdgcn_sched_barrier(0);  // (keeps the unrolled tiles from holding all of z at once)
+        }
+    __syncthreads();
+    {
+        float s = 0.f;
+        bf16x8 pk[GRAD_ROWS / 8];
+        __bf16 *__restrict__ dzt = w.dz2t + (T * H + c) * TM + rh;
+#pragma unroll
+        for (int q = 0; q < GRAD_ROWS / 8; ++q) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const float v = F[rh + 8 * q + u][c];
+                s += v;
+                pk[q][u] = (__bf16)v;
+            }
+            *(bf16x8 *)(dzt + 8 * q) = pk[q];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        column_sum(s, w.cs2);  // its barrier: the FP32 tile has been read
+#pragma unroll
+        for (int q = 0; q < GRAD_ROWS / 8; ++q)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) A[rh + 8 * q + u][c] = pk[q][u];
+    }
+    __syncthreads();
+    signal_product(A, w.wt + ((int64_t)g * 2) * H * H, wave, lane, acc);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int n1 = wave * 32 + 16 * j + col;
+        float w1[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) w1[q] = Pg[rti::OFF_W1 + n1 * 6 + q];
+        const float b1 = Pg[rti::OFF_B1 + n1];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int r = 16 * i + 4 * grp + e;
+                float z = b1;
+#pragma unroll
+                for (int q = 0; q < 6; ++q) z = fmaf(w1[q], Xs[r][q], z);
+                F[r][n1] = acc[i][j][e] * dsilu(z);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+    }
+    __syncthreads();
+    {   // first layer
+        float a[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+        for (int u = 0; u < GRAD_ROWS; ++u) {
+            const float d = F[rh + u][c];
+#pragma unroll
+            for (int q = 0; q < 6; ++q) a[q] = fmaf(d, Xs[rh + u][q], a[q]);
+            a[6] += d;
+        }
+        write_part(w.part1, a);
+    }
+}
+
+// Weight gradients of both 256x256 layers: dW[o][i] = sum_b dz[b][o] h[b][i],
+// with dz and h as [256][64] tiles, so that a lane's eight consecutive b of
+// an operand are one 16-byte load and nothing is transposed here.  A 64x64
+// tile of one layer of one network per block; the four waves split the batch
+// in contiguous quarters, each accumulating the whole tile (4x4 16x16x32 MFMA
+// tiles) straight from L2, and the partial tiles are added in a fixed order,
+// (w0 + w2) + (w1 + w3).  Bound by the 256 KB a tile reads through L2.
+__global__ __launch_bounds__(256, 4) void k_mlp_wgrad(int n, int tiles, rti::MlpWork w, float *__restrict__ grad) {
+    __shared__ __attribute__((aligned(16))) float R[2][64][64];
+    int tx, ty, gl;
+    if (!xcd_tile(4, 4, 2 * n, tx, ty, gl)) return;
+    const int g = gl >> 1, l = gl & 1;
     const int m0 = ty * 64, n0 = tx * 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    __bf16(*As)[40] = reinterpret_cast<__bf16(*)[40]>(&smem[0]) + wave * 128;  // this wave's [m][k]
-    __bf16(*Bs)[40] = As + 64;                                                  // and [n][k]
-    const __bf16 *__restrict__ A = G.A + g * G.a_g;
-    const __bf16 *__restrict__ B = G.B + g * G.b_g;
-    const int kq4 = G.K / 4;
-    const int kb = wave * kq4;
+    const int col = lane & 15, grp = lane >> 4;
+    const int64_t base = ((int64_t)g * tiles * H + col) * TM + grp * 8;
+    const __bf16 *__restrict__ A = (l ? w.dz3t : w.dz2t) + base + m0 * TM;
+    const __bf16 *__restrict__ Bm = (l ? w.h2t : w.h1t) + base + n0 * TM;
+    const int ns = 2 * tiles, s0 = ns * wave / 4, s1 = ns * (wave + 1) / 4;
     f32x4 acc[4][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // lane: k rows kr .. kr + 3 of the 32-wide slice, m (or n) columns c0 .. c0 + 7
-    const int kr = (lane >> 3) * 4, c0 = (lane & 7) * 8;
-    const int kq = (lane >> 4) * 8;
-    for (int k0 = kb; k0 < kb + kq4; k0 += 32) {
-        bf16x8 va[4], vb[4];
+    bf16x8 a[4], b[4];
+    auto load = [&](int s) {
+        const int64_t o = (int64_t)(s >> 1) * TM * H + (s & 1) * 32;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            va[t] = *(const bf16x8 *)(A + (int64_t)(k0 + kr + t) * G.sak + m0 + c0);
-            vb[t] = *(const bf16x8 *)(B + (int64_t)(k0 + kr + t) * G.sbk + n0 + c0);
+        for (int i = 0; i < 4; ++i) {
+            a[i] = *(const bf16x8 *)(A + o + 16 * i * TM);
+            b[i] = *(const bf16x8 *)(Bm + o + 16 * i * TM);
         }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-            const bf16x4 a4 = {va[0][e], va[1][e], va[2][e], va[3][e]};
-            const bf16x4 b4 = {vb[0][e], vb[1][e], vb[2][e], vb[3][e]};
-            *(bf16x4 *)&As[c0 + e][kr] = a4;
-            *(bf16x4 *)&Bs[c0 + e][kr] = b4;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        bf16x8 a[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = *(const bf16x8 *)&As[16 * i + (lane & 15)][kq];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const bf16x8 b = *(const bf16x8 *)&Bs[16 * j + (lane & 15)][kq];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b, acc[i][j], 0, 0, 0);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-    // fixed-order sum of the four partial tiles: (w0 + w2) + (w1 + w3)
-    float(*R)[64][64] = reinterpret_cast<float(*)[64][64]>(&smem[0]);
-    auto put = [&](int slot) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) R[slot][16 * i + (lane >> 4) * 4 + e][16 * j + (lane & 15)] = acc[i][j][e];
     };
-    auto add = [&](int slot) {
+    if (s0 < s1) load(s0);
+#pragma unroll 2
+    for (int s = s0; s < s1; ++s) {
+        bf16x8 ca[4], cb[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[i][j][e] += R[slot][16 * i + (lane >> 4) * 4 + e][16 * j + (lane & 15)];
-    };
-    __syncthreads();
-    if (wave >= 2) put(wave - 2);
-    __syncthreads();
-    if (wave < 2) add(wave);
-    __syncthreads();
-    if (wave == 1) put(0);
-    __syncthreads();
-    if (wave != 0) return;
-    add(0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4; ++i) {
+            ca[i] = a[i];
+            cb[i] = b[i];
+        }
+        load(s + 1 < s1 ? s + 1 : s);
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int m = m0 + 16 * i + (lane >> 4) * 4 + e, n = n0 + 16 * j + (lane & 15);
-                G.Cf[g * G.cf_g + (int64_t)m * G.ldcf + n] = acc[i][j][e];
-            }
-}
-
-// First layer in FP32: thread o of a 256-thread block computes unit o of
-// z1 = W1 x + b1 for up to 64 rows of network blockIdx.y; h1 = silu(z1) is
-// stored split in two bf16 parts (hi, lo) for the next product, z1 (and x)
-// for a backward pass.
-__global__ __launch_bounds__(256) void k_l1_fwd(const float *__restrict__ params, const float *__restrict__ X, int B,
-                                                float *__restrict__ Z, __bf16 *__restrict__ H, __bf16 *__restrict__ HL,
-                                                float *__restrict__ Xkeep) {
-    const int g = blockIdx.y, o = threadIdx.x;
-    const int m0 = blockIdx.x * 64;
-    if (m0 >= B) return;
-    const float *__restrict__ W = params + g * rti::MLP_P + rti::OFF_W1 + o * 6;
-    const float w0 = W[0], w1 = W[1], w2 = W[2], w3 = W[3], w4 = W[4], w5 = W[5];
-    const float bias = params[g * rti::MLP_P + rti::OFF_B1 + o];
-    const int m1 = min(B, m0 + 64);
-    for (int m = m0; m < m1; ++m) {
-        const int64_t r = (int64_t)g * B + m;
-        const float *__restrict__ x = X + r * 6;
-        float z = bias;
-        z = fmaf(w0, x[0], z);
-        z = fmaf(w1, x[1], z);
-        z = fmaf(w2, x[2], z);
-        z = fmaf(w3, x[3], z);
-        z = fmaf(w4, x[4], z);
-        z = fmaf(w5, x[5], z);
-        if (Z) Z[r * rti::MLP_H + o] = z;
-        const float h = silu(z);
-        const __bf16 hh = (__bf16)h;
-        H[r * rti::MLP_H + o] = hh;
-        HL[r * rti::MLP_H + o] = (__bf16)(h - (float)hh);
-        if (Xkeep && o < 6) Xkeep[r * 6 + o] = x[o];
+            for (int i = 0; i < 4; ++i)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ca[i], cb[j], acc[i][j], 0, 0, 0);
     }
-}
-
-// Rows per partial of the FP32 layers' weight gradients: short serial
-// chunks, many blocks.
-constexpr int GRAD_ROWS = 32;
-
-// First-layer gradients in FP32: dW1[o][i] = sum_m dz1[m][o] x[m][i] and
-// db1[o] = sum_m dz1[m][o]; per block of GRAD_ROWS rows a sequential
-// partial, then the partials summed in order.
-__global__ __launch_bounds__(256) void k_l1_grad_part(const float *__restrict__ DZ, const float *__restrict__ X, int B,
-                                                      float *__restrict__ part) {
-    const int g = blockIdx.y, c = blockIdx.x, o = threadIdx.x;
-    const int r0 = c * GRAD_ROWS, r1 = min(B, r0 + GRAD_ROWS);
-    float a[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int m = r0; m < r1; ++m) {
-        const int64_t r = (int64_t)g * B + m;
-        const float d = DZ[r * rti::MLP_H + o];
-        const float *__restrict__ x = X + r * 6;
+    // (32 KB of LDS: four workgroups on a CU)
+    auto each = [&](auto f) {
 #pragma unroll
-        for (int i = 0; i < 6; ++i) a[i] = fmaf(d, x[i], a[i]);
-        a[6] += d;
-    }
-    float *__restrict__ dst = part + (((int64_t)g * gridDim.x + c) * rti::MLP_H + o) * 7;
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int i = 0; i < 7; ++i) dst[i] = a[i];
-}
-__global__ __launch_bounds__(256) void k_l1_grad_final(const float *__restrict__ part, int nchunk,
-                                                       float *__restrict__ grad) {
-    const int g = blockIdx.x, o = threadIdx.x;
-    float a[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int c = 0; c < nchunk; ++c) {
-        const float *__restrict__ src = part + (((int64_t)g * nchunk + c) * rti::MLP_H + o) * 7;
+            for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int i = 0; i < 7; ++i) a[i] += src[i];
-    }
-    float *__restrict__ G = grad + (int64_t)g * rti::MLP_P;
-#pragma unroll
-    for (int i = 0; i < 6; ++i) G[rti::OFF_W1 + o * 6 + i] = a[i];
-    G[rti::OFF_B1 + o] = a[6];
-}
-
-// Output layer in FP32: y[m][o] = b4[o] + sum_k W4[o][k] silu(z3[m][k]).
-// One wave per row (the rows of a 64-row chunk of network blockIdx.y dealt
-// to the block's four waves), lane l taking k = l + 64 q in order of q, then
-// a butterfly sum over the lanes in a fixed pattern; W4 stays in registers.
-__global__ __launch_bounds__(256) void k_l4_fwd(const float *__restrict__ params, const float *__restrict__ Z3, int B,
-                                                float *__restrict__ Y) {
-    const int g = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m0 = blockIdx.x * 64;
-    if (m0 >= B) return;
-    const float *__restrict__ W = params + g * rti::MLP_P + rti::OFF_W4;
-    float w[6][4];
-#pragma unroll
-    for (int o = 0; o < 6; ++o)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) w[o][q] = W[o * rti::MLP_H + lane + 64 * q];
-    const float *__restrict__ b4 = params + g * rti::MLP_P + rti::OFF_B4;
-    const int m1 = min(B, m0 + 64);
-    for (int m = m0 + wave; m < m1; m += 4) {
-        const float *__restrict__ z = Z3 + ((int64_t)g * B + m) * rti::MLP_H;
-        float h[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) h[q] = silu(z[lane + 64 * q]);
-        float a[6];
-#pragma unroll
-        for (int o = 0; o < 6; ++o) {
-            float t = w[o][0] * h[0];
-#pragma unroll
-            for (int q = 1; q < 4; ++q) t = fmaf(w[o][q], h[q], t);
-            a[o] = t;
-        }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1)
-#pragma unroll
-            for (int o = 0; o < 6; ++o) a[o] += __shfl_xor(a[o], off);
-        if (lane < 6) {
-            float v = a[0];
-#pragma unroll
-            for (int o = 1; o < 6; ++o) v = lane == o ? a[o] : v;
-            Y[((int64_t)g * B + m) * 6 + lane] = b4[lane] + v;
-        }
-    }
-}
-
-// Output-layer gradients in FP32: dW4[o][k] = sum_m dy[m][o] silu(z3[m][k]),
-// db4[o] = sum_m dy[m][o]; per block of GRAD_ROWS rows a sequential partial
-// (thread k: six dW4 partials, and db4[k] for k < 6), then the partials in
-// order.
-__global__ __launch_bounds__(256) void k_l4_grad_part(const float *__restrict__ DY, const float *__restrict__ Z3, int B,
-                                                      float *__restrict__ part) {
-    const int g = blockIdx.y, c = blockIdx.x, k = threadIdx.x;
-    const int r0 = c * GRAD_ROWS, r1 = min(B, r0 + GRAD_ROWS);
-    float a[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int m = r0; m < r1; ++m) {
-        const int64_t r = (int64_t)g * B + m;
-        const float h = silu(Z3[r * rti::MLP_H + k]);
-        const float *__restrict__ d = DY + r * 6;
-#pragma unroll
-        for (int o = 0; o < 6; ++o) a[o] = fmaf(d[o], h, a[o]);
-        if (k < 6) a[6] += d[k];
-    }
-    float *__restrict__ dst = part + (((int64_t)g * gridDim.x + c) * rti::MLP_H + k) * 7;
-#pragma unroll
-    for (int i = 0; i < 7; ++i) dst[i] = a[i];
-}
-__global__ __launch_bounds__(256) void k_l4_grad_final(const float *__restrict__ part, int nchunk,
-                                                       float *__restrict__ grad) {
-    const int g = blockIdx.x, k = threadIdx.x;
-    float a[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int c = 0; c < nchunk; ++c) {
-        const float *__restrict__ src = part + (((int64_t)g * nchunk + c) * rti::MLP_H + k) * 7;
-#pragma unroll
-        for (int i = 0; i < 7; ++i) a[i] += src[i];
-    }
-    float *__restrict__ G = grad + (int64_t)g * rti::MLP_P;
-#pragma unroll
-    for (int o = 0; o < 6; ++o) G[rti::OFF_W4 + o * rti::MLP_H + k] = a[o];
-    if (k < 6) G[rti::OFF_B4 + k] = a[6];
-}
-
-// Back-propagation through the output layer: dz3[m][k] =
-// (sum_o dy[m][o] W4[o][k]) silu'(z3[m][k]), kept in FP32 and bf16.
-__global__ __launch_bounds__(256) void k_l4_bwd(const float *__restrict__ params, const float *__restrict__ DY,
-                                                const float *__restrict__ Z3, int B, float *__restrict__ DZ,
-                                                __bf16 *__restrict__ DZB) {
-    const int g = blockIdx.y, k = threadIdx.x;
-    const int m0 = blockIdx.x * 64;
-    if (m0 >= B) return;
-    const float *__restrict__ W = params + g * rti::MLP_P + rti::OFF_W4;
-    float w[6];
-#pragma unroll
-    for (int o = 0; o < 6; ++o) w[o] = W[o * rti::MLP_H + k];
-    const int m1 = min(B, m0 + 64);
-    for (int m = m0; m < m1; ++m) {
-        const int64_t r = (int64_t)g * B + m;
-        const float *__restrict__ d = DY + r * 6;
-        float dh = 0.f;
-#pragma unroll
-        for (int o = 0; o < 6; ++o) dh = fmaf(d[o], w[o], dh);
-        const float dz = dh * dsilu(Z3[r * rti::MLP_H + k]);
-        DZ[r * rti::MLP_H + k] = dz;
-        DZB[r * rti::MLP_H + k] = (__bf16)dz;
-    }
-}
-
-// Forward product of a hidden layer in split bf16: for network blockIdx.z,
-// z[m][n] = b[n] + sum_k h[m][k] W[n][k] over K = N = 256, with h given as
-// its two bf16 parts (Hh, Hl, written by the previous layer) and W split
-// from the FP32 master while staged; then Zout = z (FP32) and the parts of
-// silu(z) for the next layer and the backward.  A 64x64 tile per block, 4
-// waves of 2x2 16x16x32 tiles; LDS rows of 40 bf16 (80 bytes) so that every
-// stage write and fragment read is one 16-byte access.
-typedef __bf16 bf16x8v __attribute__((ext_vector_type(8)));
-
-__global__ __launch_bounds__(256) void k_gemm_x3(const __bf16 *__restrict__ Hh, const __bf16 *__restrict__ Hl,
-                                                 const float *__restrict__ params, int64_t offW, int64_t offB, int B,
-                                                 float *__restrict__ Zout, __bf16 *__restrict__ Oh,
-                                                 __bf16 *__restrict__ Ol, int n_nets) {
-    // one LDS block: the four staging arrays, reused for the output tile
-    __shared__ __attribute__((aligned(16))) __bf16 stage[4][64][40];
-    __bf16(&Ah)[64][40] = stage[0];
-    __bf16(&Al)[64][40] = stage[1];
-    __bf16(&Bh)[64][40] = stage[2];  // [n][k]
-    __bf16(&Bl)[64][40] = stage[3];
-    int tx, ty, g;
-    if (!xcd_tile(rti::MLP_H / 64, (B + 63) / 64, n_nets, tx, ty, g)) return;
-    const int m0 = ty * 64, n0 = tx * 64;
-    if (m0 >= B) return;
-    const int64_t K = rti::MLP_H;
-    const __bf16 *__restrict__ Xh = Hh + (int64_t)g * B * K;
-    const __bf16 *__restrict__ Xl = Hl + (int64_t)g * B * K;
-    const float *__restrict__ W = params + (int64_t)g * rti::MLP_P + offW;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-    f32x4 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int r = tid >> 2, kc = (tid & 3) * 8;
-    const int m = m0 + r, n = n0 + r;
-    bf16x8v zero8;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) zero8[e] = (__bf16)0.0f;
-    for (int k0 = 0; k0 < K; k0 += 32) {
-        // stage: thread t takes 8 consecutive k of row t/4 of each operand
-        if (m < B) {
-            *(bf16x8v *)&Ah[r][kc] = *(const bf16x8v *)(Xh + (int64_t)m * K + k0 + kc);
-            *(bf16x8v *)&Al[r][kc] = *(const bf16x8v *)(Xl + (int64_t)m * K + k0 + kc);
-        } else {
-            *(bf16x8v *)&Ah[r][kc] = zero8;
-            *(bf16x8v *)&Al[r][kc] = zero8;
-        }
-        {
-            const float4 *src = reinterpret_cast<const float4 *>(W + (int64_t)n * K + k0 + kc);
-            const float4 u0 = src[0], u1 = src[1];
-            const float v[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
-            bf16x8v hi, lo;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const __bf16 t = (__bf16)v[e];
-                hi[e] = t;
-                lo[e] = (__bf16)(v[e] - (float)t);
-            }
-            *(bf16x8v *)&Bh[r][kc] = hi;
-            *(bf16x8v *)&Bl[r][kc] = lo;
-        }
-        __syncthreads();
-        const int kq = (lane >> 4) * 8;
-        bf16x8 ah[2], al[2], bh[2], bl[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            ah[i] = *(const bf16x8 *)&Ah[wm + 16 * i + (lane & 15)][kq];
-            al[i] = *(const bf16x8 *)&Al[wm + 16 * i + (lane & 15)][kq];
-            bh[i] = *(const bf16x8 *)&Bh[wn + 16 * i + (lane & 15)][kq];
-            bl[i] = *(const bf16x8 *)&Bl[wn + 16 * i + (lane & 15)][kq];
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[i], bh[j], acc[i][j], 0, 0, 0);
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bl[j], acc[i][j], 0, 0, 0);
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bh[j], acc[i][j], 0, 0, 0);
-            }
-        __syncthreads();
-    }
-    // epilogue through LDS (the staging buffers, free after the last
-    // barrier): the tile of z = acc + bias, then every thread writes 16
-    // consecutive values of one row as whole 16-byte stores of z and of the
-    // two bf16 parts of silu(z)
-    const float *__restrict__ bias = params + (int64_t)g * rti::MLP_P + offB;
-    static_assert(sizeof(stage) >= 64 * 68 * sizeof(float), "output tile exceeds the staging block");
-    float(*Zs)[68] = reinterpret_cast<float(*)[68]>(&stage[0][0][0]);
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int rr = wm + 16 * i + (lane >> 4) * 4 + e, cc = wn + 16 * j + (lane & 15);
-                Zs[rr][cc] = acc[i][j][e] + bias[n0 + cc];
-            }
+                for (int e = 0; e < 4; ++e) f(R[wave & 1][16 * i + 4 * grp + e][16 * j + col], acc[i][j][e]);
+    };
+    if (wave >= 2) each([](float &r, float v) { r = v; });
     __syncthreads();
-    {
-        const int rr = tid >> 2, c0 = (tid & 3) * 16;
-        const int mm = m0 + rr;
-        if (mm < B) {
-            const int64_t o = ((int64_t)g * B + mm) * K + n0 + c0;
-            float v[16];
+    if (wave < 2) each([](float &r, float v) { r = v + r; });
+    __syncthreads();
+    float *__restrict__ C = grad + g * rti::MLP_P + (l ? rti::OFF_W3 : rti::OFF_W2);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4 t = *reinterpret_cast<const float4 *>(&Zs[rr][c0 + 4 * q]);
-                v[4 * q] = t.x;
-                v[4 * q + 1] = t.y;
-                v[4 * q + 2] = t.z;
-                v[4 * q + 3] = t.w;
-                *reinterpret_cast<float4 *>(Zout + o + 4 * q) = t;
-            }
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                bf16x8v hi, lo;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float h = silu(v[8 * q + e]);
-                    const __bf16 hh = (__bf16)h;
-                    hi[e] = hh;
-                    lo[e] = (__bf16)(h - (float)hh);
-                }
-                *reinterpret_cast<bf16x8v *>(Oh + o + 8 * q) = hi;
-                *reinterpret_cast<bf16x8v *>(Ol + o + 8 * q) = lo;
-            }
-        }
+    for (int q = 0; q < 4; ++q) {
+        const int r = q * 16 + (tid >> 4), c = (tid & 15) * 4;
+        const f32x4 v0 = *(const f32x4 *)&R[0][r][c], v1 = *(const f32x4 *)&R[1][r][c];
+        *(f32x4u *)(C + (int64_t)(m0 + r) * H + n0 + c) = v0 + v1;
     }
 }
 
-// out[g][n] = sum_m X[g][m][n], fixed order: per block of COLSUM_ROWS rows
-// a sequential partial, then partials summed in order.
-constexpr int COLSUM_ROWS = 64;
-__global__ void k_colsum_part(const float *__restrict__ X, int64_t xg, int rows, int N, float *__restrict__ part) {
-    const int g = blockIdx.z, n = blockIdx.x * blockDim.x + threadIdx.x, c = blockIdx.y;
-    if (n >= N) return;
-    const int r0 = c * COLSUM_ROWS, r1 = min(rows, r0 + COLSUM_ROWS);
+// Sums of the row partials in order: block (q, g) takes one of the 16 sums of
+// network g, thread = unit.
+__global__ __launch_bounds__(256) void k_mlp_sums(int B, rti::MlpWork w, float *__restrict__ grad) {
+    const int q = blockIdx.x, g = blockIdx.y, o = threadIdx.x;
+    const int tiles = (B + TM - 1) / TM, nch = (B + GRAD_ROWS - 1) / GRAD_ROWS;
+    const float *__restrict__ src;
+    int cnt, stride;
+    if (q < 14) {
+        src = (q < 7 ? w.part1 : w.part4) + ((int64_t)g * nch * 7 + (q < 7 ? q : q - 7)) * H + o;
+        cnt = nch;
+        stride = 7 * H;
+    } else {
+        src = (q == 14 ? w.cs2 : w.cs3) + (int64_t)g * tiles * H + o;
+        cnt = tiles;
+        stride = H;
+    }
     float s = 0.f;
-    for (int r = r0; r < r1; ++r) s += X[g * xg + (int64_t)r * N + n];
-    part[((int64_t)g * gridDim.y + c) * N + n] = s;
-}
-__global__ void k_colsum_final(const float *__restrict__ part, int nchunk, int N, float *__restrict__ out,
-                               int64_t out_g) {
-    const int g = blockIdx.y, n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
-    float s = 0.f;
-    for (int c = 0; c < nchunk; ++c) s += part[((int64_t)g * nchunk + c) * N + n];
-    out[g * out_g + n] = s;
+#pragma unroll 8
+    for (int c = 0; c < cnt; ++c) s += src[(int64_t)c * stride];
+    float *__restrict__ G = grad + (int64_t)g * rti::MLP_P;
+    if (q < 6) G[rti::OFF_W1 + o * 6 + q] = s;
+    else if (q == 6) G[rti::OFF_B1 + o] = s;
+    else if (q < 13) G[rti::OFF_W4 + (q - 7) * H + o] = s;
+    else if (q == 13) {
+        if (o < 6) G[rti::OFF_B4 + o] = s;
+    } else G[(q == 14 ? rti::OFF_B2 : rti::OFF_B3) + o] = s;
 }
 
 // AdamW with bias correction; refreshes the bf16 copy of the parameters.
@@ -699,10 +632,10 @@ __global__ void k_adamw(float *__restrict__ p, __bf16 *__restrict__ pb, float *_
 }
 
 // dy = 2 (y - t) / batch and per-block squared-error sums (fixed order).
-__global__ __launch_bounds__(256) void k_mse_grad(const float *__restrict__ y, const float *__restrict__ t,
+__global__ __launch_bounds__(1024) void k_mse_grad(const float *__restrict__ y, const float *__restrict__ t,
                                                   float *__restrict__ dy, int64_t n, float inv_batch,
                                                   float *__restrict__ part) {
-    __shared__ float sh[256];
+    __shared__ float sh[1024];
     float acc = 0.f;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         float d = y[i] - t[i];
@@ -711,67 +644,16 @@ __global__ __launch_bounds__(256) void k_mse_grad(const float *__restrict__ y, c
     }
     sh[threadIdx.x] = acc;
     __syncthreads();
-    for (int o = 128; o >= 1; o >>= 1) {
+    for (int o = 512; o >= 1; o >>= 1) {
         if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
         __syncthreads();
     }
     if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
 }
 
-__global__ void k_to_bf16(const float *__restrict__ x, __bf16 *__restrict__ y, int64_t n) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        y[i] = (__bf16)x[i];
-}
-
 }  // namespace
 
 namespace rti {
-
-hipError_t launch_gemm(const GemmArgs &G, int groups, int max_rows, hipStream_t s) {
-    const int ntx = (G.N + 63) / 64, nty = (max_rows + 63) / 64;
-    dim3 grid(xcd_grid(ntx, nty, groups));
-    // vector staging when every 8-element run it loads lies inside the
-    // operand and starts on a 16-byte boundary
-    auto al = [](const void *p, int64_t a, int64_t b) {
-        return ((uintptr_t)p % 16 == 0) && a % 8 == 0 && b % 8 == 0;
-    };
-    const bool dims = !G.rows && G.M % 8 == 0 && G.N % 8 == 0 && G.K % 8 == 0;
-    const bool a_mc = dims && G.sam == 1 && al(G.A, G.a_g, G.sak);
-    const bool a_kc = dims && G.sak == 1 && al(G.A, G.a_g, G.sam);
-    const bool b_nc = dims && G.sbn == 1 && al(G.B, G.b_g, G.sbk);
-    const bool b_nc4 = dims && G.sbn == 1 && (uintptr_t)G.B % 4 == 0 && G.b_g % 2 == 0 && G.sbk % 8 == 0;
-    // whole tiles and 16-byte aligned outputs: the LDS-staged epilogue
-    auto al16 = [](const void *p, int64_t a, int64_t b) { return ((uintptr_t)p % 16 == 0) && a % 4 == 0 && b % 4 == 0; };
-    const bool vec = dims && G.M % 64 == 0 && G.N % 64 == 0 &&
-                     (G.epi == EPI_NONE || (G.epi == EPI_DSILU && al16(G.Z, G.z_g, G.ldz) &&
-                                            (uintptr_t)G.Cb % 16 == 0 && G.cb_g % 8 == 0 && G.ldcb % 8 == 0)) &&
-                     al16(G.Cf, G.cf_g, G.ldcf);
-    if (a_mc && b_nc && G.epi == EPI_NONE && G.K % 128 == 0 && G.M % 64 == 0 && G.N % 64 == 0)
-        hipLaunchKernelGGL(k_gemm_wgrad, grid, dim3(256), 0, s, G, ntx, nty, groups);
-    else if (a_kc && b_nc4 && vec)
-        hipLaunchKernelGGL((k_gemm<L_KC, L_MC4, true>), grid, dim3(256), 0, s, G, ntx, nty, groups);
-    else if (a_kc && b_nc && vec)
-        hipLaunchKernelGGL((k_gemm<L_KC, L_MC, true>), grid, dim3(256), 0, s, G, ntx, nty, groups);
-    else if (a_mc && b_nc)
-        hipLaunchKernelGGL((k_gemm<L_MC, L_MC>), grid, dim3(256), 0, s, G, ntx, nty, groups);
-    else if (a_kc && b_nc)
-        hipLaunchKernelGGL((k_gemm<L_KC, L_MC>), grid, dim3(256), 0, s, G, ntx, nty, groups);
-    else if (a_kc && b_nc4)
-        hipLaunchKernelGGL((k_gemm<L_KC, L_MC4>), grid, dim3(256), 0, s, G, ntx, nty, groups);
-    else
-        hipLaunchKernelGGL((k_gemm<L_GEN, L_GEN>), grid, dim3(256), 0, s, G, ntx, nty, groups);
-    return hipGetLastError();
-}
-
-hipError_t launch_colsum(const float *X, int64_t xg, int rows, int N, int groups, float *part, float *out,
-                         int64_t out_g, hipStream_t s) {
-    // part holds groups x nchunk x N floats
-    int nchunk = (rows + COLSUM_ROWS - 1) / COLSUM_ROWS;
-    hipLaunchKernelGGL(k_colsum_part, dim3((N + 63) / 64, nchunk, groups), dim3(64), 0, s, X, xg, rows, N, part);
-    hipLaunchKernelGGL(k_colsum_final, dim3((N + 63) / 64, groups), dim3(64), 0, s, (const float *)part, nchunk, N,
-                       out, out_g);
-    return hipGetLastError();
-}
 
 hipError_t launch_adamw(float *p, __bf16 *pb, float *m, float *v, const float *g, int64_t n, float lr, float b1,
                         float b2, float eps, float wd, int step, hipStream_t s) {
@@ -783,147 +665,73 @@ hipError_t launch_adamw(float *p, __bf16 *pb, float *m, float *v, const float *g
 
 hipError_t launch_mse_grad(const float *y, const float *t, float *dy, int64_t n, int batch, float *part, int nblk,
                            hipStream_t s) {
-    hipLaunchKernelGGL(k_mse_grad, dim3(nblk), dim3(256), 0, s, y, t, dy, n, 1.0f / (float)batch, part);
+    hipLaunchKernelGGL(k_mse_grad, dim3(nblk), dim3(1024), 0, s, y, t, dy, n, 1.0f / (float)batch, part);
     return hipGetLastError();
 }
 
-hipError_t launch_to_bf16(const float *x, __bf16 *y, int64_t n, hipStream_t s) {
-    int blocks = (int)std::min<int64_t>((n + 255) / 256, 4096);
-    hipLaunchKernelGGL(k_to_bf16, dim3(blocks), dim3(256), 0, s, x, y, n);
-    return hipGetLastError();
+// Workspace of n networks of batch rows: the tiles are whole, their rows past
+// the batch hold the forward of zero inputs and zero signals.
+template <class F> static void mlp_layout(int n, int batch, MlpWork &w, F take) {
+    const size_t tiles = ((size_t)batch + TM - 1) / TM, nch = ((size_t)batch + GRAD_ROWS - 1) / GRAD_ROWS;
+    const size_t rows = (size_t)n * tiles * TM;
+    w.xf = (float *)take(rows * MLP_IN * 4);
+    w.z2 = (float *)take(rows * MLP_H * 4);
+    w.z3 = (float *)take(rows * MLP_H * 4);
+    w.h1t = (__bf16 *)take(rows * MLP_H * 2);
+    w.h2t = (__bf16 *)take(rows * MLP_H * 2);
+    w.dz2t = (__bf16 *)take(rows * MLP_H * 2);
+    w.dz3t = (__bf16 *)take(rows * MLP_H * 2);
+    w.wt = (__bf16 *)take((size_t)n * 2 * MLP_H * MLP_H * 2);
+    w.part1 = (float *)take(n * nch * 7 * MLP_H * 4);
+    w.part4 = (float *)take(n * nch * 7 * MLP_H * 4);
+    w.cs2 = (float *)take(n * tiles * MLP_H * 4);
+    w.cs3 = (float *)take(n * tiles * MLP_H * 4);
 }
-
-}  // namespace rti
-
-namespace rti {
 
 size_t mlp_work_bytes(int n_nets, int batch) {
-    size_t nb = (size_t)n_nets * batch;
-    size_t nch = ((size_t)batch + GRAD_ROWS - 1) / GRAD_ROWS;
-    return nb * MLP_IN * 4 + nb * MLP_OUT * 2 + nb * MLP_H * (3 * 4 + 6 * 2 + 2 * 4 + 2 * 2) +
-           (size_t)n_nets * nch * MLP_H * 7 * 4 + 16 * 256;
+    size_t total = 0;
+    MlpWork w;
+    mlp_layout(n_nets, batch, w, [&](size_t bytes) {
+        total += (bytes + 255) & ~(size_t)255;
+        return (void *)nullptr;
+    });
+    return total;
 }
 
 void mlp_work_carve(void *base, int n_nets, int batch, MlpWork &w) {
-    size_t nb = (size_t)n_nets * batch;
-    size_t nch = ((size_t)batch + GRAD_ROWS - 1) / GRAD_ROWS;
     char *p = (char *)base;
-    auto take = [&](size_t bytes) {
+    mlp_layout(n_nets, batch, w, [&](size_t bytes) {
         char *r = p;
         p += (bytes + 255) & ~(size_t)255;
         return (void *)r;
-    };
-    w.xf = (float *)take(nb * MLP_IN * 4);
-    for (int i = 0; i < 3; ++i) w.z[i] = (float *)take(nb * MLP_H * 4);
-    for (int i = 0; i < 3; ++i) w.h[i] = (__bf16 *)take(nb * MLP_H * 2);
-    for (int i = 0; i < 3; ++i) w.hl[i] = (__bf16 *)take(nb * MLP_H * 2);
-    w.dyb = (__bf16 *)take(nb * MLP_OUT * 2);
-    for (int i = 0; i < 2; ++i) w.dzf[i] = (float *)take(nb * MLP_H * 4);
-    for (int i = 0; i < 2; ++i) w.dzb[i] = (__bf16 *)take(nb * MLP_H * 2);
-    // partials: nch x 7 x 256 per network for the FP32 layers, and
-    // ceil(batch / COLSUM_ROWS) x 256 <= 7 nch x 256 for the column sums
-    w.part = (float *)take((size_t)n_nets * nch * MLP_H * 7 * 4);
+    });
 }
 
-static GemmArgs gemm0() {
-    GemmArgs G{};
-    G.epi = EPI_NONE;
-    return G;
-}
-
-// y = MLP(x) for n_nets networks of batch rows each.  keep: store the
-// pre-activations for a backward pass.
-hipError_t mlp_forward(int n, int B, const __bf16 *wb, const float *params, const float *x, float *y, const MlpWork &w,
-                       bool keep, hipStream_t s) {
-    // every layer's pre-activations go to z[l]: the next layer reads them
-    (void)wb;
-    (void)keep;
-    hipLaunchKernelGGL(k_l1_fwd, dim3((B + 63) / 64, n), dim3(256), 0, s, params, x, B, w.z[0], w.h[0], w.hl[0],
-                       w.xf);
-    const dim3 grid(xcd_grid(MLP_H / 64, (B + 63) / 64, n));
-    hipLaunchKernelGGL(k_gemm_x3, grid, dim3(256), 0, s, w.h[0], w.hl[0], params, OFF_W2, OFF_B2, B, w.z[1], w.h[1],
-                       w.hl[1], n);
-    hipLaunchKernelGGL(k_gemm_x3, grid, dim3(256), 0, s, w.h[1], w.hl[1], params, OFF_W3, OFF_B3, B, w.z[2], w.h[2],
-                       w.hl[2], n);
-    hipLaunchKernelGGL(k_l4_fwd, dim3((B + 63) / 64, n), dim3(256), 0, s, params, w.z[2], B, y);
+// y = MLP(x) for n_nets networks of batch rows each, keeping what a backward
+// pass needs in the workspace.
+hipError_t mlp_forward(int n, int B, const float *params, const float *x, float *y, const MlpWork &w, hipStream_t s) {
+    hipLaunchKernelGGL(k_mlp_fwd, dim3(xcd_grid((B + TM - 1) / TM, 1, n)), dim3(NT), 0, s, params, x, y, n, B, w);
     return hipGetLastError();
 }
 
-// grad = dL/dparams given dy = dL/dy, using the workspace of the last
-// forward with keep = true.
+// grad = dL/dparams given dy = dL/dy, using the workspace of the last forward.
 hipError_t mlp_backward(int n, int B, const __bf16 *wb, const float *params, const float *dy, float *grad,
                         const MlpWork &w, hipStream_t s) {
-    hipError_t e = hipSuccess;
-    // weight gradient dW[o][i] = sum_b d[b][o] in[b][i]
-    auto wgrad = [&](const __bf16 *d, int64_t dw, const __bf16 *in, int64_t iw, int64_t off) {
-        GemmArgs G = gemm0();
-        G.A = d;
-        G.a_g = (int64_t)B * dw;
-        G.sam = 1;
-        G.sak = dw;
-        G.B = in;
-        G.b_g = (int64_t)B * iw;
-        G.sbk = iw;
-        G.sbn = 1;
-        G.M = (int)dw;
-        G.N = (int)iw;
-        G.K = B;
-        G.Cf = grad + off;
-        G.cf_g = MLP_P;
-        G.ldcf = iw;
-        return launch_gemm(G, n, (int)dw, s);
-    };
-    // back-propagated signal dz = (d W) * silu'(z)
-    auto bprop = [&](const __bf16 *d, int64_t dw, int64_t offW, const float *z, float *dzf, __bf16 *dzb) {
-        GemmArgs G = gemm0();
-        G.A = d;
-        G.a_g = (int64_t)B * dw;
-        G.sam = dw;
-        G.sak = 1;
-        G.B = wb + offW;
-        G.b_g = MLP_P;
-        G.sbk = MLP_H;
-        G.sbn = 1;
-        G.M = B;
-        G.N = (int)MLP_H;
-        G.K = (int)dw;
-        G.epi = EPI_DSILU;
-        G.Z = z;
-        G.z_g = (int64_t)B * MLP_H;
-        G.ldz = MLP_H;
-        G.Cf = dzf;
-        G.cf_g = (int64_t)B * MLP_H;
-        G.ldcf = MLP_H;
-        G.Cb = dzb;
-        G.cb_g = (int64_t)B * MLP_H;
-        G.ldcb = MLP_H;
-        return launch_gemm(G, n, B, s);
-    };
-    // output layer (FP32): weight and bias gradients, then dz3 into buffer 0
-    {
-        const int nch4 = (B + GRAD_ROWS - 1) / GRAD_ROWS;
-        hipLaunchKernelGGL(k_l4_grad_part, dim3(nch4, n), dim3(256), 0, s, dy, w.z[2], B, w.part);
-        hipLaunchKernelGGL(k_l4_grad_final, dim3(n), dim3(256), 0, s, w.part, nch4, grad);
-        hipLaunchKernelGGL(k_l4_bwd, dim3((B + 63) / 64, n), dim3(256), 0, s, params, dy, w.z[2], B, w.dzf[0],
-                           w.dzb[0]);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    // layer 3: dz in buffer 0
-    if ((e = wgrad(w.dzb[0], MLP_H, w.h[1], MLP_H, OFF_W3)) != hipSuccess) return e;
-    if ((e = launch_colsum(w.dzf[0], (int64_t)B * MLP_H, B, (int)MLP_H, n, w.part, grad + OFF_B3, MLP_P, s)) !=
-        hipSuccess)
-        return e;
-    if ((e = bprop(w.dzb[0], MLP_H, OFF_W3, w.z[1], w.dzf[1], w.dzb[1])) != hipSuccess) return e;
-    // layer 2: dz in buffer 1
-    if ((e = wgrad(w.dzb[1], MLP_H, w.h[0], MLP_H, OFF_W2)) != hipSuccess) return e;
-    if ((e = launch_colsum(w.dzf[1], (int64_t)B * MLP_H, B, (int)MLP_H, n, w.part, grad + OFF_B2, MLP_P, s)) !=
-        hipSuccess)
-        return e;
-    if ((e = bprop(w.dzb[1], MLP_H, OFF_W2, w.z[0], w.dzf[0], w.dzb[0])) != hipSuccess) return e;
-    // layer 1 (FP32): dz in buffer 0, input x
-    const int nch = (B + GRAD_ROWS - 1) / GRAD_ROWS;
-    hipLaunchKernelGGL(k_l1_grad_part, dim3(nch, n), dim3(256), 0, s, w.dzf[0], w.xf, B, w.part);
-    hipLaunchKernelGGL(k_l1_grad_final, dim3(n), dim3(256), 0, s, w.part, nch, grad);
+    const int tiles = (B + TM - 1) / TM;
+    hipLaunchKernelGGL(k_mlp_wfrag, dim3(8, n), dim3(256), 0, s, wb, w.wt);
+    hipLaunchKernelGGL(k_mlp_bwd, dim3(xcd_grid(tiles, 1, n)), dim3(NT), 0, s, params, dy, n, B, w);
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3(xcd_grid(4, 4, 2 * n)), dim3(256), 0, s, n, tiles, w, grad);
+    hipLaunchKernelGGL(k_mlp_sums, dim3(16, n), dim3(256), 0, s, B, w, grad);
+    return hipGetLastError();
+}
+
+hipError_t launch_mlp_rows(const GroupCtl &C, const SurrArgs &S, int blocks, hipStream_t s) {
+    hipLaunchKernelGGL(k_mlp_infer_rows, dim3(blocks), dim3(NT), 0, s, C, S);
+    return hipGetLastError();
+}
+
+hipError_t launch_mlp_grouped(const int *ctl, const SurrArgs &S, int blocks, hipStream_t s) {
+    hipLaunchKernelGGL(k_mlp_infer, dim3(blocks), dim3(NT), 0, s, ctl, S);
     return hipGetLastError();
 }
 

@@ -32,9 +32,6 @@ using namespace rtd;
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 // SplitMix64 finaliser (Steele, Lea, Flood 2014) as a counter-based generator.
 __device__ __forceinline__ uint64_t splitmix64(uint64_t z) {
     z += 0x9E3779B97F4A7C15ull;
@@ -42,8 +39,6 @@ __device__ __forceinline__ uint64_t splitmix64(uint64_t z) {
     z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
     return z ^ (z >> 31);
 }
-
-__device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
 
 // Canonical chord baseline of a crossing with cos th = c, sin th = s.
 __device__ __forceinline__ void chord_baseline(float c, float s, V3<float> &uc, V3<float> &vin) {
@@ -320,138 +315,6 @@ __global__ __launch_bounds__(256) void k_xprep(const rti::TraceArgs A, const rti
     }
 }
 
-// Fused grouped MLP forward.  A workgroup takes 64-row tiles of one network
-// (persistent over the pass's tile list) and keeps the tile's activations
-// in LDS as FP32: the first layer in FP32, the two 256x256 products on
-// v_mfma_f32_16x16x32_bf16 in three-term split bf16 (Ah Bh + Ah Bl + Al Bh,
-// both operands split as they are read: activations from LDS, weights from
-// the FP32 master through L2), the output layer in FP32.  Rounding points
-// and summation orders are those of the training forward pass.
-__device__ __forceinline__ void split8(const float *v, bf16x8 &hi, bf16x8 &lo) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const __bf16 h = (__bf16)v[e];
-        hi[e] = h;
-        lo[e] = (__bf16)(v[e] - (float)h);
-    }
-}
-
-__global__ __launch_bounds__(256) void k_mlp_infer(const int *__restrict__ ctl, const rti::SurrArgs S) {
-    // FP32 rows of 260 (1040 bytes, 16-byte aligned for 128-bit reads)
-    __shared__ __attribute__((aligned(16))) float Hf[64][260];
-    __shared__ float Xs[64][6];
-    const int total_tiles = ctl[rti::XC_TILE + 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int t = blockIdx.x; t < total_tiles; t += gridDim.x) {
-        // network of tile t: the last one whose first tile is <= t
-        const int toff = lane < S.n_nets ? ctl[rti::XC_TILE + lane] : 0x7fffffff;
-        const int g = uniform_i(__popcll(ballot(toff <= t)) - 1);
-        const int off = ctl[rti::XC_ROW + g], cnt = ctl[rti::XC_ROW + g + 1] - off;
-        const int m0 = off + (t - ctl[rti::XC_TILE + g]) * 64;
-        const int M = min(64, off + cnt - m0);
-        const float *__restrict__ Pg = S.params + (int64_t)g * S.stride;
-        for (int e = tid; e < 64 * 6; e += 256) {
-            const int r = e / 6, k = e - r * 6;
-            Xs[r][k] = r < M ? S.xin[6 * (int64_t)(m0 + r) + k] : 0.f;
-        }
-        __syncthreads();
-        {   // layer 1, FP32: thread = unit
-            const float *W = Pg + rti::OFF_W1 + tid * 6;
-            const float w0 = W[0], w1 = W[1], w2 = W[2], w3 = W[3], w4 = W[4], w5 = W[5];
-            const float b = Pg[rti::OFF_B1 + tid];
-            for (int r = 0; r < 64; ++r) {
-                float z = b;
-                z = fmaf(w0, Xs[r][0], z);
-                z = fmaf(w1, Xs[r][1], z);
-                z = fmaf(w2, Xs[r][2], z);
-                z = fmaf(w3, Xs[r][3], z);
-                z = fmaf(w4, Xs[r][4], z);
-                z = fmaf(w5, Xs[r][5], z);
-                Hf[r][tid] = silu_f(z);
-            }
-        }
-        __syncthreads();
-        const int kq = (lane >> 4) * 8;
-        // layers 2 and 3: wave w owns output columns [64 w, 64 w + 64)
-        for (int l = 0; l < 2; ++l) {
-            const float *__restrict__ W = Pg + (l == 0 ? rti::OFF_W2 : rti::OFF_W3);
-            const float *__restrict__ bias = Pg + (l == 0 ? rti::OFF_B2 : rti::OFF_B3);
-            f32x4 acc[4][4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-            for (int k0 = 0; k0 < 256; k0 += 32) {
-                bf16x8 bh[4], bl[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int n = wave * 64 + 16 * j + (lane & 15);
-                    const float4 *src = reinterpret_cast<const float4 *>(W + (int64_t)n * 256 + k0 + kq);
-                    const float4 u0 = src[0], u1 = src[1];
-                    const float v[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
-                    split8(v, bh[j], bl[j]);
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float4 *src = reinterpret_cast<const float4 *>(&Hf[16 * i + (lane & 15)][k0 + kq]);
-                    const float4 u0 = src[0], u1 = src[1];
-                    const float v[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
-                    bf16x8 ah, al;
-                    split8(v, ah, al);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[j], acc[i][j], 0, 0, 0);
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[j], acc[i][j], 0, 0, 0);
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[j], acc[i][j], 0, 0, 0);
-                    }
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int n = wave * 64 + 16 * j + (lane & 15);
-                    const float bn = bias[n];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) Hf[16 * i + (lane >> 4) * 4 + e][n] = silu_f(acc[i][j][e] + bn);
-                }
-            __syncthreads();
-        }
-        // output layer, FP32, in the training forward's order: one wave per
-        // row, lane l taking k = l + 64 q in order of q, then a butterfly sum
-        // over the lanes, then the bias
-        {
-            float w4[6][4];
-#pragma unroll
-            for (int o = 0; o < 6; ++o)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) w4[o][q] = Pg[rti::OFF_W4 + o * 256 + lane + 64 * q];
-            for (int m = wave; m < M; m += 4) {
-                float a[6];
-#pragma unroll
-                for (int o = 0; o < 6; ++o) {
-                    float t = w4[o][0] * Hf[m][lane];
-#pragma unroll
-                    for (int q = 1; q < 4; ++q) t = fmaf(w4[o][q], Hf[m][lane + 64 * q], t);
-                    a[o] = t;
-                }
-#pragma unroll
-                for (int off = 32; off >= 1; off >>= 1)
-#pragma unroll
-                    for (int o = 0; o < 6; ++o) a[o] += __shfl_xor(a[o], off);
-                if (lane < 6) {
-                    float v = a[0];
-#pragma unroll
-                    for (int o = 1; o < 6; ++o) v = lane == o ? a[o] : v;
-                    S.xout[6 * (int64_t)(m0 + m) + lane] = Pg[rti::OFF_B4 + lane] + v;
-                }
-            }
-        }
-        __syncthreads();
-    }
-}
-
 // Decode, probe and apply.  The error estimate of a jump, in scene units:
 //   R (e_pos + | |u| - 1 | + plane) + L (e_dir + angle + plane)
 // with e_pos, e_dir the calibrated bounds of the bin of cos th (the larger
@@ -585,13 +448,8 @@ hipError_t launch_surr_stage(const TraceArgs &a, const SurrArgs &S, const float4
                              hipStream_t s) {
     hipLaunchKernelGGL(k_xoff, dim3(1), dim3(64), 0, s, a, pass);
     hipLaunchKernelGGL(k_xprep, dim3(1024), dim3(256), 0, s, a, S, pass);
-    hipLaunchKernelGGL(k_mlp_infer, dim3(mlp_blocks), dim3(256), 0, s, (const int *)a.xctl, S);
+    (void)launch_mlp_grouped((const int *)a.xctl, S, mlp_blocks, s);
     hipLaunchKernelGGL(k_xapply, dim3(1024), dim3(256), 0, s, a, S, bump_f);
-    return hipGetLastError();
-}
-
-hipError_t launch_mlp_grouped(const int *ctl, const SurrArgs &S, int blocks, hipStream_t s) {
-    hipLaunchKernelGGL(k_mlp_infer, dim3(blocks), dim3(256), 0, s, ctl, S);
     return hipGetLastError();
 }
 
