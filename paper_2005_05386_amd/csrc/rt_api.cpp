@@ -81,6 +81,8 @@ struct rt_ctx {
     size_t surr_sb_bytes = 0;
     bool surr_sb_dirty = true;
     int surr_eligible = 0;
+    void *d_grp_ws = nullptr;          // split weights of rt_mlp_fwd_grouped
+    size_t grp_ws_bytes = 0;
     void *d_xbuf = nullptr;            // crossing queues, sized for xbuf_cap rays
     int64_t xbuf_cap = 0;
     void *d_ibuf = nullptr;            // illumination workspace, sized for ibuf_cap pixels
@@ -182,6 +184,7 @@ void rt_destroy(rt_ctx *c) {
         (void)hipFree(c->d_gen_ks);
         (void)hipFree(c->d_surr);
         (void)hipFree(c->d_surr_sb);
+        (void)hipFree(c->d_grp_ws);
         (void)hipFree(c->d_xbuf);
         (void)hipFree(c->d_ibuf);
         for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
@@ -1236,10 +1239,24 @@ rt_status rt_mlp_fwd_grouped(rt_ctx *c, int n_nets, const int32_t *rows, const u
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return hip_fail(c, e, "hipSetDevice");
     if (tiles == 0) return RT_OK;
+    // the context's buffer for the split weights: calls on one stream take
+    // turns on it, a call on another stream waits for the last one
+    const size_t need = (size_t)n_nets * rti::MLP_WSPLIT * 2;
+    if (c->last_stream != (hipStream_t)stream || c->grp_ws_bytes < need) {
+        rt_status st = sync_last(c);
+        if (st != RT_OK) return st;
+    }
+    if (c->grp_ws_bytes < need) {
+        (void)hipFree(c->d_grp_ws);
+        c->d_grp_ws = nullptr;
+        c->grp_ws_bytes = 0;
+        if ((e = hipMalloc(&c->d_grp_ws, need)) != hipSuccess) return hip_fail(c, e, "hipMalloc (grouped mlp)");
+        c->grp_ws_bytes = need;
+    }
     rti::SurrArgs S{};
     S.n_nets = n_nets;
     S.stride = RT_MLP_PARAMS;
-    S.wb = (const __bf16 *)w_bf16;
+    S.wsplit = (const __bf16 *)c->d_grp_ws;
     S.params = params;
     S.xin = (float *)x;
     S.xout = y;
@@ -1465,10 +1482,11 @@ rt_status rt_surrogate_load(rt_ctx *c, int n_nets, const uint16_t *w_bf16, const
     if (e != hipSuccess) return hip_fail(c, e, "hipSetDevice");
     rt_status st = sync_last(c);
     if (st != RT_OK) return st;
-    const size_t P = RT_MLP_PARAMS, PP = rti::MLP_P_PAD;
+    const size_t P = RT_MLP_PARAMS;
     auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
-    const size_t o_w = 0, o_p = al(n_nets * PP * 2), o_s = o_p + al(n_nets * PP * 4), o_a = o_s + al(n_nets * 4),
-                 o_e = o_a + al((size_t)n_nets * n_tab * 4), total = o_e + al((size_t)n_nets * n_bins * 8);
+    const size_t o_w = 0, o_p = al(n_nets * (size_t)rti::MLP_WSPLIT * 2), o_s = o_p + al(n_nets * P * 4),
+                 o_a = o_s + al(n_nets * 4), o_e = o_a + al((size_t)n_nets * n_tab * 4),
+                 total = o_e + al((size_t)n_nets * n_bins * 8);
     if (c->surr_bytes < total) {
         (void)hipFree(c->d_surr);
         c->d_surr = nullptr;
@@ -1477,19 +1495,22 @@ rt_status rt_surrogate_load(rt_ctx *c, int n_nets, const uint16_t *w_bf16, const
         c->surr_bytes = total;
     }
     char *d = (char *)c->d_surr;
-    if ((e = hipMemcpy2D(d + o_w, PP * 2, w_bf16, P * 2, P * 2, n_nets, hipMemcpyDeviceToDevice)) != hipSuccess ||
-        (e = hipMemcpy2D(d + o_p, PP * 4, params, P * 4, P * 4, n_nets, hipMemcpyDeviceToDevice)) != hipSuccess ||
+    if ((e = hipMemcpy(d + o_p, params, n_nets * P * 4, hipMemcpyDeviceToDevice)) != hipSuccess ||
         (e = hipMemcpy(d + o_s, scale, n_nets * 4, hipMemcpyHostToDevice)) != hipSuccess ||
         (e = hipMemcpy(d + o_a, arc, (size_t)n_nets * n_tab * 4, hipMemcpyDeviceToDevice)) != hipSuccess ||
         (e = hipMemcpy(d + o_e, err, (size_t)n_nets * n_bins * 8, hipMemcpyDeviceToDevice)) != hipSuccess)
         return hip_fail(c, e, "hipMemcpy (surrogate)");
+    // the products' weights, split once for every trace
+    rti::launch_wsplit((const float *)(d + o_p), (int64_t)P, n_nets, (__bf16 *)(d + o_w), nullptr);
+    if ((e = hipGetLastError()) != hipSuccess || (e = hipStreamSynchronize(nullptr)) != hipSuccess)
+        return hip_fail(c, e, "kernel launch (surrogate weights)");
     rti::SurrArgs S{};
     S.n_nets = n_nets;
-    S.stride = (int64_t)PP;
+    S.stride = (int64_t)P;
     S.n_tab = n_tab;
     S.n_bins = n_bins;
     S.tol = tol;
-    S.wb = (const __bf16 *)(d + o_w);
+    S.wsplit = (const __bf16 *)(d + o_w);
     S.params = (const float *)(d + o_p);
     S.scale = (const float *)(d + o_s);
     S.arc = (const float *)(d + o_a);

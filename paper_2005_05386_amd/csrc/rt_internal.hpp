@@ -40,10 +40,6 @@ constexpr int CTR_XQ = 193;          // offset of the pass's crossing count (sur
 constexpr int CTR_SURR_WORDS = 256;
 constexpr int MAX_NETS = 64;
 constexpr int XC_CNT = 0, XC_ROW = 64, XC_TILE = 136;
-// Per-network parameter stride of the networks the tracer holds (16-byte
-// aligned rows for vector loads of bf16 weights).
-constexpr int64_t MLP_P_PAD = 134920;
-
 constexpr int MAX_PASSES_API = 512;
 constexpr int SCAN_BLOCK = 1024;     // chunks per block of the survivor scan
 
@@ -137,7 +133,7 @@ struct SurrArgs {
     int n_nets, n_tab, n_bins;
     int64_t stride;       // parameters per network in wb / params (multiple of 8)
     float tol;
-    const __bf16 *wb;     // [n_nets][stride], 16-byte aligned
+    const __bf16 *wsplit; // [n_nets][MLP_WSPLIT] W2, W3 in two bf16 parts
     const float *params;  // [n_nets][stride]
     const float *scale;   // [n_nets]
     const float *arc;     // [n_nets][n_tab] arc in units of sigma at cos(theta) = i / (n_tab - 1)
@@ -223,6 +219,10 @@ constexpr int64_t OFF_W1 = 0, OFF_B1 = OFF_W1 + MLP_H * MLP_IN, OFF_W2 = OFF_B1 
                   OFF_W3 = OFF_B2 + MLP_H, OFF_B3 = OFF_W3 + MLP_H * MLP_H, OFF_W4 = OFF_B3 + MLP_H,
                   OFF_B4 = OFF_W4 + MLP_OUT * MLP_H, MLP_P = OFF_B4 + MLP_OUT;
 
+// Values of one network's W2 and W3 as two bf16 parts.
+constexpr int MLP_WSPLIT = 4 * 256 * 256;
+// Fill them (ws [n][MLP_WSPLIT], 16-byte aligned) from FP32 masters `stride` apart.
+void launch_wsplit(const float *params, int64_t stride, int n, __bf16 *ws, hipStream_t s);
 // Workspace of a forward pass kept for the backward: rows in whole tiles of
 // 64, T = tiles per network, Bp = 64 T.
 struct MlpWork {
@@ -231,6 +231,7 @@ struct MlpWork {
     float *z3;             // [n][Bp][256] pre-activations of layer 3
     __bf16 *h1t, *h2t;     // [n][T][256][64] activations (bf16, high part)
     __bf16 *dz2t, *dz3t;   // [n][T][256][64] back-propagated signals
+    __bf16 *ws;            // [n] W2, W3 as two bf16 parts in the forward products' fragment order
     __bf16 *wt;            // [n][2][256 * 256] W2, W3 in the backward products' fragment order
     float *part1, *part4;  // [n][ceil(B/32)][7][256] partial gradients of the FP32 layers
     float *cs2, *cs3;      // [n][T][256] partial bias gradients
@@ -258,6 +259,7 @@ hipError_t launch_cross_cal(const float *X, const float *P, const float *Y, cons
 // Fused grouped MLP forward: ctl holds per-network row offsets at XC_ROW
 // and tile offsets at XC_TILE; uses S.wb, S.params, S.stride, S.n_nets,
 // S.xin, S.xout.
+// launch_mlp_rows fills S.wsplit from S.params first.
 struct GroupCtl {
     int w[XC_TILE + 65];
 };

@@ -82,13 +82,30 @@ __device__ __forceinline__ float dsilu(float z) {
     return s * (1.0f + z * (1.0f - s));
 }
 
-__device__ __forceinline__ void split8(const float *v, bf16x8 &hi, bf16x8 &lo) {
+// W2 and W3 of the FP32 master as the two bf16 parts, in the order a wave reads
+// them as the B operand of h W^T (B(k, n) = W[n][k]): [layer][part] then
+// fragment (n/16, k/32), lane, 8 consecutive k.  A thread splits 8 k.  Split
+// once per call instead of by every tile, and a fragment is one contiguous
+// kilobyte; rows of the master are a kilobyte apart, which spreads a load of
+// sixteen of them over four of L2's sixteen channels.
+constexpr int WSPLIT = rti::MLP_WSPLIT;
+__global__ __launch_bounds__(256) void k_mlp_wsplit(const float *__restrict__ params, int64_t stride,
+                                                    __bf16 *__restrict__ ws) {
+    const int g = blockIdx.y, t = blockIdx.x * 256 + threadIdx.x;  // 2 layers x 16 x 8 x 64
+    const int l = t >> 13, f = t & 8191, lane = f & 63;
+    const int n = (f >> 9) * 16 + (lane & 15), k = ((f >> 6) & 7) * 32 + (lane >> 4) * 8;
+    const float *src = params + (int64_t)g * stride + (l == 0 ? rti::OFF_W2 : rti::OFF_W3) + n * H + k;
+    const f32x4u u0 = *(const f32x4u *)src, u1 = *(const f32x4u *)(src + 4);
+    bf16x8 hi, lo;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        const __bf16 h = (__bf16)v[e];
-        hi[e] = h;
-        lo[e] = (__bf16)(v[e] - (float)h);
+        const float v = e < 4 ? u0[e & 3] : u1[e & 3];
+        hi[e] = (__bf16)v;
+        lo[e] = (__bf16)(v - (float)hi[e]);
     }
+    __bf16 *dst = ws + (int64_t)g * WSPLIT + (int64_t)l * 2 * H * H + f * 8;
+    *(bf16x8 *)dst = hi;
+    *(bf16x8 *)(dst + H * H) = lo;
 }
 
 // Sum over the wave by the butterfly l ^ 32, 16, 8, 4, 2, 1, without LDS: half
@@ -121,16 +138,15 @@ struct KeepTile {
 
 // One 64-row tile (M valid rows, the rest zero inputs) of the network at Pg.
 // Eight waves, wave w owning output columns [32 w, 32 w + 32) of the two
-// products; the tile's activations sit in LDS as the two bf16 parts, the FP32
-// master weights stream through L2 and are split as they arrive, the next
-// slice of 32 k on its way while the current one is multiplied.  Bound by
-// the matrix cores' 3 x 16.8 MFLOP per tile next to the vector work of the
-// splits and SiLUs; 68 KB of LDS and at most 128 registers keep two workgroups,
+// products; the tile's activations sit in LDS as the two bf16 parts, the
+// weights' two parts (Wg) stream through L2 as whole fragments, the next slice
+// of 32 k on its way while the current one is multiplied.  Bound by the matrix
+// cores' 3 x 16.8 MFLOP per tile next to the vector work of the SiLUs; 68 KB of LDS and at most 128 registers keep two workgroups,
 // four waves per SIMD, on a CU, so one's vector work runs under the other's
 // products (four waves of 64 columns, two per SIMD, took @4W@).
 template <bool KEEP>
 __device__ __forceinline__ void forward_tile(char *smem, float (*Xs)[6], const float *__restrict__ Pg,
-                                             const float *__restrict__ X, float *__restrict__ Y, int M,
+                                             const __bf16 *__restrict__ Wg, const float *__restrict__ X, float *__restrict__ Y, int M,
                                              const KeepTile &K) {
     __bf16(*Ah)[AROW] = reinterpret_cast<__bf16(*)[AROW]>(smem);
     __bf16(*Al)[AROW] = Ah + TM;
@@ -173,34 +189,31 @@ __device__ __forceinline__ void forward_tile(char *smem, float (*Xs)[6], const f
     __syncthreads();
 #pragma unroll 1
     for (int l = 0; l < 2; ++l) {
-        const float *__restrict__ W = Pg + (l == 0 ? rti::OFF_W2 : rti::OFF_W3) + (wave * 32 + col) * H + kq;
+        const __bf16 *__restrict__ W = Wg + l * 2 * H * H + (wave * 2 * 8 * 64 + lane) * 8;
         const float *__restrict__ bias = Pg + (l == 0 ? rti::OFF_B2 : rti::OFF_B3) + wave * 32 + col;
         f32x4 acc[4][2];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-        f32x4u raw[2][2];
+        bf16x8 nh[2], nl[2];
+        auto load = [&](int k) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            raw[j][0] = *(const f32x4u *)(W + 16 * j * H);
-            raw[j][1] = *(const f32x4u *)(W + 16 * j * H + 4);
-        }
-#pragma unroll 1
+            for (int j = 0; j < 2; ++j) {
+                nh[j] = *(const bf16x8 *)(W + (j * 8 + k) * 64 * 8);
+                nl[j] = *(const bf16x8 *)(W + (j * 8 + k) * 64 * 8 + H * H);
+            }
+        };
+        load(0);
+#pragma unroll 2
         for (int k0 = 0; k0 < H; k0 += 32) {
             bf16x8 bh[2], bl[2];
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const float v[8] = {raw[j][0][0], raw[j][0][1], raw[j][0][2], raw[j][0][3],
-                                    raw[j][1][0], raw[j][1][1], raw[j][1][2], raw[j][1][3]};
-                split8(v, bh[j], bl[j]);
+                bh[j] = nh[j];
+                bl[j] = nl[j];
             }
-            const int kn = k0 + 32 < H ? k0 + 32 : k0;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                raw[j][0] = *(const f32x4u *)(W + 16 * j * H + kn);
-                raw[j][1] = *(const f32x4u *)(W + 16 * j * H + kn + 4);
-            }
+            load(min(k0 / 32 + 1, 7));
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const bf16x8 ah = *(const bf16x8 *)&Ah[16 * i + col][k0 + kq];
@@ -291,7 +304,7 @@ __global__ __launch_bounds__(NT, 4) void k_mlp_fwd(const float *__restrict__ par
     const int m0 = t * TM;
     const int64_t T = (int64_t)g * tiles + t;
     const KeepTile K{w.xf + T * TM * 6, w.z2 + T * TM * H, w.z3 + T * TM * H, w.h1t + T * TM * H, w.h2t + T * TM * H};
-    forward_tile<true>(smem, Xs, params + g * rti::MLP_P, X + ((int64_t)g * B + m0) * 6, Y + ((int64_t)g * B + m0) * 6,
+    forward_tile<true>(smem, Xs, params + g * rti::MLP_P, w.ws + (int64_t)g * WSPLIT, X + ((int64_t)g * B + m0) * 6, Y + ((int64_t)g * B + m0) * 6,
                        min(TM, B - m0), K);
 }
 
@@ -308,7 +321,7 @@ __device__ __forceinline__ void infer_tiles(const int *__restrict__ ctl, const r
         const int g = __builtin_amdgcn_readfirstlane(__popcll(__ballot(toff <= t)) - 1);
         const int off = ctl[rti::XC_ROW + g], cnt = ctl[rti::XC_ROW + g + 1] - off;
         const int m0 = (t - ctl[rti::XC_TILE + g]) * TM;
-        forward_tile<false>(smem, Xs, S.params + (int64_t)g * S.stride, S.xin + 6 * (int64_t)(off + m0),
+        forward_tile<false>(smem, Xs, S.params + (int64_t)g * S.stride, S.wsplit + (int64_t)g * WSPLIT, S.xin + 6 * (int64_t)(off + m0),
                             S.xout + 6 * (int64_t)(off + m0), min(TM, cnt - m0), KeepTile{});
     }
 }
@@ -681,6 +694,7 @@ template <class F> static void mlp_layout(int n, int batch, MlpWork &w, F take) 
     w.h2t = (__bf16 *)take(rows * MLP_H * 2);
     w.dz2t = (__bf16 *)take(rows * MLP_H * 2);
     w.dz3t = (__bf16 *)take(rows * MLP_H * 2);
+    w.ws = (__bf16 *)take((size_t)n * MLP_WSPLIT * 2);
     w.wt = (__bf16 *)take((size_t)n * 2 * MLP_H * MLP_H * 2);
     w.part1 = (float *)take(n * nch * 7 * MLP_H * 4);
     w.part4 = (float *)take(n * nch * 7 * MLP_H * 4);
@@ -707,9 +721,14 @@ void mlp_work_carve(void *base, int n_nets, int batch, MlpWork &w) {
     });
 }
 
+void launch_wsplit(const float *params, int64_t stride, int n, __bf16 *ws, hipStream_t s) {
+    hipLaunchKernelGGL(k_mlp_wsplit, dim3(64, n), dim3(256), 0, s, params, stride, ws);
+}
+
 // y = MLP(x) for n_nets networks of batch rows each, keeping what a backward
 // pass needs in the workspace.
 hipError_t mlp_forward(int n, int B, const float *params, const float *x, float *y, const MlpWork &w, hipStream_t s) {
+    launch_wsplit(params, MLP_P, n, w.ws, s);
     hipLaunchKernelGGL(k_mlp_fwd, dim3(xcd_grid((B + TM - 1) / TM, 1, n)), dim3(NT), 0, s, params, x, y, n, B, w);
     return hipGetLastError();
 }
@@ -726,6 +745,7 @@ hipError_t mlp_backward(int n, int B, const __bf16 *wb, const float *params, con
 }
 
 hipError_t launch_mlp_rows(const GroupCtl &C, const SurrArgs &S, int blocks, hipStream_t s) {
+    launch_wsplit(S.params, S.stride, S.n_nets, const_cast<__bf16 *>(S.wsplit), s);
     hipLaunchKernelGGL(k_mlp_infer_rows, dim3(blocks), dim3(NT), 0, s, C, S);
     return hipGetLastError();
 }
