@@ -963,14 +963,12 @@ static rt_status trace_impl(rt_ctx *c, const rt_camera *cam, const rt_step_rule 
         int v = std::atoi(g);
         if (v >= 1) grid = v;
     }
-    // Passes of at most four waves per SIMD run the small-launch variant: its
-    // 128 registers allow no more, and that is where the two meet (64x64 to
-    // 721x403 frames with the line at 2, 4, 6 and 8: 4 is best or level
-    // everywhere, 6 and 8 lose 3% on 721x403).
+    // Passes of at most three waves per SIMD run the small-launch variant: its
+    // registers allow four, and the variants meet between two and four (with
+    // the line at 0 / 2 / 4: 721x403 anisotropic bumps 19.2 / 18.1 / 18.4 ms,
+    // 473x458 twist 6.7 / 6.0 / 6.1, 679x676 quadric 3.02 / 3.04 / 2.95).
     a.lat_chunks = 0;
-    if ((c->kind == RT_METRIC_GRAPH_GAUSS || c->kind == RT_METRIC_GRAPH_ANISO) && r->kind != RT_STEP_RK45 && !a.count &&
-        !a.batch && !use_surr)
-        a.lat_chunks = c->n_cu * 4 * 4;
+    if (rti::has_small_variant(a.kind, r->kind) && !a.count && !a.batch && !use_surr) a.lat_chunks = c->n_cu * 4 * 3;
     hipStream_t s = (hipStream_t)stream;
     bool timed = (r->flags & RT_FLAG_TIMING) != 0;
     if (timed) {

@@ -282,5 +282,6 @@ int adjoint_max_bumps();
 // Blocks per CU the trace kernel can keep resident for this kind/step.
 int trace_blocks_per_cu(int kind, int step);
 bool supported(int kind, int step);
+bool has_small_variant(int kernel_kind, int step);  // a pass of few chunks may run the small-launch variant
 
 }  // namespace rti

@@ -78,6 +78,11 @@ __device__ __forceinline__ void write_ckpt(const TraceArgs &A, int id, int c, V3
 // (80 B: also t as two floats and the step size).
 constexpr bool compact_record(int step, bool surr) { return step != STEP_RK45 && !surr; }
 
+// Kinds and integrators with a small-launch variant of the pass kernel.
+constexpr bool has_small_variant(int kind, int step) {
+    return step != STEP_RK45 && kind != KIND_EUCLID && kind != KIND_ZTWIST;
+}
+
 // ========================================================= ray generation
 // Initial state of a ray: x = eye, y = the pixel direction d scaled to unit
 // length in the metric at the eye (y = d / sqrt(g(d, d))).  Computed by the
@@ -109,8 +114,15 @@ __device__ __forceinline__ float4 *batch_save() {
 constexpr bool flat_outside(int kind) {
     return kind == KIND_EUCLID || kind == KIND_GRAPH || kind == KIND_GANISO || is_deform(kind);
 }
+// The twist's acceleration vanishes in the computed arithmetic once
+// rho >= TWIST_FREE: exp(-2 rho) < 2^-25 there, so tanh rho rounds to 1 and
+// the sech^2 terms are exact zeros; what is left carries exp(-rho^2) < 2e-33
+// times at most rho^3, |theta0| <= 1.5 and amp <= 1, and the z component is
+// zero.  With |a| < 1e-27, a velocity component of at least TWIST_MIN_V is the
+// same float after adding h a for any h < 1e4.
+constexpr float TWIST_FREE = 8.7f, TWIST_MIN_V = 1e-15f;
 // Distance from the box [mn, mx] of the wave's positions to the nearest cut
-// region or object, rounded down; called by the whole wave.  Cut regions and
+// region (twist: to the ball of radius TWIST_FREE) or object, rounded down; called by the whole wave.  Cut regions and
 // tori are taken as balls about their centres.
 template <int KIND>
 __device__ __forceinline__ float free_distance(const TraceArgs &A, const float4 *__restrict__ Bs,
@@ -118,7 +130,8 @@ __device__ __forceinline__ float free_distance(const TraceArgs &A, const float4 
                                                const float *__restrict__ TOR, int lane, const float mn[3],
                                                const float mx[3]) {
     float gap = __builtin_huge_valf();
-    if (KIND != KIND_EUCLID && lane < A.n_bumps) {
+    if constexpr (KIND == KIND_TWIST) gap = sqrt_(box_dist2(0.f, 0.f, 0.f, mn, mx)) - TWIST_FREE;
+    if (KIND != KIND_EUCLID && KIND != KIND_TWIST && lane < A.n_bumps) {
         const float4 *__restrict__ q = Bs + (is_deform(KIND) ? DEFORM_F4 : 2) * lane;
         const float4 b0 = q[0], b1 = q[1];
         float R;
@@ -218,21 +231,26 @@ __device__ __forceinline__ void chord_scan(const uint64_t sm[4], uint64_t om, in
 #ifndef RT_GRAPH_WAVES
 #define RT_GRAPH_WAVES 8  // the same for the isotropic graph metric, plain and taped (64 registers, no spill in the step loop)
 #endif
+#ifndef RT_TWIST_WAVES
+#define RT_TWIST_WAVES 6  // the twist (4K frame 198.2 / 197.7 / 205.3 / 203.2 ms at 7 / 6 / 5 / 4)
+#endif
 #ifndef RT_BATCH_WAVES
 #define RT_BATCH_WAVES 6  // the same for the batched-segment variant
 #endif
 #ifndef RT_LAT_WAVES
 #define RT_LAT_WAVES 4  // the same for the small-launch variant
 #endif
-// LAT: the variant for passes of few chunks (graph metrics of bumps, fixed
-// steps; at most lat_chunks, four waves per SIMD).  A wave alone on its SIMD
+// LAT: the variant for passes of few chunks (fixed steps; at most
+// lat_chunks, three waves per SIMD).  A wave alone on its SIMD
 // issues a vector instruction every 5 to 6 cycles and waits out every scalar
 // load, so what counts is the length of its own instruction stream: one or two
 // listed bumps stay in registers for the whole window, more are read from the
 // wave's list in LDS four at a time.  128 registers, no spills.  Against the
 // walk (start of this design, then with free flight and the march below, then
 // this): 64x64, one bump 1.25 / 1.09 / 0.91 ms; 86x84, 61 bumps 16.1 / 17.4 /
-// 11.3 ms; 721x403, 12 anisotropic bumps 20.3 / 19.2 / 18.4 ms.  In launches
+// 11.3 ms; 721x403, 12 anisotropic bumps 20.3 / 19.2 / 18.2 ms.  The other
+// kinds only gain the registers (473x458 twist 8.0 / 6.7 / 6.1 ms, 206x192
+// deformations 2.7 / 1.03 / 0.99 ms).  In launches
 // that fill the SIMDs the walk is faster (the list's padding and register
 // copies are issue slots), so those keep it.
 // BATCH: batched multi-segment intersection (Sec. 4.1 proposes testing many
@@ -246,7 +264,7 @@ __device__ __forceinline__ void chord_scan(const uint64_t sm[4], uint64_t om, in
 // only once its box is cleared.  Windows and object lists only bound the
 // work, so the outputs equal the plain kernel's bit for bit.
 template <int KIND, int STEP, bool COUNT, bool SURR = false, bool TAPE = false, bool BATCH = false, bool LAT = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LAT ? RT_LAT_WAVES : STEP == STEP_RK45 || KIND == KIND_DEFORM_ROT ? 6 : (BATCH ? RT_BATCH_WAVES : (KIND == KIND_GRAPH && !SURR ? RT_GRAPH_WAVES : RT_PASS_WAVES)), 8))) void k_trace_pass(TraceArgs A, int pass, const float4 *__restrict__ BF,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LAT ? RT_LAT_WAVES : STEP == STEP_RK45 || KIND == KIND_DEFORM_ROT ? 6 : (BATCH ? RT_BATCH_WAVES : (KIND == KIND_GRAPH && !SURR ? RT_GRAPH_WAVES : (KIND == KIND_TWIST ? RT_TWIST_WAVES : RT_PASS_WAVES))), 8))) void k_trace_pass(TraceArgs A, int pass, const float4 *__restrict__ BF,
                                                     const float4 *__restrict__ SPH,
                                                     const float4 *__restrict__ PLN,
                                                     const float *__restrict__ TOR) {
@@ -256,16 +274,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LAT ? RT_LA
     // under DP5(4) and learned crossings; fixed-step traces derive t from the
     // step count and neither read nor keep them
     constexpr bool CARRY_T = STEP == STEP_RK45 || SURR;
-    static_assert(!LAT || ((KIND == KIND_GRAPH || KIND == KIND_GANISO) && STEP != STEP_RK45 && !COUNT && !SURR && !BATCH),
-                  "small-launch variant: graph metrics of bumps, fixed steps");
-    float4 *list = nullptr;  // LAT: this wave's bump list
-    if constexpr (LAT) {
+    static_assert(!LAT || (has_small_variant(KIND, STEP) && !COUNT && !SURR && !BATCH),
+                  "small-launch variant: fixed steps, plain and taped");
+    constexpr bool LIST = LAT && (KIND == KIND_GRAPH || KIND == KIND_GANISO);
+    float4 *list = nullptr;  // LIST: this wave's bump list
+    if constexpr (LIST) {
         __shared__ float4 lists[4 * LIST_F4];
         list = lists + (threadIdx.x >> 6) * LIST_F4;
     }
-    int groups = 0;  // LAT: groups of the list
+    int groups = 0;  // LIST: its groups
     constexpr bool TIGHT = STEP != STEP_RK45 && !COUNT && !SURR && !BATCH;
-    constexpr bool FREE = flat_outside(KIND) && !COUNT && !SURR && !BATCH;
+    constexpr bool FLAT = flat_outside(KIND) && !COUNT && !SURR && !BATCH;
+    constexpr bool FREE = FLAT || (KIND == KIND_TWIST && STEP != STEP_RK45 && !COUNT && !SURR && !BATCH);
     const int lane = lane_id();
     const int xcd0 = blockIdx.x % N_XCD;
     int *pass_ctr = A.ctr + rti::CTR_PASS0 + pass * rti::CTR_PASS_WORDS;
@@ -513,7 +533,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LAT ? RT_LA
                             need = rho * rho <= Bs[DEFORM_F4 * lane + 2].w * 1.00001f;
                         }
                         bmask = ballot(need);
-                        if constexpr (LAT) groups = list_fill<KIND == KIND_GANISO>(list, bmask, need, b0, b1);
+                        if constexpr (LIST) groups = list_fill<KIND == KIND_GANISO>(list, bmask, need, b0, b1);
                         else if constexpr (TIGHT && KIND == KIND_GRAPH) cutm = ballot(beyond);
 #pragma unroll
                         for (int w = 0; w < 4; ++w) {
@@ -554,10 +574,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LAT ? RT_LA
                             // and so are those of the further windows that end before the
                             // nearest cut region or object.  There a g-unit velocity has
                             // Euclidean speed 1 (2% margin), the step's stages included.
-                            if (((KIND == KIND_EUCLID ? 0ull : bmask) | sm[0] | sm[1] | sm[2] | sm[3] | omask) == 0) {
+                            // The twist is free only beyond its ball, and only if no
+                            // velocity component is too small to absorb its acceleration.
+                            const bool empty = ((FLAT && KIND != KIND_EUCLID ? bmask : 0ull) | sm[0] | sm[1] | sm[2] | sm[3] | omask) == 0;
+                            if (empty && (FLAT || ballot(act && !(fminf(fabsf(y.x), fabsf(y.y)) >= TWIST_MIN_V)) == 0)) {
                                 const float D = free_distance<KIND>(A, Bs, SPH, PLN, TOR, lane, pmn, pmx);
-                                const float q = fminf((D - 2e-4f) * rcp_(1.02f * A.h_max), 1e6f);
-                                n_free = max((int)q - 2, A.K) / A.K * A.K;
+                                const float q = fminf((D - 2e-4f) * rcp_((FLAT ? 1.02f : 1.08f) * A.h_max), 1e6f);
+                                n_free = (int)q - 2;
+                                if constexpr (FLAT) n_free = max(n_free, A.K);
+                                // (adaptive steps cull at multiples of the window)
+                                if constexpr (!TIGHT) n_free = n_free / A.K * A.K;
+                                n_free = max(n_free, 0);
                             }
                         }
                     }
@@ -720,7 +747,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LAT ? RT_LA
                             for (; j < n; ++j) {
                                 checkpoint();
                                 const V3<float> p = xh + xl;
-                                if (FREE && KIND != KIND_EUCLID && bmask == 0) {
+                                if (FLAT && KIND != KIND_EUCLID && bmask == 0) {
                                     // objects but no bump in the window
                                     dx = free_step<STEP>(y, A.h);
                                     dv = mk(0.f, 0.f, 0.f);
@@ -737,7 +764,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LAT ? RT_LA
                                 y = y + dv;
                             }
                         };
-                        if constexpr (LAT) {
+                        if constexpr (LIST) {
                             constexpr bool AN = KIND == KIND_GANISO;
                             const int nb = __popcll(bmask);
                             if (nb == 1) march(HeldAcc<AN, 1>(Bs, bmask));
@@ -1386,7 +1413,7 @@ hipError_t launch_pass(const TraceArgs &a, const rti::DeviceData &d, int p, int 
             return hipGetLastError();
         }
     }
-    if constexpr ((KIND == KIND_GRAPH || KIND == KIND_GANISO) && STEP != STEP_RK45 && !SURR) {
+    if constexpr (has_small_variant(KIND, STEP) && !SURR) {
         // the small-launch variant: the first pass by its known chunk count, a
         // later pass by the survivors (each variant reads the count and only
         // one proceeds; frames that are small to begin with need one launch)
@@ -1463,6 +1490,8 @@ template <int KIND, int STEP> int occ() {
 }  // namespace
 
 namespace rti {
+
+bool has_small_variant(int kind, int step) { return ::has_small_variant(kind, step); }
 
 bool supported(int kind, int step) {
     return kind >= 0 && kind <= 7 && step >= 0 && step <= 2;

@@ -56,7 +56,17 @@ def aniso(n):
     return wl
 
 
+def far_twist():
+    """The twist seen from beyond the radius where it is flat: flights in and out."""
+    wl = W.get("twist_4k")
+    wl["camera"] = dict(wl["camera"], eye=W.f32((0.3, 0.2, -12.0)))
+    return wl
+
+
 CASES = {
+    "twist_far": (far_twist, {"h": 0.01}),
+    "twist_far_rk45": (far_twist, {"kind": W.RK45, "h_max": 0.02, "t_max": 25.0, "pass_steps": 4000}),
+    "twist_euler": (lambda: W.get("twist_4k"), {"kind": W.EULER}),
     "bumps16": (lambda: W.get("bumps16_1080p"), {}),
     "euler": (lambda: W.get("bumps16_1080p"), {"kind": W.EULER}),
     "rk45": (lambda: W.get("bumps16_1080p_rk45"), {}),
@@ -89,12 +99,14 @@ def test_equals_counted_trace(rt, name, size):
     same(rt, wl, dict(wl["rule"], **rule))
 
 
-@pytest.mark.parametrize("size", [(512, 512), (520, 512)])
-def test_both_sides_of_the_small_launch_line(rt, size):
-    """4096 chunks run the small-launch variant from the first pass on; 4160
-    start in the other and hand the later passes over as rays end."""
-    print("[gpu-case] small-launch line", size, flush=True)
-    wl = W.with_size(W.get("bumps16_1080p"), *size)
+@pytest.mark.parametrize("name", ["bumps16_1080p", "twist_4k", "deform16_1080p"])
+@pytest.mark.parametrize("size", [(512, 384), (520, 384), (512, 512)])
+def test_both_sides_of_the_small_launch_line(rt, size, name):
+    """On 256 CUs 3072 chunks run the small-launch variant from the first pass
+    on; 3120 and 4096 start in the other and hand the later passes over as
+    rays end."""
+    print("[gpu-case] small-launch line", name, size, flush=True)
+    wl = W.with_size(W.get(name), *size)
     same(rt, wl, dict(wl["rule"], pass_steps=128, h=0.02, max_steps=1000))
 
 
