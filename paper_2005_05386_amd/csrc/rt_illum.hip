@@ -84,31 +84,97 @@ __device__ __forceinline__ uint64_t bump_window(const float4 *__restrict__ Bs, i
     return mask;
 }
 
-// Integrate the geodesic from (q, v) over arc length T: n = ceil(T / h)
-// RK4 steps, the last one shortened; two-float position.  Returns false on
-// a non-finite state or a step budget overrun.
+// Steps of length h that every lane with `on` can take from p before it can
+// reach a cut region (an anisotropic one taken as a ball), by the speed bound
+// |y| <= 1 with a 2% margin; called by the whole wave.
 template <int KIND>
-__device__ __forceinline__ bool shoot(IAcc<KIND> &acc, const rti::IllumArgs &A, V3<float> q, V3<float> v, float T,
-                                      V3<float> &X, V3<float> &Y) {
+__device__ __forceinline__ int free_steps(const float4 *__restrict__ Bs, int n, V3<float> p, bool on, float h) {
+    float gap = 1e6f;
+    for (int b = 0; b < n; ++b) {
+        const float4 b0 = Bs[2 * b], b1 = Bs[2 * b + 1];
+        const V3<float> d = mk(p.x - b0.x, p.y - b0.y, p.z - b0.z);
+        float R;
+        if constexpr (KIND == KIND_GRAPH) R = sqrt_(b1.z);
+        else R = sqrt_(b1.w) * rsqrt_(fminf(fminf(b1.x, b1.y), b1.z));
+        gap = fminf(gap, sqrt_(dot(d, d)) - R * 1.0001f);
+    }
+    const float q = (wave_min(on ? gap : 1e6f) * 0.999f - 2e-4f) * rcp_(1.02f * h);
+    return max((int)fminf(q, 1e6f) - 2, 0);
+}
+
+// Integrate the geodesic from (q, v) over arc length T: n = ceil(T / h)
+// RK4 steps, the last one shortened; two-float position.  False on a
+// non-finite state or a step budget overrun (and for lanes not active, which
+// only take part in the wave's questions: called by the whole wave).  Where
+// the window reaches no bump the lanes fly free, a constant increment per
+// step, until the nearest cut region: the long shots of the last iterations
+// spend most of their length outside the bumps.
+template <int KIND>
+__device__ __forceinline__ bool shoot(IAcc<KIND> &acc, const rti::IllumArgs &A, bool active, V3<float> q, V3<float> v,
+                                      float T, V3<float> &X, V3<float> &Y) {
     const float h = A.h;
-    const int n = max(1, (int)ceilf(T / h));
-    if (n > A.max_steps) return false;
+    int n = active ? max(1, (int)ceilf(T / h)) : 0;
+    bool ok = active && n <= A.max_steps;
+    if (!ok) n = 0;
     V3<float> xh = q, xl = mk(0.f, 0.f, 0.f), y = v;
-    for (int i = 0; i < n; ++i) {
-        if constexpr (bump_cull<KIND>)
-            if (i % rti::ILLUM_CULL_EVERY == 0 && A.cull_margin >= 0.f)
-                acc.mask = bump_window<KIND>(acc.B, A.n_bumps, lane_box(xh + xl, A.cull_margin));
-        const float hs = i == n - 1 ? T - (float)(n - 1) * h : h;
-        V3<float> dx, dv;
-        if (!step_rk4<float>(acc, xh + xl, y, hs, dx, dv) || !finite6(dx, dv)) return false;
-        two_sum_add(xh.x, xl.x, dx.x);
-        two_sum_add(xh.y, xl.y, dx.y);
-        two_sum_add(xh.z, xl.z, dx.z);
-        y = y + dv;
+    int wend = 0;
+    for (int i = 0; ballot(i < n) != 0;) {
+        if constexpr (bump_cull<KIND>) {
+            if (i >= wend && A.cull_margin >= 0.f) {
+                wend = i + rti::ILLUM_CULL_EVERY;
+                const bool on = i < n;
+                uint64_t mask = 0;
+                if (on) mask = bump_window<KIND>(acc.B, A.n_bumps, lane_box(xh + xl, A.cull_margin));
+                // (the same for every lane with on)
+                const int src = __builtin_ctzll(ballot(on));
+                acc.mask = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mask, src) |
+                           ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mask >> 32), src) << 32);
+                if (acc.mask == 0) {
+                    const V3<float> dx = free_step<STEP_RK4>(y, h);
+                    const int m = free_steps<KIND>(acc.B, A.n_bumps, xh + xl, on, h);
+                    if (m > 0 && ballot(on && !finite6(dx, mk(0.f, 0.f, 0.f))) == 0) {
+                        if (on) {
+                            y = y + mk(0.f, 0.f, 0.f);
+                            const int c = min(m, n - 1 - i);
+                            for (int j = 0; j < c; ++j) {
+                                two_sum_add(xh.x, xl.x, dx.x);
+                                two_sum_add(xh.y, xl.y, dx.y);
+                                two_sum_add(xh.z, xl.z, dx.z);
+                            }
+                            if (c < m) {
+                                // the lane's last, shortened step
+                                const V3<float> dl = free_step<STEP_RK4>(y, T - (float)(n - 1) * h);
+                                two_sum_add(xh.x, xl.x, dl.x);
+                                two_sum_add(xh.y, xl.y, dl.y);
+                                two_sum_add(xh.z, xl.z, dl.z);
+                                n = 0;
+                            }
+                        }
+                        i += m;
+                        wend = i;
+                        continue;
+                    }
+                }
+            }
+        }
+        if (i < n) {
+            const float hs = i == n - 1 ? T - (float)(n - 1) * h : h;
+            V3<float> dx, dv;
+            if (!step_rk4<float>(acc, xh + xl, y, hs, dx, dv) || !finite6(dx, dv)) {
+                ok = false;
+                n = 0;
+            } else {
+                two_sum_add(xh.x, xl.x, dx.x);
+                two_sum_add(xh.y, xl.y, dx.y);
+                two_sum_add(xh.z, xl.z, dx.z);
+                y = y + dv;
+            }
+        }
+        ++i;
     }
     X = xh + xl;
     Y = y;
-    return true;
+    return ok;
 }
 
 // March the same geodesic with the chord of every step tested against the
@@ -272,8 +338,8 @@ enum { ST_LIT = 1, ST_BLOCKED = 0, ST_AWAY = 2, ST_NONE = -1, ST_NOHIT = -3, ST_
 
 // The target of the shots of pixel P: the light, or during the
 // continuation the point q + cont (L - q) of the straight segment.
-template <class P> __device__ __forceinline__ V3<float> target(const rti::IllumArgs &A, const P &Px, V3<float> L) {
-    return A.cont < 1.f ? axpy(A.cont, L - Px.q, Px.q) : L;
+template <class P> __device__ __forceinline__ V3<float> target(float cont, const P &Px, V3<float> L) {
+    return cont < 1.f ? axpy(cont, L - Px.q, Px.q) : L;
 }
 
 // Initial state: pixels that hit start from the straight segment.
@@ -301,26 +367,23 @@ __global__ __launch_bounds__(256) void k_illum_init(rti::IllumArgs A, const floa
     }
 }
 
-// Residual of the base shot of pixel pix: returns 1 when a Newton step is
-// to be taken, 0 when the pixel leaves the list (converged, marked ST_CONV,
-// or stalled: from the fifth iteration on, a residual that did not halve).
-__device__ __forceinline__ int judge(const rti::IllumArgs &A, int pix, int it, V3<float> F) {
+// Residual F of the base shot in iteration it: a Newton step is to be taken,
+// or the pixel leaves the list, converged or stalled (from the fifth iteration
+// on, a residual that did not halve).  last: the previous residual, updated.
+enum { J_STEP, J_CONV, J_STALL };
+__device__ __forceinline__ int judge(const rti::IllumArgs &A, int it, V3<float> F, float &last) {
     const float fn = fmaxf(fabsf(F.x), fmaxf(fabsf(F.y), fabsf(F.z)));
-    const bool stalled = it >= 4 && fn > 0.5f * A.w_F[pix];
-    A.w_F[pix] = fn;
-    if (fn < A.tol) {
-        A.status[pix] = A.conv_code;
-        return 0;
-    }
-    return stalled ? 0 : 1;
+    const bool stalled = it >= 4 && fn > 0.5f * last;
+    last = fn;
+    return fn < A.tol ? J_CONV : (stalled ? J_STALL : J_STEP);
 }
 
 // Damped Newton step on (al, be, T) from the residual F = X - L, the end
 // velocity Y (the T column) and the shots Xa, Xb at al + eps, be + eps;
 // true when the pixel stays on the list.
 template <int KIND>
-__device__ __forceinline__ bool newton(const rti::IllumArgs &A, const Pixel<KIND> &P, int pix, V3<float> L, float eps,
-                                      float al, float be, float T, V3<float> F, V3<float> X, V3<float> Y,
+__device__ __forceinline__ bool newton(const rti::IllumArgs &A, const Pixel<KIND> &P, V3<float> L, float eps,
+                                      float &al, float &be, float &T, V3<float> F, V3<float> X, V3<float> Y,
                                       V3<float> Xa, V3<float> Xb) {
     const V3<float> ca = (1.f / eps) * (Xa - X), cb = (1.f / eps) * (Xb - X);
     const float M[9] = {ca.x, cb.x, Y.x, ca.y, cb.y, Y.y, ca.z, cb.z, Y.z};
@@ -338,17 +401,114 @@ __device__ __forceinline__ bool newton(const rti::IllumArgs &A, const Pixel<KIND
     const float sa = m > 0.3f ? 0.3f / m : 1.f;
     const float sT = fabsf(dT) > 0.5f * T ? 0.5f * T / fabsf(dT) : 1.f;
     const float sc = fminf(sa, sT);
-    A.w_al[pix] = al + sc * da;
-    A.w_be[pix] = be + sc * db;
-    A.w_T[pix] = T + sc * dT;
+    al = al + sc * da;
+    be = be + sc * db;
+    T = T + sc * dT;
     // geodesics much longer than the straight segment are not pursued
-    return T + sc * dT <= 4.f * sqrtf(P.gdd(A, L - P.q)) + 1.f;
+    return T <= 4.f * sqrtf(P.gdd(A, L - P.q)) + 1.f;
 }
 
 // Pixels per wave when the three shots of an iteration run on three lanes.
 constexpr int PAR_PIX = 21;
 // Angle displacement of the finite-difference shots.
 constexpr float ILLUM_EPS = 1e-3f;
+
+// Waves that a short list is spread over: two per SIMD.  More would share the
+// vector issue, fewer would leave SIMDs without one.
+constexpr int SOLVE_WAVES = 2048;
+
+// A list is short while 8192 waves (one pass of the GPU) hold it at three
+// lanes per pixel.
+constexpr int SHORT_LIST = 8192 * PAR_PIX;
+// Blocks of four waves that hold any short list of a frame of n pixels, and
+// SOLVE_WAVES waves.
+inline int solve_blocks(int64_t n) {
+    return (int)std::max<int64_t>(SOLVE_WAVES / 4, (std::min<int64_t>(n, SHORT_LIST) + 4 * PAR_PIX - 1) / (4 * PAR_PIX));
+}
+
+// A short list[it & 1]: the pixels' remaining iterations, each pixel on its
+// own; the launches that follow find their lists empty.  Lanes 3j, 3j+1, 3j+2
+// of a wave shoot the base and the two displaced directions of pixel j side by
+// side; lane 3j judges, takes the Newton step and hands the new state to its
+// neighbours.  During the continuation a pixel that converges goes on to the
+// next stage's target at once.  A shot is a serial chain of up to thousands of
+// steps, so a launch per iteration lasted as long as its longest shot, and the
+// sum of those maxima was most of the time; here a pixel's time is the sum of
+// its own shots.  Same values as the launches one by one.
+template <int KIND, bool ONE>
+__global__ __launch_bounds__(256) void k_illum_solve(rti::IllumArgs A, const float4 *__restrict__ BF, int it) {
+    const int *in = A.list[it & 1];
+    const int n_in = A.ctr[it];
+    if (n_in > SHORT_LIST) return;
+    const uint64_t all = all_bumps(A.n_bumps);
+    const V3<float> L = mk(A.light[0], A.light[1], A.light[2]);
+    const float eps = ILLUM_EPS;
+    const int lane = lane_id(), role = lane % 3, src = lane - role;
+    const int per_wave = min(PAR_PIX, max(1, (n_in + SOLVE_WAVES - 1) / SOLVE_WAVES));
+    const int base = (blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6)) * per_wave;
+    if (base >= n_in) return;
+    const int k = base + lane / 3;
+    bool live = lane < 3 * per_wave && k < n_in;
+    int pix = 0;
+    float al = 0.f, be = 0.f, T = 0.f, last = 0.f, cont = A.cont;
+    int code = A.conv_code;
+    Pixel<KIND> P{};
+    P.Bs = BF;  // (idle lanes: any table)
+    if (live) {
+        pix = in[k];
+        P = pixel<KIND, ONE>(A, BF, pix);
+        al = A.w_al[pix];
+        be = A.w_be[pix];
+        T = A.w_T[pix];
+        last = A.w_F[pix];
+    }
+    while (ballot(live)) {
+        bool ok = false;
+        V3<float> X = mk(0.f, 0.f, 0.f), Y = X;
+        V3<float> v = X;
+        if (live) v = P.dir(A, role == 1 ? al + eps : al, role == 2 ? be + eps : be);
+        IAcc<KIND> acc{P.Bs, all, A.twist_amp, A.twist_theta0, nullptr, nullptr};
+        ok = shoot<KIND>(acc, A, live, P.q, v, T, X, Y);
+        // the displaced shots to lane 3j
+        const int s1 = min(lane + 1, 63), s2 = min(lane + 2, 63);
+        const V3<float> Xa = mk(__shfl(X.x, s1), __shfl(X.y, s1), __shfl(X.z, s1));
+        const V3<float> Xb = mk(__shfl(X.x, s2), __shfl(X.y, s2), __shfl(X.z, s2));
+        const int oka = __shfl((int)ok, s1), okb = __shfl((int)ok, s2);
+        int next = 0;  // iterations done if the pixel goes on, else 0
+        if (live && role == 0 && ok) {
+            const V3<float> Lp = target(cont, P, L);
+            const V3<float> F = X - Lp;
+            const int j = judge(A, it, F, last);
+            if (j == J_STEP) {
+                if (oka && okb && newton<KIND>(A, P, Lp, eps, al, be, T, F, X, Y, Xa, Xb) && it + 1 < A.max_iters)
+                    next = it + 1;
+            } else if (j == J_CONV && code == ST_CONT) {
+                // the next stage of the continuation starts from here
+                const int st = (int)(cont * rti::ILLUM_CONT_STAGES + 0.5f);
+                const float lam0 = (float)st / rti::ILLUM_CONT_STAGES, lam1 = (float)(st + 1) / rti::ILLUM_CONT_STAGES;
+                T *= lam1 / lam0;
+                last = __builtin_huge_valf();
+                cont = lam1;
+                code = st + 1 < rti::ILLUM_CONT_STAGES ? ST_CONT : ST_CONV;
+                next = -1;
+            } else if (j == J_CONV) {
+                A.status[pix] = code;
+            }
+            if (next == 0) {
+                A.w_al[pix] = al;
+                A.w_be[pix] = be;
+                A.w_T[pix] = T;
+                A.w_F[pix] = last;
+            }
+        }
+        next = __shfl(next, src);
+        al = __shfl(al, src);
+        be = __shfl(be, src);
+        T = __shfl(T, src);
+        live = live && next != 0;
+        it = max(next, 0);
+    }
+}
 
 // One Newton iteration for every pixel of list[it & 1]: shoot; converged
 // pixels are marked, the others take a damped step and move to the next list.
@@ -357,65 +517,42 @@ constexpr float ILLUM_EPS = 1e-3f;
 // step keeps its end point and velocity and goes to the step list, whose
 // displaced shots k_illum_step takes two lanes per pixel; so lanes whose
 // pixel converged do not wait on the displaced shots of their neighbours.
-// Once the list fits in one pass at three lanes per pixel (the
-// latency-bound last iterations), lanes 3j, 3j+1, 3j+2 of a wave shoot the
-// base and the two displaced directions of pixel j side by side and the
-// step list stays empty.  Both ways compute the same values.
+// A short list may have been solved by k_illum_solve before (solved: leave it).
+// Both ways compute the same values.
 template <int KIND, bool ONE>
-__global__ __launch_bounds__(256) void k_illum_iter(rti::IllumArgs A, const float4 *__restrict__ BF, int it) {
+__global__ __launch_bounds__(256) void k_illum_iter(rti::IllumArgs A, const float4 *__restrict__ BF, int it, bool solved) {
     const int *in = A.list[it & 1];
-    int *out = A.list[(it + 1) & 1];
     const int n_in = A.ctr[it];
     const uint64_t all = all_bumps(A.n_bumps);
     const V3<float> L = mk(A.light[0], A.light[1], A.light[2]);
-    const float eps = ILLUM_EPS;
-    const int per_block = PAR_PIX * (blockDim.x / 64);
-    if (n_in <= (int)gridDim.x * per_block) {
-        const int lane = lane_id(), role = lane % 3;
-        for (int base = blockIdx.x * per_block; base < n_in; base += gridDim.x * per_block) {
-            const int k = base + (threadIdx.x >> 6) * PAR_PIX + lane / 3;
-            const bool act = lane < 3 * PAR_PIX && k < n_in;
-            bool again = false, ok = false;
-            int pix = 0;
-            V3<float> X = mk(0.f, 0.f, 0.f), Y = X;
-            float al = 0.f, be = 0.f, T = 0.f;
-            Pixel<KIND> P{};
-            if (act) {
-                pix = in[k];
-                P = pixel<KIND, ONE>(A, BF, pix);
-                IAcc<KIND> acc{P.Bs, all, A.twist_amp, A.twist_theta0, nullptr, nullptr};
-                al = A.w_al[pix];
-                be = A.w_be[pix];
-                T = A.w_T[pix];
-                const float as = role == 1 ? al + eps : al, bs = role == 2 ? be + eps : be;
-                ok = shoot<KIND>(acc, A, P.q, P.dir(A, as, bs), T, X, Y);
-            }
-            // the displaced shots of lanes 3j+1, 3j+2 to lane 3j
-            const int src = lane + 1 < 64 ? lane + 1 : lane, src2 = lane + 2 < 64 ? lane + 2 : lane;
-            const V3<float> Xa = mk(__shfl(X.x, src), __shfl(X.y, src), __shfl(X.z, src));
-            const V3<float> Xb = mk(__shfl(X.x, src2), __shfl(X.y, src2), __shfl(X.z, src2));
-            const int oka = __shfl((int)ok, src), okb = __shfl((int)ok, src2);
-            if (act && role == 0 && ok) {
-                const V3<float> Lp = target(A, P, L);
-                const V3<float> F = X - Lp;
-                if (judge(A, pix, it, F) && oka && okb) again = newton<KIND>(A, P, pix, Lp, eps, al, be, T, F, X, Y, Xa, Xb);
-            }
-            append(out, A.ctr + it + 1, pix, again);
-        }
-        return;
-    }
+    if (solved && n_in <= SHORT_LIST) return;
     int *steps = A.list[2];
     for (int base = blockIdx.x * blockDim.x; base < n_in; base += gridDim.x * blockDim.x) {
         const int k = base + threadIdx.x;
+        const bool act = k < n_in;
         bool due = false;
         int pix = 0;
-        if (k < n_in) {
+        Pixel<KIND> P{};
+        P.Bs = BF;
+        V3<float> X = mk(0.f, 0.f, 0.f), Y = X, v = X;
+        float T = 0.f;
+        if (act) {
             pix = in[k];
-            const Pixel<KIND> P = pixel<KIND, ONE>(A, BF, pix);
-            IAcc<KIND> acc{P.Bs, all, A.twist_amp, A.twist_theta0, nullptr, nullptr};
-            V3<float> X, Y;
-            if (shoot<KIND>(acc, A, P.q, P.dir(A, A.w_al[pix], A.w_be[pix]), A.w_T[pix], X, Y) &&
-                judge(A, pix, it, X - target(A, P, L))) {
+            P = pixel<KIND, ONE>(A, BF, pix);
+            T = A.w_T[pix];
+            v = P.dir(A, A.w_al[pix], A.w_be[pix]);
+        }
+        IAcc<KIND> acc{P.Bs, all, A.twist_amp, A.twist_theta0, nullptr, nullptr};
+        const bool ok = shoot<KIND>(acc, A, act, P.q, v, T, X, Y);
+        if (act) {
+            int j = J_STALL;
+            if (ok) {
+                float last = A.w_F[pix];
+                j = judge(A, it, X - target(A.cont, P, L), last);
+                A.w_F[pix] = last;
+                if (j == J_CONV) A.status[pix] = A.conv_code;
+            }
+            if (j == J_STEP) {
                 A.w_X[3 * pix] = X.x;
                 A.w_X[3 * pix + 1] = X.y;
                 A.w_X[3 * pix + 2] = X.z;
@@ -445,21 +582,22 @@ __global__ __launch_bounds__(256) void k_illum_step(rti::IllumArgs A, const floa
     for (int base = blockIdx.x * per_block; base < n_st; base += gridDim.x * per_block) {
         const int k = base + (threadIdx.x >> 1);
         const bool act = k < n_st;
-        bool again = false, ok = false;
+        bool again = false;
         int pix = 0;
-        V3<float> Xs = mk(0.f, 0.f, 0.f), Ys = Xs;
+        V3<float> Xs = mk(0.f, 0.f, 0.f), Ys = Xs, v = Xs;
         float al = 0.f, be = 0.f, T = 0.f;
         Pixel<KIND> P{};
+        P.Bs = BF;
         if (act) {
             pix = steps[k];
             P = pixel<KIND, ONE>(A, BF, pix);
-            IAcc<KIND> acc{P.Bs, all, A.twist_amp, A.twist_theta0, nullptr, nullptr};
             al = A.w_al[pix];
             be = A.w_be[pix];
             T = A.w_T[pix];
-            const float as = role == 0 ? al + eps : al, bs = role == 1 ? be + eps : be;
-            ok = shoot<KIND>(acc, A, P.q, P.dir(A, as, bs), T, Xs, Ys);
+            v = P.dir(A, role == 0 ? al + eps : al, role == 1 ? be + eps : be);
         }
+        IAcc<KIND> acc{P.Bs, all, A.twist_amp, A.twist_theta0, nullptr, nullptr};
+        const bool ok = shoot<KIND>(acc, A, act, P.q, v, T, Xs, Ys);
         // the beta shot of lane 2j+1 to lane 2j
         const int src = lane | 1;
         const V3<float> Xb = mk(__shfl(Xs.x, src), __shfl(Xs.y, src), __shfl(Xs.z, src));
@@ -467,8 +605,11 @@ __global__ __launch_bounds__(256) void k_illum_step(rti::IllumArgs A, const floa
         if (act && role == 0 && ok && okb) {
             const V3<float> X = mk(A.w_X[3 * pix], A.w_X[3 * pix + 1], A.w_X[3 * pix + 2]);
             const V3<float> Y = mk(A.w_Y[3 * pix], A.w_Y[3 * pix + 1], A.w_Y[3 * pix + 2]);
-            const V3<float> Lp = target(A, P, L);
-            again = newton<KIND>(A, P, pix, Lp, eps, al, be, T, X - Lp, X, Y, Xs, Xb);
+            const V3<float> Lp = target(A.cont, P, L);
+            again = newton<KIND>(A, P, Lp, eps, al, be, T, X - Lp, X, Y, Xs, Xb);
+            A.w_al[pix] = al;
+            A.w_be[pix] = be;
+            A.w_T[pix] = T;
         }
         append(out, A.ctr + it + 1, pix, again);
     }
@@ -619,10 +760,14 @@ __global__ __launch_bounds__(256) void k_illum_cont(rti::IllumArgs A, const floa
 
 template <int KIND, bool ONE>
 void illum_rounds(const rti::IllumArgs &a, const rti::DeviceData &d, int grid, hipStream_t s) {
-    for (int it = 0; it < a.max_iters; ++it) {
-        hipLaunchKernelGGL((k_illum_iter<KIND, ONE>), dim3(grid), dim3(256), 0, s, a, d.bump_f, it);
-        hipLaunchKernelGGL((k_illum_step<KIND, ONE>), dim3(grid), dim3(256), 0, s, a, d.bump_f, it);
-    }
+    const int sgrid = solve_blocks((int64_t)a.n_sets * a.width * a.height);
+    // one iteration's launches; solve: the pixels of a short list go to their end
+    auto iteration = [&](const rti::IllumArgs &q, int it, bool solve) {
+        if (solve) hipLaunchKernelGGL((k_illum_solve<KIND, ONE>), dim3(sgrid), dim3(256), 0, s, q, d.bump_f, it);
+        hipLaunchKernelGGL((k_illum_iter<KIND, ONE>), dim3(grid), dim3(256), 0, s, q, d.bump_f, it, solve);
+        hipLaunchKernelGGL((k_illum_step<KIND, ONE>), dim3(grid), dim3(256), 0, s, q, d.bump_f, it);
+    };
+    for (int it = 0; it < a.max_iters; ++it) iteration(a, it, true);
     // retries from converged neighbours, a quarter of the iterations each (a
     // seed from a neighbour is close: 1080p 432 -> 390 ms for 99.88 -> 99.83%
     // of the hits found, the quadric unchanged); each round has its own
@@ -632,10 +777,7 @@ void illum_rounds(const rti::IllumArgs &a, const rti::DeviceData &d, int grid, h
     for (int round = 1; round <= rti::ILLUM_RETRY_ROUNDS; ++round) {
         r.ctr = a.ctr + round * 2 * (a.max_iters + 1);
         hipLaunchKernelGGL((k_illum_seed<KIND, ONE>), dim3(grid), dim3(256), 0, s, r, d.bump_f, r.ctr);
-        for (int it = 0; it < r.max_iters; ++it) {
-            hipLaunchKernelGGL((k_illum_iter<KIND, ONE>), dim3(grid), dim3(256), 0, s, r, d.bump_f, it);
-            hipLaunchKernelGGL((k_illum_step<KIND, ONE>), dim3(grid), dim3(256), 0, s, r, d.bump_f, it);
-        }
+        for (int it = 0; it < r.max_iters; ++it) iteration(r, it, it == 0);
     }
     // continuation in the light position for the pixels still unsolved, half
     // the iterations per stage (a quarter loses 15% of the quadric's hits)
@@ -646,10 +788,7 @@ void illum_rounds(const rti::IllumArgs &a, const rti::DeviceData &d, int grid, h
         r.cont = lam1;
         r.conv_code = st + 1 < rti::ILLUM_CONT_STAGES ? ST_CONT : ST_CONV;
         hipLaunchKernelGGL((k_illum_cont<KIND, ONE>), dim3(grid), dim3(256), 0, s, r, d.bump_f, r.ctr, lam0, lam1);
-        for (int it = 0; it < r.max_iters; ++it) {
-            hipLaunchKernelGGL((k_illum_iter<KIND, ONE>), dim3(grid), dim3(256), 0, s, r, d.bump_f, it);
-            hipLaunchKernelGGL((k_illum_step<KIND, ONE>), dim3(grid), dim3(256), 0, s, r, d.bump_f, it);
-        }
+        for (int it = 0; it < r.max_iters; ++it) iteration(r, it, it == 0);
     }
     hipLaunchKernelGGL((k_illum_finish<KIND, ONE>), dim3(grid), dim3(256), 0, s, a, d.bump_f, d.sph_f, d.pln_f,
                        d.tor_f);
