@@ -191,6 +191,17 @@ __device__ __forceinline__ float rk4_vjp(const float4 *__restrict__ B, uint64_t 
     return sb;
 }
 
+// rk4_vjp where no bump acts at any stage: the new position is p + sg y and the
+// velocity stays, so only Vb changes (the sums of rk4_vjp in its order).
+__device__ __forceinline__ void free_vjp(float sg, V3<float> Xb, V3<float> &Vb) {
+    const float h6 = sg * (1.0f / 6.0f);
+    const V3<float> Y1 = (1.f * h6) * Xb, Y2 = (2.f * h6) * Xb;
+    Vb = Vb + Y1;
+    Vb = Vb + Y2;
+    Vb = Vb + Y2;
+    Vb = Vb + Y1;
+}
+
 // Gradient of the implicit function of object id at x.
 __device__ __forceinline__ V3<float> obj_grad(const TraceArgs &A, const float4 *__restrict__ SPH,
                                               const float4 *__restrict__ PLN, const float *__restrict__ TOR, int id,
@@ -358,9 +369,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
                 if (j + 1 < lmax) {
                     if (j % CULL == 0) wm = cull_mask(Bs, nb, h0 + l0, j + 1 < len, margin);
                     if (j + 1 < len) {
-                        Acc32<KIND_GRAPH, false> accw{Bs, wm, 0.f, 0.f, nullptr, nullptr};
-                        V3<float> dx, dv;
-                        step_rk4<float>(accw, h0 + l0, y0, A.h, dx, dv);
+                        V3<float> dx, dv = mk(0.f, 0.f, 0.f);
+                        if (wm == 0) {
+                            dx = free_step<STEP_RK4>(y0, A.h);
+                        } else {
+                            Acc32<KIND_GRAPH, false> accw{Bs, wm, 0.f, 0.f, nullptr, nullptr};
+                            step_rk4<float>(accw, h0 + l0, y0, A.h, dx, dv);
+                        }
                         n_rec++;
                         two_sum_add(h0.x, l0.x, dx.x);
                         two_sum_add(h0.y, l0.y, dx.y);
@@ -384,7 +399,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
                 }
                 if (j % CULL == CULL - 1 || ballot(j == len - 1)) wm = cull_mask(Bs, nb, px, has, margin);
                 if (has) {
-                    (void)rk4_vjp<true>(Bs, wm, px, vy, A.h, xb, yb, T);
+                    if (wm == 0) free_vjp(A.h, xb, yb);
+                    else (void)rk4_vjp<true>(Bs, wm, px, vy, A.h, xb, yb, T);
                     n_rev++;
                 }
             }
