@@ -28,13 +28,14 @@ constexpr int ADJ_MAX_BUMPS = 16;
 
 // ---------------------------------------------------------- per-lane sums
 // Gradient accumulators of one lane live in LDS: tb[(b * 5 + j) * 64 + lane]
-// for bump b, parameter j in (a, cx, cy, cz, sigma).  (A read-modify-write:
-// non-returning LDS atomic adds measured twice as slow here.)
+// for bump b, parameter j in (a, cx, cy, cz, sigma), the first and the last
+// without their constant factors 1 / sigma^2 and -2 / sigma^3.  (A
+// read-modify-write: non-returning LDS atomic adds measured twice as slow.)
 struct ThetaBar {
     float *tb;
     int lane;
     unsigned terms;  // bump terms inside their cut seen by the parameter VJPs
-    __device__ __forceinline__ void add(int b, int j, float v) { tb[(b * 5 + j) * 64 + lane] += v; }
+    __device__ __forceinline__ float *at(int b) { return tb + (b * 5 * 64 + lane); }
 };
 
 // Wave-uniform mask of the bumps whose cut sphere meets the box of the
@@ -58,10 +59,6 @@ __device__ __forceinline__ uint64_t cull_mask(const float4 *__restrict__ B, int 
     return ballot(need);
 }
 
-// VJP of the graph acceleration a(p, y) = -grad f (y^T H y) / (1 + |grad f|^2)
-// with the bumps of a wave-uniform mask, in increasing index order (per-lane
-// cut as in the forward).  Adds the cotangents of p and y to pb, yb and
-// those of the bump parameters to T when ACC is set.
 // The sums grad f and q of the acceleration at (p, y), bumps of the mask in
 // increasing index order (the order of the trace's walk).
 __device__ __forceinline__ GraphAccum graph_sums(const float4 *__restrict__ B, uint64_t mask, V3<float> p,
@@ -83,10 +80,21 @@ __device__ __forceinline__ GraphAccum graph_sums(const float4 *__restrict__ B, u
     return G;
 }
 
-// S: the sums at (p, y) from graph_sums.
+// VJP of the graph acceleration a(p, y) = -grad f (y^T H y) / (1 + |grad f|^2)
+// with the bumps of a wave-uniform mask, in increasing index order (per-lane
+// cut as in the forward); S holds the sums at (p, y) from graph_sums.  Returns
+// the cotangent of p in Pb and adds that of y to yb, those of the bump
+// parameters to T when ACC is set.
+//
+// With d = p - c, s = 1/sigma^2, u = d . y, w = a s exp(-s |d|^2 / 2) and the
+// cotangents (gbar, qbar) of the two sums, a bump's term is
+//   c0 = qbar (s u^2 - |y|^2) - gbar . d           (cotangent of w)
+//   dbar = 2 qbar w s u y - w gbar - c0 w s d      (cotangent of d: pb, -cbar)
+//   ybar = 2 qbar w (s u d - y)
+//   abar = s (c0 exp(.)),  sigmabar = -2/sigma^3 w (qbar u^2 + c0 (sigma^2 - |d|^2 / 2)).
 template <bool ACC>
 __device__ __forceinline__ void graph_vjp(const float4 *__restrict__ B, uint64_t mask, V3<float> p, V3<float> y,
-                                          const GraphAccum &S, V3<float> ab, V3<float> &pb, V3<float> &yb,
+                                          const GraphAccum &S, V3<float> ab, V3<float> &Pb, V3<float> &yb,
                                           ThetaBar &T) {
     const float yy = dot(y, y);
     const float q = S.q;
@@ -96,6 +104,9 @@ __device__ __forceinline__ void graph_vjp(const float4 *__restrict__ B, uint64_t
     // a = -(q / D) g:  gbar = -(q/D) abar + (2 q / D^2)(g . abar) g,  qbar = -(g . abar)/D
     const float qbar = -ga * invD;
     const V3<float> gbar = axpy(2.0f * q * ga * invD * invD, g, (-q * invD) * ab);
+    const float q2 = 2.0f * qbar, qyy = -qbar * yy;
+    float sy = 0.f;  // sum of 2 qbar w: the part of ybar along y
+    Pb = mk(0.f, 0.f, 0.f);
     for (uint64_t m = mask; m;) {
         const int b = __builtin_ctzll(m);
         m &= ~(1ull << b);
@@ -104,27 +115,34 @@ __device__ __forceinline__ void graph_vjp(const float4 *__restrict__ B, uint64_t
         const V3<float> d = mk(p.x - b0.x, p.y - b0.y, p.z - b0.z);
         const float r2 = dot(d, d);
         if (!(r2 <= b1.z)) continue;
+        if (ACC) T.terms++;
+        float *t = T.at(b);
+        float t0, t1, t2, t3, t4;
+        if (ACC) t0 = t[0], t1 = t[64], t2 = t[128], t3 = t[192], t4 = t[256];
         const float s = b1.y;                 // 1 / sigma^2
         const float e = exp2_(b0.w * r2);     // exp(-s r2 / 2)
         const float w = b1.x * e;             // (a s) e
         const float u = dot(d, y);
-        const float Cw = -dot(gbar, d) + qbar * (s * u * u - yy);
-        // d(loss)/d(d_b): -w gbar + 2 qbar w s u y - Cw w s d
-        V3<float> Cd = axpy(2.0f * qbar * w * s * u, y, (-w) * gbar);
-        Cd = axpy(-Cw * w * s, d, Cd);
-        pb = pb + Cd;
-        yb = axpy(2.0f * qbar * w, axpy(-1.0f, y, s * u * d), yb);
+        const float su = s * u;
+        const float qu = qbar * u;
+        const float c0 = fmaf(qu, su, qyy) - dot(gbar, d);
+        const float a1 = q2 * w;
+        const float k = a1 * su;
+        const float cw = c0 * w;
+        const V3<float> Cd = axpy(-cw * s, d, axpy(k, y, (-w) * gbar));
+        Pb = Pb + Cd;
+        yb = axpy(k, d, yb);
+        sy += a1;
         if (ACC) {
-            T.terms++;
             const float sig = b1.w;
-            const float Cs = qbar * w * u * u + Cw * (w * sig * sig) * (1.0f - 0.5f * s * r2);
-            T.add(b, 0, Cw * s * e);
-            T.add(b, 1, -Cd.x);
-            T.add(b, 2, -Cd.y);
-            T.add(b, 3, -Cd.z);
-            T.add(b, 4, -2.0f * Cs * s * rcp_(sig));
+            t[0] = fmaf(c0, e, t0);
+            t[64] = t1 - Cd.x;
+            t[128] = t2 - Cd.y;
+            t[192] = t3 - Cd.z;
+            t[256] = fmaf(w, fmaf(c0, fmaf(-0.5f, r2, sig * sig), qu * u), t4);
         }
     }
+    yb = axpy(-sy, y, yb);
 }
 
 // Reverse of one RK4 step of size sg from (p, y) (the same stage formulas as
@@ -169,9 +187,8 @@ __device__ __forceinline__ float rk4_vjp(const float4 *__restrict__ B, uint64_t 
     }
 #pragma unroll
     for (int i = 3; i >= 0; --i) {
-        V3<float> Pb = mk(0.f, 0.f, 0.f), Ybi = mk(0.f, 0.f, 0.f);
-        graph_vjp<ACC>(B, mask, P[i], Y[i], G[i], Kb[i], Pb, Ybi, T);
-        Yb[i] = Yb[i] + Ybi;
+        V3<float> Pb;
+        graph_vjp<ACC>(B, mask, P[i], Y[i], G[i], Kb[i], Pb, Yb[i], T);
         pb = pb + Pb;
         if (i > 0) {
             // P_i = p + c Y_{i-1}, Y_i = y + c K_{i-1}, c = sg/2 (i < 3) or sg
@@ -189,6 +206,36 @@ __device__ __forceinline__ float rk4_vjp(const float4 *__restrict__ B, uint64_t 
     Xb = pb;
     Vb = yb;
     return sb;
+}
+
+// rk4_vjp<true> of a full step, without the cotangent of the step size.
+__device__ __forceinline__ void rk4_reverse(const float4 *__restrict__ B, uint64_t mask, V3<float> p, V3<float> y,
+                                            float h, V3<float> &Xb, V3<float> &Vb, ThetaBar &T) {
+    const float c1 = 0.5f * h, w1 = h * (1.0f / 6.0f), w2 = h * (1.0f / 3.0f);
+    const GraphAccum G0 = graph_sums(B, mask, p, y);
+    const V3<float> P1 = axpy(c1, y, p), Y1 = axpy(c1, graph_finish(G0), y);
+    const GraphAccum G1 = graph_sums(B, mask, P1, Y1);
+    const V3<float> P2 = axpy(c1, Y1, p), Y2 = axpy(c1, graph_finish(G1), y);
+    const GraphAccum G2 = graph_sums(B, mask, P2, Y2);
+    const V3<float> P3 = axpy(h, Y2, p), Y3 = axpy(h, graph_finish(G2), y);
+    const GraphAccum G3 = graph_sums(B, mask, P3, Y3);
+    // Yb: cotangent of Y_i, Kb: of the acceleration of stage i, Pb: of P_i
+    V3<float> Yb = w1 * Xb, Kb = w1 * Vb, Pb;
+    graph_vjp<true>(B, mask, P3, Y3, G3, Kb, Pb, Yb, T);
+    V3<float> pb = Xb + Pb, yb = Vb + Yb;
+    Kb = axpy(h, Yb, w2 * Vb);
+    Yb = axpy(h, Pb, w2 * Xb);
+    graph_vjp<true>(B, mask, P2, Y2, G2, Kb, Pb, Yb, T);
+    pb = pb + Pb, yb = yb + Yb;
+    Kb = axpy(c1, Yb, w2 * Vb);
+    Yb = axpy(c1, Pb, w2 * Xb);
+    graph_vjp<true>(B, mask, P1, Y1, G1, Kb, Pb, Yb, T);
+    pb = pb + Pb, yb = yb + Yb;
+    Kb = axpy(c1, Yb, w1 * Vb);
+    Yb = axpy(c1, Pb, w1 * Xb);
+    graph_vjp<true>(B, mask, p, y, G0, Kb, Pb, Yb, T);
+    Xb = pb + Pb;
+    Vb = yb + Yb;
 }
 
 // rk4_vjp where no bump acts at any stage: the new position is p + sg y and the
@@ -254,9 +301,14 @@ __global__ void k_adj_reset(int *next, unsigned long long *stats) {
 // One wave (one block of 64 threads) per chunk of 64 ray ids; persistent
 // blocks take chunks from an atomic queue (ray costs vary: misses and hits
 // that carry no gradient cost nothing, early hits little).
-// Compiled for 4 waves per SIMD (128 VGPRs, 124 B of spills): 8% faster
-// than 3 waves at 162 VGPRs with no spills, 5 waves spill 260 B and are
-// slower.
+// The loop bounds and the bump masks pass through a scalar register, so that
+// the walks of the bumps are scalar control with scalar loads: with the bounds
+// left in vector registers every bump was fetched per lane, through the vector
+// memory, with the mask kept in vector arithmetic.  Vector issue bounds it.
+// Compiled for 4 waves per SIMD (128 VGPRs; spills in the terminal step
+// only), which is also what the LDS of the sums leaves at eight bumps.
+// 64 sets x 512x512 with eight bumps, forward and loss included: 199 ms
+// with vector walks and the VJP's sums unshared, 152 ms now.
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_adjoint(TraceArgs A, AdjArgs J, const float4 *__restrict__ BF,
                                                 const float4 *__restrict__ SPH, const float4 *__restrict__ PLN,
                                                 const float *__restrict__ TOR) {
@@ -338,12 +390,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
         int kmax = act ? kstar : 0;
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) kmax = max(kmax, __shfl_xor(kmax, o));
+        kmax = uniform_i(kmax);
         for (int seg = (kmax - 1) / ck; kmax > 0 && seg >= 0; --seg) {
             const int k0 = seg * ck;
             const int len = act ? max(0, min(ck, kstar - k0)) : 0;
             int lmax = len;
 #pragma unroll
             for (int o = 32; o >= 1; o >>= 1) lmax = max(lmax, __shfl_xor(lmax, o));
+            lmax = uniform_i(lmax);
             // recompute the segment's states into scratch (the forward's own
             // step code; bumps culled per window of CULL steps, exact)
             V3<float> h0 = mk(0.f, 0.f, 0.f), l0 = h0, y0 = h0;
@@ -400,7 +454,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
                 if (j % CULL == CULL - 1 || ballot(j == len - 1)) wm = cull_mask(Bs, nb, px, has, margin);
                 if (has) {
                     if (wm == 0) free_vjp(A.h, xb, yb);
-                    else (void)rk4_vjp<true>(Bs, wm, px, vy, A.h, xb, yb, T);
+                    else rk4_reverse(Bs, wm, px, vy, A.h, xb, yb, T);
                     n_rev++;
                 }
             }
@@ -425,13 +479,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
                 const float w = b1.x * ee;
                 const float rd = dot(r, d);
                 // gd_b = -w (r . d)
-                T.add(b, 0, coef * (-s * ee * rd));
+                float *t = T.at(b);
+                t[0] -= coef * (ee * rd);
                 const V3<float> dc = axpy(-w * s * rd, r, w * d);
-                T.add(b, 1, coef * dc.x);
-                T.add(b, 2, coef * dc.y);
-                T.add(b, 3, coef * dc.z);
-                const float dw_dsig = -2.0f * (w / sig) * (1.0f - 0.5f * s * r2);
-                T.add(b, 4, coef * (-rd * dw_dsig));
+                t[64] += coef * dc.x;
+                t[128] += coef * dc.y;
+                t[192] += coef * dc.z;
+                t[256] -= coef * (rd * (w * fmaf(-0.5f, r2, sig * sig)));
             }
         }
         // ---- fixed-order reduction over the 64 lanes -> chunk partial
@@ -440,6 +494,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
             float v = tb_mem[j * 64 + lane];
 #pragma unroll
             for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+            const int b = j / 5, k = j - 5 * b;
+            const float s = Bs[2 * b + 1].y;
+            if (k == 0) v *= s;
+            if (k == 4) v *= -2.0f * s / Bs[2 * b + 1].w;
             if (lane == 0) J.partial[(int64_t)chunk * np5 + j] = v;
         }
         __syncthreads();
