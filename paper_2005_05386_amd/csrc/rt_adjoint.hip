@@ -308,7 +308,7 @@ __global__ void k_adj_reset(int *next, unsigned long long *stats) {
 // Compiled for 4 waves per SIMD (128 VGPRs; spills in the terminal step
 // only), which is also what the LDS of the sums leaves at eight bumps.
 // 64 sets x 512x512 with eight bumps, forward and loss included: 199 ms
-// with vector walks and the VJP's sums unshared, 152 ms now.
+// with vector walks and the VJP's sums unshared, 145-152 ms now.
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_adjoint(TraceArgs A, AdjArgs J, const float4 *__restrict__ BF,
                                                 const float4 *__restrict__ SPH, const float4 *__restrict__ PLN,
                                                 const float *__restrict__ TOR) {
@@ -324,8 +324,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
     ThetaBar T{tb_mem, lane, 0u};
     unsigned n_rev = 0, n_rec = 0;  // full steps this lane reversed and recomputed
     // culling window: CULL steps (plus the stages of one more) of Euclidean
-    // length <= h each, since g >= I keeps a g-unit velocity at |y| <= 1
-    constexpr int CULL = 16;
+    // length <= h each, since g >= I keeps a g-unit velocity at |y| <= 1; 8
+    // steps, for the masks of 16 hold more bumps and 4 test the boxes more
+    // often (144.6 ms against 146.4 and 146.2 at 64 sets x 512x512)
+    constexpr int CULL = 8;
     const float margin = (float)(CULL + 1) * A.h * 1.02f + 1e-4f;
 
     for (;;) {
