@@ -1058,7 +1058,8 @@ rt_status rt_illuminate(rt_ctx *c, const rt_camera *cam, const rt_outputs *trace
         c->d_ibuf = nullptr;
         c->ibuf_cap = 0;
         e = hipMalloc(&c->d_ibuf, (size_t)n * 52 +
-                                      (1 + rti::ILLUM_RETRY_ROUNDS + rti::ILLUM_CONT_STAGES) * 130 * sizeof(int) + 256);
+                                      (1 + rti::ILLUM_RETRY_ROUNDS + rti::ILLUM_CONT_STAGES) * rti::illum_ctr_words(64) *
+                                          sizeof(int) + 256);
         if (e != hipSuccess) return hip_fail(c, e, "hipMalloc (illumination workspace)");
         c->ibuf_cap = n;
     }

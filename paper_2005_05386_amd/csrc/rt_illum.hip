@@ -177,6 +177,116 @@ __device__ __forceinline__ bool shoot(IAcc<KIND> &acc, const rti::IllumArgs &A, 
     return ok;
 }
 
+// Isotropic bumps spread over the 16 lanes of a DPP row: lane l holds the
+// bumps l, l + 16, ... of a table of up to 16 NB (the others have weight
+// zero), every lane of the row the same state.  A stage computes the terms of
+// 16 bumps at once, each lane its own, and then every lane adds them up in
+// increasing index order, the terms broadcast along the row: the values of the
+// walk, without its chain of loads and exponentials.  Groups of four bumps
+// that act on no lane of the wave are left out (their terms are zero).  Needs
+// all 64 lanes.
+template <int NB> struct RowBumps {
+    float4 b0[NB], b1[NB];
+    bool &seen;  // some bump acted since cleared
+    // The terms of the bumps of lanes N..N+3 of each row, in this order: one
+    // move and four multiply-adds per bump, their first factor read along the
+    // row (from the compiler, a move for each of the five).
+    template <int N>
+    static __device__ __forceinline__ void add4(GraphAccum &A, float w, V3<float> d, float t) {
+        float w0, w1;
+#define RT_ROW_TERM(W, L) \
+    "v_mov_b32_dpp " W ", %6 row_newbcast:" L " row_mask:0xf bank_mask:0xf\n\t" \
+    "v_fmac_f32_dpp %0, %7, " W " row_newbcast:" L " row_mask:0xf bank_mask:0xf\n\t" \
+    "v_fmac_f32_dpp %1, %8, " W " row_newbcast:" L " row_mask:0xf bank_mask:0xf\n\t" \
+    "v_fmac_f32_dpp %2, %9, " W " row_newbcast:" L " row_mask:0xf bank_mask:0xf\n\t" \
+    "v_fmac_f32_dpp %3, %10, " W " row_newbcast:" L " row_mask:0xf bank_mask:0xf\n\t"
+        __asm__("s_nop 1\n\t" RT_ROW_TERM("%4", "%c11") RT_ROW_TERM("%5", "%c12") RT_ROW_TERM("%4", "%c13")
+                    RT_ROW_TERM("%5", "%c14")
+                : "+v"(A.gx), "+v"(A.gy), "+v"(A.gz), "+v"(A.q), "=&v"(w0), "=&v"(w1)
+                : "v"(w), "v"(d.x), "v"(d.y), "v"(d.z), "v"(t), "n"(N), "n"(N + 1), "n"(N + 2), "n"(N + 3));
+#undef RT_ROW_TERM
+    }
+    __device__ __forceinline__ bool operator()(V3<float> p, V3<float> y, V3<float> &a) const {
+        GraphAccum A{0.f, 0.f, 0.f, 0.f};
+        const float yy = dot(y, y);
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const V3<float> d = mk(p.x - b0[k].x, p.y - b0[k].y, p.z - b0[k].z);
+            const float r2 = fmaf(d.z, d.z, fmaf(d.y, d.y, d.x * d.x));
+            const float e = exp2_(b0[k].w * r2);
+            const float w = r2 <= b1[k].z ? -(b1[k].x * e) : 0.0f;  // (both factors of q negated)
+            const float dv = fmaf(d.z, y.z, fmaf(d.y, y.y, d.x * y.x));
+            const float t = -fmaf(b1[k].y, dv * dv, -yy);
+            const uint64_t in = ballot(w != 0.0f);
+            const uint32_t m = (uint32_t)in | (uint32_t)(in >> 32);
+            if (m & 0x000F000Fu) add4<0>(A, w, d, t);
+            if (m & 0x00F000F0u) add4<4>(A, w, d, t);
+            if (m & 0x0F000F00u) add4<8>(A, w, d, t);
+            if (m & 0xF000F000u) add4<12>(A, w, d, t);
+            seen |= m != 0;
+        }
+        a = graph_finish(A);
+        return true;
+    }
+};
+
+// shoot of one geodesic per row, T the same in every lane (the whole wave
+// takes the same steps; a row that failed is left to run on).
+template <int NB>
+__device__ __forceinline__ bool shoot_rows(const float4 (&b0)[NB], const float4 (&b1)[NB], const rti::IllumArgs &A,
+                                           V3<float> q, V3<float> v, float T, V3<float> &X, V3<float> &Y) {
+    const float h = A.h;
+    const int n = uniform_i(max(1, (int)ceilf(T / h)));
+    bool ok = n <= A.max_steps, seen = false;
+    V3<float> xh = q, xl = mk(0.f, 0.f, 0.f), y = v;
+    RowBumps<NB> acc{{}, {}, seen};
+    float R[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+        acc.b0[k] = b0[k];
+        acc.b1[k] = b1[k];
+        R[k] = b1[k].z >= 0.f ? sqrt_(b1[k].z) * 1.0001f : -1e6f;
+    }
+    int fly = 0;  // first step to look for free flight again
+    for (int i = 0; i < n && ballot(ok);) {
+        seen = false;
+        const float hs = i == n - 1 ? T - (float)(n - 1) * h : h;
+        V3<float> dx, dv;
+        step_rk4<float>(acc, xh + xl, y, hs, dx, dv);
+        ok = ok && finite6(dx, dv);
+        two_sum_add(xh.x, xl.x, dx.x);
+        two_sum_add(xh.y, xl.y, dx.y);
+        two_sum_add(xh.z, xl.z, dx.z);
+        y = y + dv;
+        ++i;
+        if (!seen && i >= fly) {
+            // steps free of every cut region for every row, as free_steps
+            const V3<float> p = xh + xl;
+            float gap = 1e6f;
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                const V3<float> d = mk(p.x - b0[k].x, p.y - b0[k].y, p.z - b0[k].z);
+                gap = fminf(gap, sqrt_(dot(d, d)) - R[k]);
+            }
+            const float f = (wave_min(ok ? gap : 1e6f) * 0.999f - 2e-4f) * rcp_(1.02f * h);
+            const int m = uniform_i(min((int)fminf(f, 1e6f) - 2, n - 1 - i));
+            fly = i + 4;
+            if (m > 0) {
+                const V3<float> dx1 = free_step<STEP_RK4>(y, h);
+                for (int j = 0; j < m; ++j) {
+                    two_sum_add(xh.x, xl.x, dx1.x);
+                    two_sum_add(xh.y, xl.y, dx1.y);
+                    two_sum_add(xh.z, xl.z, dx1.z);
+                }
+                i += m;
+            }
+        }
+    }
+    X = xh + xl;
+    Y = y;
+    return ok;
+}
+
 // March the same geodesic with the chord of every step tested against the
 // objects of the window; true when nothing is crossed between t = skip and
 // t = T.
@@ -417,6 +527,11 @@ constexpr float ILLUM_EPS = 1e-3f;
 // vector issue, fewer would leave SIMDs without one.
 constexpr int SOLVE_WAVES = 2048;
 
+// Pixels that k_illum_rows takes, one per wave: four waves per SIMD.  1080p with
+// 16 bumps takes 245, 240, 235 and 248 ms at 1024, 2048, 4096 and 8192; frames
+// of 3 to 90 thousand pixels change by 1% to 15% in the same order.
+constexpr int ROWS_MAX = 4096;
+
 // A list is short while 8192 waves (one pass of the GPU) hold it at three
 // lanes per pixel.
 constexpr int SHORT_LIST = 8192 * PAR_PIX;
@@ -424,6 +539,32 @@ constexpr int SHORT_LIST = 8192 * PAR_PIX;
 // SOLVE_WAVES waves.
 inline int solve_blocks(int64_t n) {
     return (int)std::max<int64_t>(SOLVE_WAVES / 4, (std::min<int64_t>(n, SHORT_LIST) + 4 * PAR_PIX - 1) / (4 * PAR_PIX));
+}
+
+// What the shots of iteration it of a pixel lead to: the iterations done if it
+// goes on (-1: none, at the next target of the continuation), else 0.
+template <int KIND>
+__device__ __forceinline__ int advance(const rti::IllumArgs &A, const Pixel<KIND> &P, V3<float> L, int it, bool okab,
+                                       V3<float> X, V3<float> Y, V3<float> Xa, V3<float> Xb, float &al, float &be,
+                                       float &T, float &last, float &cont, int &code, int *status) {
+    const V3<float> Lp = target(cont, P, L);
+    const V3<float> F = X - Lp;
+    const int j = judge(A, it, F, last);
+    if (j == J_STEP) {
+        if (okab && newton<KIND>(A, P, Lp, ILLUM_EPS, al, be, T, F, X, Y, Xa, Xb) && it + 1 < A.max_iters) return it + 1;
+    } else if (j == J_CONV && code == ST_CONT) {
+        // the next stage of the continuation starts from here
+        const int st = (int)(cont * rti::ILLUM_CONT_STAGES + 0.5f);
+        const float lam0 = (float)st / rti::ILLUM_CONT_STAGES, lam1 = (float)(st + 1) / rti::ILLUM_CONT_STAGES;
+        T *= lam1 / lam0;
+        last = __builtin_huge_valf();
+        cont = lam1;
+        code = st + 1 < rti::ILLUM_CONT_STAGES ? ST_CONT : ST_CONV;
+        return -1;
+    } else if (j == J_CONV) {
+        *status = code;
+    }
+    return 0;
 }
 
 // A short list[it & 1]: the pixels' remaining iterations, each pixel on its
@@ -435,11 +576,15 @@ inline int solve_blocks(int64_t n) {
 // steps, so a launch per iteration lasted as long as its longest shot, and the
 // sum of those maxima was most of the time; here a pixel's time is the sum of
 // its own shots.  Same values as the launches one by one.
+// rows: k_illum_rows follows; lists of up to ROWS_MAX pixels are left to it
+// whole, and of a longer list the last ROWS_MAX pixels to be solved (their
+// state in w_X and the arrays of the state).
 template <int KIND, bool ONE>
-__global__ __launch_bounds__(256) void k_illum_solve(rti::IllumArgs A, const float4 *__restrict__ BF, int it) {
+__global__ __launch_bounds__(256) void k_illum_solve(rti::IllumArgs A, const float4 *__restrict__ BF, int it, bool rows) {
     const int *in = A.list[it & 1];
     const int n_in = A.ctr[it];
-    if (n_in > SHORT_LIST) return;
+    if (n_in > SHORT_LIST || (rows && n_in <= ROWS_MAX)) return;
+    int *done = A.ctr + 2 * (A.max_iters + 1) + it, *handed = A.ctr + 3 * (A.max_iters + 1) + it;
     const uint64_t all = all_bumps(A.n_bumps);
     const V3<float> L = mk(A.light[0], A.light[1], A.light[2]);
     const float eps = ILLUM_EPS;
@@ -476,24 +621,7 @@ __global__ __launch_bounds__(256) void k_illum_solve(rti::IllumArgs A, const flo
         const int oka = __shfl((int)ok, s1), okb = __shfl((int)ok, s2);
         int next = 0;  // iterations done if the pixel goes on, else 0
         if (live && role == 0 && ok) {
-            const V3<float> Lp = target(cont, P, L);
-            const V3<float> F = X - Lp;
-            const int j = judge(A, it, F, last);
-            if (j == J_STEP) {
-                if (oka && okb && newton<KIND>(A, P, Lp, eps, al, be, T, F, X, Y, Xa, Xb) && it + 1 < A.max_iters)
-                    next = it + 1;
-            } else if (j == J_CONV && code == ST_CONT) {
-                // the next stage of the continuation starts from here
-                const int st = (int)(cont * rti::ILLUM_CONT_STAGES + 0.5f);
-                const float lam0 = (float)st / rti::ILLUM_CONT_STAGES, lam1 = (float)(st + 1) / rti::ILLUM_CONT_STAGES;
-                T *= lam1 / lam0;
-                last = __builtin_huge_valf();
-                cont = lam1;
-                code = st + 1 < rti::ILLUM_CONT_STAGES ? ST_CONT : ST_CONV;
-                next = -1;
-            } else if (j == J_CONV) {
-                A.status[pix] = code;
-            }
+            next = advance<KIND>(A, P, L, it, oka && okb, X, Y, Xa, Xb, al, be, T, last, cont, code, A.status + pix);
             if (next == 0) {
                 A.w_al[pix] = al;
                 A.w_be[pix] = be;
@@ -505,8 +633,87 @@ __global__ __launch_bounds__(256) void k_illum_solve(rti::IllumArgs A, const flo
         al = __shfl(al, src);
         be = __shfl(be, src);
         T = __shfl(T, src);
+        const int ended = __popcll(ballot(live && role == 0 && next == 0));
         live = live && next != 0;
         it = max(next, 0);
+        if (rows) {
+            int left = 0;
+            if (lane == 0) {
+                left = ended ? atomicAdd(done, ended) + ended : __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                left = n_in - left;
+            }
+            if (uniform_i(left) <= ROWS_MAX) {
+                if (live && role == 0) {
+                    A.w_al[pix] = al;
+                    A.w_be[pix] = be;
+                    A.w_T[pix] = T;
+                    A.w_F[pix] = last;
+                    A.w_X[3 * pix] = __int_as_float(it);
+                    A.w_X[3 * pix + 1] = cont;
+                    A.w_X[3 * pix + 2] = __int_as_float(code);
+                }
+                append(A.list[2], handed, pix, live && role == 0);
+                return;
+            }
+        }
+    }
+}
+
+// The pixels of a list of up to ROWS_MAX, or those that k_illum_solve handed
+// over, to their end: one wave per pixel, its three shots on three rows of 16
+// lanes (the fourth repeats the base), the bumps spread over the lanes of each
+// row.  What is left there are serial chains of up to 50 shots of hundreds of
+// steps, whose latency is the time: with the walk of the bumps in every lane
+// 2.4 to 5 us a step even on an idle GPU, spread over the lanes about 1 us.
+// 1080p with 16 bumps 270 ms without these launches, 235 with them; 72x48 with
+// 13 bumps 90 and 36.  Same values as the other launches.
+template <int NB, bool ONE>
+__global__ __launch_bounds__(64) void k_illum_rows(rti::IllumArgs A, const float4 *__restrict__ BF, int it) {
+    const int n_in = A.ctr[it];
+    if (n_in > SHORT_LIST) return;
+    const bool whole = n_in <= ROWS_MAX;
+    const int n = whole ? n_in : min(A.ctr[3 * (A.max_iters + 1) + it], ROWS_MAX);
+    const int k = blockIdx.x;
+    if (k >= n) return;
+    const int lane = lane_id(), role = lane >> 4;
+    const V3<float> L = mk(A.light[0], A.light[1], A.light[2]);
+    const int pix = uniform_i(whole ? A.list[it & 1][k] : A.list[2][k]);
+    const Pixel<KIND_GRAPH> P = pixel<KIND_GRAPH, ONE>(A, BF, pix);
+    float4 b0[NB], b1[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+        const int b = (lane & 15) + 16 * j;
+        b0[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+        b1[j] = make_float4(0.f, 0.f, -1.f, 1.f);
+        if (b < A.n_bumps) b0[j] = P.Bs[2 * b], b1[j] = P.Bs[2 * b + 1];
+    }
+    float al = A.w_al[pix], be = A.w_be[pix], T = A.w_T[pix], last = A.w_F[pix], cont = A.cont;
+    int code = A.conv_code;
+    if (!whole) {
+        it = __float_as_int(A.w_X[3 * pix]);
+        cont = A.w_X[3 * pix + 1];
+        code = __float_as_int(A.w_X[3 * pix + 2]);
+    }
+    for (;;) {
+        V3<float> X, Y;
+        const V3<float> v = P.dir(A, role == 1 ? al + ILLUM_EPS : al, role == 2 ? be + ILLUM_EPS : be);
+        const uint64_t ok = ballot(shoot_rows<NB>(b0, b1, A, P.q, v, T, X, Y));
+        if (!(ok & 1ull)) break;
+        const V3<float> Xa = mk(__shfl(X.x, 16), __shfl(X.y, 16), __shfl(X.z, 16));
+        const V3<float> Xb = mk(__shfl(X.x, 32), __shfl(X.y, 32), __shfl(X.z, 32));
+        X = mk(__shfl(X.x, 0), __shfl(X.y, 0), __shfl(X.z, 0));
+        Y = mk(__shfl(Y.x, 0), __shfl(Y.y, 0), __shfl(Y.z, 0));
+        const bool okab = ((ok >> 16) & (ok >> 32) & 1ull) != 0;
+        const int next = uniform_i(
+            advance<KIND_GRAPH>(A, P, L, it, okab, X, Y, Xa, Xb, al, be, T, last, cont, code, A.status + pix));
+        if (next == 0) break;
+        it = max(next, 0);
+    }
+    if (lane == 0) {
+        A.w_al[pix] = al;
+        A.w_be[pix] = be;
+        A.w_T[pix] = T;
+        A.w_F[pix] = last;
     }
 }
 
@@ -761,9 +968,17 @@ __global__ __launch_bounds__(256) void k_illum_cont(rti::IllumArgs A, const floa
 template <int KIND, bool ONE>
 void illum_rounds(const rti::IllumArgs &a, const rti::DeviceData &d, int grid, hipStream_t s) {
     const int sgrid = solve_blocks((int64_t)a.n_sets * a.width * a.height);
+    const int rgrid = (int)std::min<int64_t>((int64_t)a.n_sets * a.width * a.height, ROWS_MAX);
+    const bool rows = KIND == KIND_GRAPH && a.n_bumps > 0 && a.n_bumps <= 32;
     // one iteration's launches; solve: the pixels of a short list go to their end
     auto iteration = [&](const rti::IllumArgs &q, int it, bool solve) {
-        if (solve) hipLaunchKernelGGL((k_illum_solve<KIND, ONE>), dim3(sgrid), dim3(256), 0, s, q, d.bump_f, it);
+        if (solve) hipLaunchKernelGGL((k_illum_solve<KIND, ONE>), dim3(sgrid), dim3(256), 0, s, q, d.bump_f, it, rows);
+        if constexpr (KIND == KIND_GRAPH) {
+            if (solve && rows && a.n_bumps <= 16)
+                hipLaunchKernelGGL((k_illum_rows<1, ONE>), dim3(rgrid), dim3(64), 0, s, q, d.bump_f, it);
+            else if (solve && rows)
+                hipLaunchKernelGGL((k_illum_rows<2, ONE>), dim3(rgrid), dim3(64), 0, s, q, d.bump_f, it);
+        }
         hipLaunchKernelGGL((k_illum_iter<KIND, ONE>), dim3(grid), dim3(256), 0, s, q, d.bump_f, it, solve);
         hipLaunchKernelGGL((k_illum_step<KIND, ONE>), dim3(grid), dim3(256), 0, s, q, d.bump_f, it);
     };
@@ -775,7 +990,7 @@ void illum_rounds(const rti::IllumArgs &a, const rti::DeviceData &d, int grid, h
     rti::IllumArgs r = a;
     r.max_iters = std::max(a.max_iters / 4, 1);
     for (int round = 1; round <= rti::ILLUM_RETRY_ROUNDS; ++round) {
-        r.ctr = a.ctr + round * 2 * (a.max_iters + 1);
+        r.ctr = a.ctr + round * rti::illum_ctr_words(a.max_iters);
         hipLaunchKernelGGL((k_illum_seed<KIND, ONE>), dim3(grid), dim3(256), 0, s, r, d.bump_f, r.ctr);
         for (int it = 0; it < r.max_iters; ++it) iteration(r, it, it == 0);
     }
@@ -784,7 +999,7 @@ void illum_rounds(const rti::IllumArgs &a, const rti::DeviceData &d, int grid, h
     r.max_iters = std::max(a.max_iters / 2, 1);
     for (int st = 0; st < rti::ILLUM_CONT_STAGES; ++st) {
         const float lam0 = (float)st / rti::ILLUM_CONT_STAGES, lam1 = (float)(st + 1) / rti::ILLUM_CONT_STAGES;
-        r.ctr = a.ctr + (1 + rti::ILLUM_RETRY_ROUNDS + st) * 2 * (a.max_iters + 1);
+        r.ctr = a.ctr + (1 + rti::ILLUM_RETRY_ROUNDS + st) * rti::illum_ctr_words(a.max_iters);
         r.cont = lam1;
         r.conv_code = st + 1 < rti::ILLUM_CONT_STAGES ? ST_CONT : ST_CONV;
         hipLaunchKernelGGL((k_illum_cont<KIND, ONE>), dim3(grid), dim3(256), 0, s, r, d.bump_f, r.ctr, lam0, lam1);
@@ -797,7 +1012,7 @@ void illum_rounds(const rti::IllumArgs &a, const rti::DeviceData &d, int grid, h
 template <int KIND>
 hipError_t illum_kind(const rti::IllumArgs &a, const rti::DeviceData &d, int grid, hipStream_t s) {
     hipLaunchKernelGGL(k_illum_zero, dim3(1), dim3(256), 0, s, a.ctr,
-                       (1 + rti::ILLUM_RETRY_ROUNDS + rti::ILLUM_CONT_STAGES) * 2 * (a.max_iters + 1));
+                       (1 + rti::ILLUM_RETRY_ROUNDS + rti::ILLUM_CONT_STAGES) * rti::illum_ctr_words(a.max_iters));
     hipLaunchKernelGGL((k_illum_init<KIND>), dim3(grid), dim3(256), 0, s, a, d.bump_f);
     if (a.n_sets == 1)
         illum_rounds<KIND, true>(a, d, grid, s);

@@ -197,7 +197,8 @@ struct IllumArgs {
     float *w_al, *w_be, *w_T, *w_F;  // angles, length, last residual
     float *w_X, *w_Y;                // base shot's end point and velocity [3 per pixel]
     int *list[3];
-    int *ctr;  // 2 (max_iters + 1) words for each shooting attempt: list sizes, then step-list sizes
+    int *ctr;  // illum_ctr_words for each shooting attempt, by iteration: list sizes, step-list sizes, pixels ended
+               // in the solve launch, pixels it handed over
     // continuation rounds: the shots aim at q + cont (L - q) instead of L,
     // and a pixel that converges there is marked conv_code
     float cont;
@@ -211,6 +212,7 @@ constexpr int ILLUM_RETRY_ROUNDS = 3;
 // position: targets q + lambda (L - q) for the ILLUM_CONT_STAGES values
 // lambda = 1/S, 2/S, ..., 1, each stage started from the previous solution.
 constexpr int ILLUM_CONT_STAGES = 8;
+constexpr int illum_ctr_words(int max_iters) { return 4 * (max_iters + 1); }
 hipError_t launch_illum(const IllumArgs &a, const DeviceData &d, int grid, hipStream_t s);
 // ------------------------------------------------------------- MLP (BF16)
 // Per-network parameter layout (floats / bf16 values).

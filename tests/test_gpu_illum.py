@@ -219,3 +219,26 @@ def test_edge_cases(rt):
         d = L - q
         v = d / np.sqrt(d @ orc.metric_tensor(q) @ d)
         assert np.abs(sh["dir"][p] / np.linalg.norm(sh["dir"][p]) - v / np.linalg.norm(v)).max() < 1e-5, p
+
+
+@pytest.mark.parametrize("w,h", [(24, 16), (160, 104)])
+@pytest.mark.parametrize("n", [1, 16, 17, 32])
+def test_spread_bumps_equal_the_walk(rt, n, w, h):
+    """Isotropic tables of up to 32 bumps end their Newton iterations with the
+    bumps spread over the lanes of a wave (a table of up to 16, and of up to
+    32; lists that start short and ones handed over); a longer table walks
+    them.  Bumps of amplitude zero make the table long and add nothing, so the
+    outputs are equal bit for bit."""
+    say("illumination", w, h, "bumps", n, "against the same padded to 33")
+    wl = W.with_size(W.get("bumps16_1080p"), w, h)
+    rng = np.random.default_rng(n)
+    b = np.concatenate([rng.uniform(0.1, 0.5, (n, 1)), rng.uniform(-2, 2, (n, 3)), rng.uniform(0.15, 0.4, (n, 1))], 1)
+    pad = np.tile(np.array([[0.0, 3.0, 3.0, 3.0, 0.3]]), (33 - n, 1))
+    res = []
+    for bumps in (b, np.concatenate([b, pad])):
+        metric = dict(wl["metric"], bumps=bumps[None].astype(np.float32))
+        res.append(_run(rt, dict(wl, metric=metric)))
+    (ta, sa), (tb, sb) = res
+    assert np.array_equal(ta["hit"], tb["hit"]) and (ta["id"] >= 0).any()
+    for k in sa:
+        assert np.array_equal(sa[k], sb[k], equal_nan=True), k
