@@ -19,7 +19,7 @@
 // tiles with the row running fastest, h1, h2, dz2, dz3 (bf16), which is
 // the order in which a lane of the weight-gradient product takes them.
 // 64 networks x 1024 rows, per training step without the data generator:
-// 680 us with one launch per layer and reduction, @STEP@ us with these.
+// 680 us with one launch per layer and reduction, 365 us with these.
 //
 // Lane l of a 16x16x32 MFMA supplies A[l%16][8(l/16) .. 8(l/16)+7] and
 // B[8(l/16) .. +7][l%16] and receives D[4(l/16) + j][l%16], j = 0..3.
@@ -141,9 +141,11 @@ struct KeepTile {
 // products; the tile's activations sit in LDS as the two bf16 parts, the
 // weights' two parts (Wg) stream through L2 as whole fragments, the next slice
 // of 32 k on its way while the current one is multiplied.  Bound by the matrix
-// cores' 3 x 16.8 MFLOP per tile next to the vector work of the SiLUs; 68 KB of LDS and at most 128 registers keep two workgroups,
-// four waves per SIMD, on a CU, so one's vector work runs under the other's
-// products (four waves of 64 columns, two per SIMD, took @4W@).
+// cores' 3 x 16.8 MFLOP per tile next to the vector work of the SiLUs; 68 KB
+// of LDS and at most 128 registers keep two workgroups, four waves per SIMD, on
+// a CU, so one's vector work runs under the other's products (64 networks x
+// 1024 rows: 105 us; with four waves of 64 columns, two per SIMD, 125 against
+// 112 with these before the weights were split once).
 template <bool KEEP>
 __device__ __forceinline__ void forward_tile(char *smem, float (*Xs)[6], const float *__restrict__ Pg,
                                              const __bf16 *__restrict__ Wg, const float *__restrict__ X, float *__restrict__ Y, int M,

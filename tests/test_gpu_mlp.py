@@ -127,3 +127,53 @@ def test_training_reduces_loss(env):
         tr.adamw(pt, pb, m, v, g, 2e-3, step)
     say("loss", losses[0], "->", losses[-1])
     assert losses[-1] < 0.05 * losses[0]
+
+
+@pytest.mark.parametrize("n,batch", [(2, 63), (2, 64), (2, 65), (1, 127), (1, 128), (1, 129), (5, 1000)])
+def test_mlp_tile_edges(env, n, batch):
+    """Batches about the 64-row tiles: forward and backward against the oracle
+    within the bounds of test_mlp_forward_backward_match_oracle, and the work
+    buffer of one batch used again with other rows (the padding rows of the
+    last tile add nothing)."""
+    rt, torch, tr = env
+    say("mlp tile edges n_nets=%d batch=%d" % (n, batch))
+    p, pt, pb = _params(torch, n)
+    p32 = p.astype(np.float32).astype(np.float64)
+    rng = np.random.default_rng(batch)
+    work = tr.mlp_work(n, batch)
+    for scale in (3.0, 1.0):
+        x = (scale * rng.normal(size=(n, batch, 6))).astype(np.float32)
+        dy = rng.normal(size=(n, batch, 6)).astype(np.float32)
+        y = tr.mlp_fwd(pb, pt, torch.tensor(x, device="cuda"), work).cpu().numpy()
+        g = tr.mlp_bwd(pb, pt, torch.tensor(dy, device="cuda"), work).cpu().numpy()
+    for i in range(n):
+        yr, _ = mlp.forward(p32[i], x[i].astype(np.float64), bf16=True)
+        assert np.abs(y[i] - yr).max() <= 2e-5 * max(1.0, np.abs(yr).max()), i
+        gr = mlp.backward(p32[i], x[i].astype(np.float64), dy[i].astype(np.float64), bf16=True)
+        for blk, (a, b) in enumerate(zip(mlp.split(g[i].astype(np.float64)), mlp.split(gr))):
+            assert np.abs(a - b).max() <= 3e-3 * max(1e-3, np.abs(b).max()), (i, blk)
+
+
+def test_grouped_forward_on_two_streams(env):
+    """Grouped calls on two streams in turn, the group count growing between
+    them: each result equals the same call made alone."""
+    rt, torch, tr = env
+    say("grouped forward on two streams")
+    rng = np.random.default_rng(8)
+    calls = []
+    for n in (1, 3, 40, 2):
+        _, pt, pb = _params(torch, n)
+        rows = [int(r) for r in rng.integers(0, 150, n)]
+        rows[0] = 65
+        x = torch.tensor(rng.normal(size=(sum(rows), 6)).astype(np.float32), device="cuda")
+        calls.append((pb, pt, x, rows))
+    alone = [tr.mlp_fwd_grouped(*c).clone() for c in calls]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    got = []
+    for k, c in enumerate(calls * 2):
+        with torch.cuda.stream(streams[k % 2]):
+            got.append(tr.mlp_fwd_grouped(*c))
+    torch.cuda.synchronize()
+    for k, y in enumerate(got):
+        assert torch.equal(y, alone[k % len(calls)]), k
