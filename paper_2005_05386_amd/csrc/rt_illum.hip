@@ -485,14 +485,42 @@ template <class P> __device__ __forceinline__ V3<float> target(float cont, const
     return cont < 1.f ? axpy(cont, L - Px.q, Px.q) : L;
 }
 
+// Pixels per wave when the three shots of an iteration run on three lanes.
+constexpr int PAR_PIX = 21;
+// A list is short while 8192 waves (one pass of the GPU) hold it at three
+// lanes per pixel.
+constexpr int SHORT_LIST = 8192 * PAR_PIX;
+
+// Pixel t of the frames, in the order of the lists, and the count of such t.
+// Frames of more than SHORT_LIST pixels go in 8x8 tiles, one per wave (-1
+// beyond the edge): the windows of the full-grid launches then cover a tile
+// instead of a strip of 64 pixels and reach fewer bumps (1080p with 16 bumps
+// 236 ms in strips, 224 in tiles; 818x557 with 4 bumps 18.5 and 18.3).  Smaller
+// frames, whose lists are solved pixel by pixel, keep the strips (127x75 with 3
+// bumps 3.97 ms, in tiles 4.45: the finish reaches more objects at once).
+__device__ __forceinline__ bool in_tiles(const rti::IllumArgs &A) {
+    return (int64_t)A.n_sets * A.width * A.height > SHORT_LIST;
+}
+__device__ __forceinline__ int64_t pixel_count(const rti::IllumArgs &A) {
+    return in_tiles(A) ? (int64_t)A.n_sets * ((A.width + 7) / 8) * ((A.height + 7) / 8) * 64
+                       : (int64_t)A.n_sets * A.width * A.height;
+}
+__device__ __forceinline__ int nth_pixel(const rti::IllumArgs &A, int64_t t) {
+    if (!in_tiles(A)) return t < (int64_t)A.n_sets * A.width * A.height ? (int)t : -1;
+    const int tx = (A.width + 7) / 8, ty = (A.height + 7) / 8;
+    const int w = (int)(t >> 6), set = w / (tx * ty), r = w - set * (tx * ty), j = r / tx, i = r - j * tx;
+    const int x = 8 * i + (int)(t & 7), y = 8 * j + (int)((t >> 3) & 7);
+    return set < A.n_sets && x < A.width && y < A.height ? (set * A.height + y) * A.width + x : -1;
+}
+
 // Initial state: pixels that hit start from the straight segment.
 template <int KIND>
 __global__ __launch_bounds__(256) void k_illum_init(rti::IllumArgs A, const float4 *__restrict__ BF) {
-    const int n = A.n_sets * A.width * A.height;
-    for (int base = blockIdx.x * blockDim.x; base < n; base += gridDim.x * blockDim.x) {
-        const int pix = base + threadIdx.x;
-        const bool hit = pix < n && A.id[pix] >= 0;
-        if (pix < n) {
+    const int64_t n = pixel_count(A);
+    for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < n; base += gridDim.x * blockDim.x) {
+        const int pix = nth_pixel(A, base + threadIdx.x);
+        const bool hit = pix >= 0 && A.id[pix] >= 0;
+        if (pix >= 0) {
             float T = 0.f;
             if (hit) {
                 const Pixel<KIND> P = pixel<KIND>(A, BF, pix);
@@ -551,8 +579,6 @@ __device__ __forceinline__ bool newton(const rti::IllumArgs &A, const Pixel<KIND
     return T <= 4.f * sqrtf(P.gdd(A, L - P.q)) + 1.f;
 }
 
-// Pixels per wave when the three shots of an iteration run on three lanes.
-constexpr int PAR_PIX = 21;
 // Angle displacement of the finite-difference shots.
 constexpr float ILLUM_EPS = 1e-3f;
 
@@ -565,9 +591,6 @@ constexpr int SOLVE_WAVES = 2048;
 // of 3 to 90 thousand pixels change by 1% to 15% in the same order.
 constexpr int ROWS_MAX = 4096;
 
-// A list is short while 8192 waves (one pass of the GPU) hold it at three
-// lanes per pixel.
-constexpr int SHORT_LIST = 8192 * PAR_PIX;
 // Blocks of four waves that hold any short list of a frame of n pixels, and
 // SOLVE_WAVES waves.
 inline int solve_blocks(int64_t n) {
@@ -861,9 +884,11 @@ template <int KIND, bool ONE>
 __global__ __launch_bounds__(256) void k_illum_finish(rti::IllumArgs A, const float4 *__restrict__ BF,
                                                       const float4 *__restrict__ SPH, const float4 *__restrict__ PLN,
                                                       const float *__restrict__ TOR) {
-    const int n = A.n_sets * A.width * A.height;
+    const int64_t n = pixel_count(A);
     const uint64_t all = all_bumps(A.n_bumps);
-    for (int pix = blockIdx.x * blockDim.x + threadIdx.x; pix < n; pix += gridDim.x * blockDim.x) {
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
+        const int pix = nth_pixel(A, t);
+        if (pix < 0) continue;
         int status = A.status[pix];
         if (status == ST_NOHIT) {
             if (A.dir) A.dir[3 * pix] = A.dir[3 * pix + 1] = A.dir[3 * pix + 2] = 0.f;
@@ -925,11 +950,11 @@ __global__ void k_illum_zero(int *ctr, int n) {
 template <int KIND, bool ONE>
 __global__ __launch_bounds__(256) void k_illum_seed(rti::IllumArgs A, const float4 *__restrict__ BF, int *ctr) {
     const int HW = A.width * A.height;
-    const int n = A.n_sets * HW;
-    for (int base = blockIdx.x * blockDim.x; base < n; base += gridDim.x * blockDim.x) {
-        const int pix = base + threadIdx.x;
+    const int64_t n = pixel_count(A);
+    for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < n; base += gridDim.x * blockDim.x) {
+        const int pix = nth_pixel(A, base + threadIdx.x);
         bool take = false;
-        if (pix < n && A.status[pix] == ST_NONE) {
+        if (pix >= 0 && A.status[pix] == ST_NONE) {
             const int set = pix / HW, r = pix - set * HW, j = r / A.width, i = r - j * A.width;
             const V3<float> q = mk(A.hit[3 * pix], A.hit[3 * pix + 1], A.hit[3 * pix + 2]);
             int best = -1;
@@ -972,12 +997,12 @@ __global__ __launch_bounds__(256) void k_illum_seed(rti::IllumArgs A, const floa
 template <int KIND, bool ONE>
 __global__ __launch_bounds__(256) void k_illum_cont(rti::IllumArgs A, const float4 *__restrict__ BF, int *ctr,
                                                     float lam0, float lam1) {
-    const int n = A.n_sets * A.width * A.height;
+    const int64_t n = pixel_count(A);
     const V3<float> L = mk(A.light[0], A.light[1], A.light[2]);
-    for (int base = blockIdx.x * blockDim.x; base < n; base += gridDim.x * blockDim.x) {
-        const int pix = base + threadIdx.x;
+    for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < n; base += gridDim.x * blockDim.x) {
+        const int pix = nth_pixel(A, base + threadIdx.x);
         bool take = false;
-        if (pix < n) {
+        if (pix >= 0) {
             const int st = A.status[pix];
             if (lam0 == 0.f && st == ST_NONE) {
                 const Pixel<KIND> P = pixel<KIND, ONE>(A, BF, pix);
