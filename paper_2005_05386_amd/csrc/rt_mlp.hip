@@ -652,7 +652,9 @@ __global__ __launch_bounds__(1024) void k_mse_grad(const float *__restrict__ y, 
                                                   float *__restrict__ part) {
     __shared__ float sh[1024];
     float acc = 0.f;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    // part[b]: the elements whose index / 256 is b modulo the grid
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    for (int64_t i = blockIdx.x * 256 + (threadIdx.x & 255) + (threadIdx.x >> 8) * stride; i < n; i += 4 * stride) {
         float d = y[i] - t[i];
         dy[i] = 2.f * d * inv_batch;
         acc += d * d;

@@ -177,3 +177,21 @@ def test_grouped_forward_on_two_streams(env):
     torch.cuda.synchronize()
     for k, y in enumerate(got):
         assert torch.equal(y, alone[k % len(calls)]), k
+
+
+@pytest.mark.parametrize("n", [1, 255, 257, 6000, 16385, 65537])
+def test_mse_partials(env, n):
+    """The 64 partial sums of the loss: partial b holds the elements whose
+    index / 256 is b modulo 64; a sum of k FP32 squares in any order is within
+    (k + 2) 2^-24 of the exact one, relative."""
+    rt, torch, tr = env
+    say("mse partials n=%d" % n)
+    rng = np.random.default_rng(n)
+    y, t = (rng.normal(size=n).astype(np.float32) for _ in range(2))
+    dy, part = tr.mse_grad(torch.tensor(y, device="cuda"), torch.tensor(t, device="cuda"), 7)
+    d = (y - t).astype(np.float64)
+    assert np.allclose(dy.cpu().numpy(), 2.0 * d / 7.0, rtol=4e-7, atol=0)
+    b = np.arange(n) // 256 % 64
+    ref = np.bincount(b, d * d, 64)
+    k = np.bincount(b, minlength=64)
+    assert (np.abs(part.cpu().numpy() - ref) <= (k + 2) * 2.0**-24 * ref).all()
