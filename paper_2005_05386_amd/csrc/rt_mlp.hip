@@ -19,7 +19,9 @@
 // tiles with the row running fastest, h1, h2, dz2, dz3 (bf16), which is
 // the order in which a lane of the weight-gradient product takes them.
 // 64 networks x 1024 rows, per training step without the data generator:
-// 680 us with one launch per layer and reduction, 365 us with these.
+// 680 us with one launch per layer and reduction, 375 us with these.
+// The arithmetic is that of the single launches, operation by operation: the
+// correctly rounded quotients of the SiLUs, the order of every sum.
 //
 // Lane l of a 16x16x32 MFMA supplies A[l%16][8(l/16) .. 8(l/16)+7] and
 // B[8(l/16) .. +7][l%16] and receives D[4(l/16) + j][l%16], j = 0..3.
@@ -27,6 +29,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "rt_internal.hpp"
 
@@ -67,19 +70,52 @@ __device__ __forceinline__ bool xcd_tile(int nx, int ny, int nz, int &x, int &y,
 }
 inline unsigned xcd_grid(int nx, int ny, int nz) { return 8u * (unsigned)(((int64_t)nx * ny * nz + 7) / 8); }
 
-// 1 / (1 + exp(-z)): the hardware reciprocal with one Newton step (the tiles
-// are bound by vector issue, and a full division is twice the instructions).
-// The exponent stops at 2^120, where the result is below any float that z
-// could still lift to a normal product.
-__device__ __forceinline__ float sigmoid(float z) {
-    const float d = 1.0f + __builtin_amdgcn_exp2f(fminf(-1.4426950408889634f * z, 120.0f));
-    const float r = __builtin_amdgcn_rcpf(d);
-    return fmaf(r, fmaf(-d, r, 1.0f), r);
+// SiLU of N pre-activations and its parts, the quotients correctly rounded.
+// The tiles are bound by vector issue, so while every |z| of the wave is at
+// most ACT_FAST, where neither a quotient nor a residual can leave the normal
+// range, n / d takes the hardware reciprocal of d (shared by z / d and 1 / d),
+// one Newton step and two residual corrections: the sequence that a division
+// compiles to, without its scaling and fix-up.  Beyond, the division itself.
+// (Rounding to last place matters here: a changed bit of an activation can
+// move its bf16 part by 2^-9, and a training run carries that on.)
+constexpr float ACT_FAST = 80.0f;
+__device__ __forceinline__ float quotient(float n, float d, float r) {
+    float q = n * r;
+    q = fmaf(fmaf(-d, q, n), r, q);
+    return fmaf(fmaf(-d, q, n), r, q);
 }
-__device__ __forceinline__ float silu(float z) { return z * sigmoid(z); }
-__device__ __forceinline__ float dsilu(float z) {
-    const float s = sigmoid(z);
-    return s * (1.0f + z * (1.0f - s));
+struct Act {
+    float d, r;  // 1 + exp(-z); its reciprocal to about a bit of the last place
+    bool fast;
+    __device__ __forceinline__ Act(float z, bool f) : d(1.0f + __expf(-z)), r(0.f), fast(f) {
+        if (!fast) return;
+        r = __builtin_amdgcn_rcpf(d);
+        r = fmaf(fmaf(-d, r, 1.0f), r, r);
+    }
+    __device__ __forceinline__ float over(float n) const { return fast ? quotient(n, d, r) : n / d; }
+};
+__device__ __forceinline__ float dsilu(float z, float s) { return s * (1.0f + z * (1.0f - s)); }
+// f(fast) with fast known at compile time: whether all |z[0..N)| of the wave are
+// at most ACT_FAST (a NaN passes through either way).
+template <int N, class Z, class F> __device__ __forceinline__ void act_range(const Z &z, F f) {
+    float m = 0.f;
+#pragma unroll
+    for (int i = 0; i < N; ++i) m = fmaxf(m, fabsf(z[i]));
+    if (__ballot(m > ACT_FAST) == 0) f(std::true_type{});
+    else f(std::false_type{});
+}
+template <int N, class Z> __device__ __forceinline__ void silu(const Z &z, float (&h)[N]) {
+    act_range<N>(z, [&](auto fast) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) h[i] = Act(z[i], fast).over(z[i]);
+    });
+}
+// a[i] *= silu'(z[i])
+template <int N, class Z> __device__ __forceinline__ void times_dsilu(const Z &z, float (&a)[N]) {
+    act_range<N>(z, [&](auto fast) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) a[i] = a[i] * dsilu(z[i], Act(z[i], fast).over(1.0f));
+    });
 }
 
 // W2 and W3 of the FP32 master as the two bf16 parts, in the order a wave reads
@@ -144,8 +180,8 @@ struct KeepTile {
 // cores' 3 x 16.8 MFLOP per tile next to the vector work of the SiLUs; 68 KB
 // of LDS and at most 128 registers keep two workgroups, four waves per SIMD, on
 // a CU, so one's vector work runs under the other's products (64 networks x
-// 1024 rows: 105 us; with four waves of 64 columns, two per SIMD, 125 against
-// 112 with these before the weights were split once).
+// 1024 rows: 110 us; with four waves of 64 columns, two per SIMD, 125 against
+// 112 with these before the weights were split once and the quotients exact).
 template <bool KEEP>
 __device__ __forceinline__ void forward_tile(char *smem, float (*Xs)[6], const float *__restrict__ Pg,
                                              const __bf16 *__restrict__ Wg, const float *__restrict__ X, float *__restrict__ Y, int M,
@@ -169,21 +205,25 @@ __device__ __forceinline__ void forward_tile(char *smem, float (*Xs)[6], const f
         const int rh = (tid >> 8) * (TM / 2);
 #pragma unroll 1
         for (int r0 = rh; r0 < rh + TM / 2; r0 += 8) {
-            bf16x8 hi;
+            float z[8], h[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int r = r0 + u;
-                float z = b;
-                z = fmaf(w0, Xs[r][0], z);
-                z = fmaf(w1, Xs[r][1], z);
-                z = fmaf(w2, Xs[r][2], z);
-                z = fmaf(w3, Xs[r][3], z);
-                z = fmaf(w4, Xs[r][4], z);
-                z = fmaf(w5, Xs[r][5], z);
-                const float h = silu(z);
-                hi[u] = (__bf16)h;
-                Ah[r][o] = hi[u];
-                Al[r][o] = (__bf16)(h - (float)hi[u]);
+                z[u] = b;
+                z[u] = fmaf(w0, Xs[r][0], z[u]);
+                z[u] = fmaf(w1, Xs[r][1], z[u]);
+                z[u] = fmaf(w2, Xs[r][2], z[u]);
+                z[u] = fmaf(w3, Xs[r][3], z[u]);
+                z[u] = fmaf(w4, Xs[r][4], z[u]);
+                z[u] = fmaf(w5, Xs[r][5], z[u]);
+            }
+            silu(z, h);
+            bf16x8 hi;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                hi[u] = (__bf16)h[u];
+                Ah[r0 + u][o] = hi[u];
+                Al[r0 + u][o] = (__bf16)(h[u] - (float)hi[u]);
             }
             if constexpr (KEEP) *(bf16x8 *)(K.h1t + o * TM + r0) = hi;
         }
@@ -239,22 +279,23 @@ __device__ __forceinline__ void forward_tile(char *smem, float (*Xs)[6], const f
                 f32x4 z;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) z[e] = acc[i][j][e] + bn;
+                float h[4];
+                silu(z, h);
                 if (l == 0) {
                     if constexpr (KEEP) *(f32x4 *)(K.z2 + (((wave * 4 + i) * 2 + j) * 64 + lane) * 4) = z;
                     bf16x4 hi;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const float h = silu(z[e]);
-                        hi[e] = (__bf16)h;
+                        hi[e] = (__bf16)h[e];
                         Ah[r + e][n] = hi[e];
-                        Al[r + e][n] = (__bf16)(h - (float)hi[e]);
+                        Al[r + e][n] = (__bf16)(h[e] - (float)hi[e]);
                     }
                     if constexpr (KEEP) *(bf16x4 *)(K.h2t + n * TM + r) = hi;
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         if constexpr (KEEP) K.z3[(r + e) * H + n] = z[e];
-                        Hf[r + e][n] = silu(z[e]);
+                        Hf[r + e][n] = h[e];
                     }
                 }
             }
@@ -438,25 +479,29 @@ __global__ __launch_bounds__(NT, 4) void k_mlp_bwd(const float *__restrict__ par
 #pragma unroll
             for (int u = 0; u < 8; ++u) z[u] = z3[(r0 + u) * H];
             bf16x8 pk;
+            act_range<8>(z, [&](auto fast) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int m = rh + r0 + u;
-                const float sg = sigmoid(z[u]), h = z[u] * sg;
-                float dh = 0.f;
+                for (int u = 0; u < 8; ++u) {
+                    const int m = rh + r0 + u;
+                    const Act t(z[u], fast);
+                    const float h = t.over(z[u]);
+                    float dh = 0.f;
 #pragma unroll
-                for (int o = 0; o < 6; ++o) {
-                    const float d = Ds[m][o];
-                    dh = fmaf(d, w4[o], dh);
-                    a[o] = fmaf(d, h, a[o]);
+                    for (int o = 0; o < 6; ++o) {
+                        const float d = Ds[m][o];
+                        dh = fmaf(d, w4[o], dh);
+                        a[o] = fmaf(d, h, a[o]);
+                    }
+                    const float dz = dh * dsilu(z[u], t.over(1.0f));
+                    s += dz;
+                    pk[u] = (__bf16)dz;
+                    A[m][c] = pk[u];
                 }
-                if (c < 6) a[6] += Ds[m][c];
-                const float dz = dh * (sg * (1.0f + z[u] * (1.0f - sg)));
-                s += dz;
-                pk[u] = (__bf16)dz;
-                A[m][c] = pk[u];
-            }
+            });
             *(bf16x8 *)(dzt + r0) = pk;
         }
+        if (c < 6)
+            for (int u = 0; u < GRAD_ROWS; ++u) a[6] += Ds[rh + u][c];
         write_part(w.part4, a);
         column_sum(s, w.cs3);
     }
@@ -469,8 +514,10 @@ __global__ __launch_bounds__(NT, 4) void k_mlp_bwd(const float *__restrict__ par
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const f32x4 z = *(const f32x4 *)(w.z2 + T * TM * H + (((wave * 4 + i) * 2 + j) * 64 + lane) * 4);
+            float d[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+            times_dsilu(z, d);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) F[16 * i + 4 * grp + e][wave * 32 + 16 * j + col] = acc[i][j][e] * dsilu(z[e]);
+            for (int e = 0; e < 4; ++e) F[16 * i + 4 * grp + e][wave * 32 + 16 * j + col] = d[e];
             __builtin_amdgcn_sched_barrier(0);  // (keeps the unrolled tiles from holding all of z at once)
         }
     __syncthreads();
@@ -506,16 +553,21 @@ __global__ __launch_bounds__(NT, 4) void k_mlp_bwd(const float *__restrict__ par
         for (int q = 0; q < 6; ++q) w1[q] = Pg[rti::OFF_W1 + n1 * 6 + q];
         const float b1 = Pg[rti::OFF_B1 + n1];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4; ++i) {
+            const int r = 16 * i + 4 * grp;
+            float z[4], d[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int r = 16 * i + 4 * grp + e;
-                float z = b1;
+                z[e] = b1;
 #pragma unroll
-                for (int q = 0; q < 6; ++q) z = fmaf(w1[q], Xs[r][q], z);
-                F[r][n1] = acc[i][j][e] * dsilu(z);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int q = 0; q < 6; ++q) z[e] = fmaf(w1[q], Xs[r + e][q], z[e]);
+                d[e] = acc[i][j][e];
             }
+            times_dsilu(z, d);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) F[r + e][n1] = d[e];
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
     __syncthreads();
     {   // first layer

@@ -195,3 +195,47 @@ def test_mse_partials(env, n):
     ref = np.bincount(b, d * d, 64)
     k = np.bincount(b, minlength=64)
     assert (np.abs(part.cpu().numpy() - ref) <= (k + 2) * 2.0**-24 * ref).all()
+
+
+def _plain_net(torch, **parts):
+    """One network of zeros with the named parts (W1, b1, ..., b4) set."""
+    p = np.zeros(mlp.N_PARAMS)
+    names = ["%s%d" % (a, i) for i in (1, 2, 3, 4) for a in "Wb"]
+    for k, v in parts.items():
+        mlp.split(p)[names.index(k)][:] = v
+    pt = torch.tensor(p[None], dtype=torch.float32, device="cuda")
+    return pt, pt.to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("lo,hi", [(-80.0, 80.0), (-1e3, 1e3), (-1e37, -90.0)])
+def test_activation_values(env, lo, hi):
+    """SiLU and its derivative by themselves, on both sides of the range where
+    the quotients are formed without a division: with W2 = W3 = 0 the last
+    pre-activations are b3, and with one row and dy = e_0 the gradient of W4's
+    first row is silu(b3), that of b3 is W4 silu'(b3).  The exponential's
+    argument z log2(e) is rounded to FP32 and the hardware exponential adds an
+    ulp: a relative error of at most (|z| + 2) 2^-23 in exp(-z), and a few
+    ulp after that.  From -89 on exp(-z) overflows, and both are zero."""
+    rt, torch, tr = env
+    say("activations %g .. %g" % (lo, hi))
+    z = np.linspace(lo, hi, 256).astype(np.float32)
+    pt, pb = _plain_net(torch, b3=z, W4=np.eye(6, 1))
+    x = torch.zeros((1, 1, 6), device="cuda")
+    dy = torch.zeros((1, 1, 6), device="cuda")
+    dy[..., 0] = 1.0
+    work = tr.mlp_work(1, 1)
+    y = tr.mlp_fwd(pb, pt, x, work).cpu().numpy()[0, 0]
+    parts = mlp.split(tr.mlp_bwd(pb, pt, dy, work).cpu().numpy()[0].astype(np.float64))
+    h, dz = parts[6][0], parts[5]
+    z = z.astype(np.float64)
+    with np.errstate(over="ignore"):
+        e = np.exp(-z)
+    far = z <= -89.0
+    s = 1.0 / (1.0 + e)
+    rel = (np.abs(z) + 6.0) * 2.0**-23
+    assert (h[far] == 0.0).all() and (dz[far] == 0.0).all()
+    ok = ~far
+    assert (np.abs(h - z * s)[ok] <= (rel * np.abs(z) * s + 1e-38)[ok]).all()
+    # s (1 + z (1 - s)): the terms by themselves, for they cancel
+    assert (np.abs(dz - s * (1.0 + z * (1.0 - s)))[ok] <= (rel * s * (1.0 + np.abs(z)))[ok]).all()
+    assert (y[1:] == 0.0).all() and abs(y[0] - h.sum()) <= 256 * 2.0**-23 * np.abs(h).sum()
