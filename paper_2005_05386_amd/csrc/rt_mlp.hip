@@ -461,30 +461,41 @@ __global__ __launch_bounds__(NT, 4) void k_mlp_bwd(const float *__restrict__ par
             for (int i = 0; i < 7; ++i) dst[i * H] = a[i];
         }
     };
-    // a column's sum from its two halves (called by all threads)
-    auto column_sum = [&](float s, float *out) {
-        if (half == 0) S0[c] = s;
+    // a column's sum over the tile's rows in order (called by all threads)
+    auto column_sum = [&](const float (&v)[GRAD_ROWS], float *out) {
+        float s = 0.f;
+        if (half == 0) {
+#pragma unroll
+            for (int u = 0; u < GRAD_ROWS; ++u) s += v[u];
+            S0[c] = s;
+        }
         __syncthreads();
-        if (half == 1) out[T * H + c] = S0[c] + s;
+        if (half == 1) {
+            s = S0[c];
+#pragma unroll
+            for (int u = 0; u < GRAD_ROWS; ++u) s += v[u];
+            out[T * H + c] = s;
+        }
     };
     {   // output layer
-        float w4[6], a[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, s = 0.f;
+        float w4[6], a[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, dz[GRAD_ROWS];
 #pragma unroll
         for (int o = 0; o < 6; ++o) w4[o] = Pg[rti::OFF_W4 + o * H + c];
         const float *__restrict__ z3 = w.z3 + (T * TM + rh) * H + c;
         __bf16 *__restrict__ dzt = w.dz3t + (T * H + c) * TM + rh;
-#pragma unroll 1
-        for (int r0 = 0; r0 < GRAD_ROWS; r0 += 8) {
-            float z[8];
+        // (dz: first the column of z3, then, row by row, its signal)
 #pragma unroll
-            for (int u = 0; u < 8; ++u) z[u] = z3[(r0 + u) * H];
-            bf16x8 pk;
-            act_range<8>(z, [&](auto fast) {
+        for (int u = 0; u < GRAD_ROWS; ++u) dz[u] = z3[u * H];
+        act_range<GRAD_ROWS>(dz, [&](auto fast) {
+#pragma unroll
+            for (int r0 = 0; r0 < GRAD_ROWS; r0 += 8) {
+                bf16x8 pk;
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     const int m = rh + r0 + u;
-                    const Act t(z[u], fast);
-                    const float h = t.over(z[u]);
+                    const float z = dz[r0 + u];
+                    const Act t(z, fast);
+                    const float h = t.over(z);
                     float dh = 0.f;
 #pragma unroll
                     for (int o = 0; o < 6; ++o) {
@@ -492,18 +503,18 @@ __global__ __launch_bounds__(NT, 4) void k_mlp_bwd(const float *__restrict__ par
                         dh = fmaf(d, w4[o], dh);
                         a[o] = fmaf(d, h, a[o]);
                     }
-                    const float dz = dh * dsilu(z[u], t.over(1.0f));
-                    s += dz;
-                    pk[u] = (__bf16)dz;
+                    dz[r0 + u] = dh * dsilu(z, t.over(1.0f));
+                    pk[u] = (__bf16)dz[r0 + u];
                     A[m][c] = pk[u];
+                    if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // (four rows in registers at a time)
                 }
-            });
-            *(bf16x8 *)(dzt + r0) = pk;
-        }
+                *(bf16x8 *)(dzt + r0) = pk;
+            }
+        });
         if (c < 6)
             for (int u = 0; u < GRAD_ROWS; ++u) a[6] += Ds[rh + u][c];
         write_part(w.part4, a);
-        column_sum(s, w.cs3);
+        column_sum(dz, w.cs3);
     }
     // (column_sum's barrier: the tile of signals is complete)
     f32x4 acc[4][2];
@@ -522,21 +533,20 @@ __global__ __launch_bounds__(NT, 4) void k_mlp_bwd(const float *__restrict__ par
         }
     __syncthreads();
     {
-        float s = 0.f;
+        float dz[GRAD_ROWS];
         bf16x8 pk[GRAD_ROWS / 8];
         __bf16 *__restrict__ dzt = w.dz2t + (T * H + c) * TM + rh;
 #pragma unroll
         for (int q = 0; q < GRAD_ROWS / 8; ++q) {
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const float v = F[rh + 8 * q + u][c];
-                s += v;
-                pk[q][u] = (__bf16)v;
+                dz[8 * q + u] = F[rh + 8 * q + u][c];
+                pk[q][u] = (__bf16)dz[8 * q + u];
             }
             *(bf16x8 *)(dzt + 8 * q) = pk[q];
             __builtin_amdgcn_sched_barrier(0);
         }
-        column_sum(s, w.cs2);  // its barrier: the FP32 tile has been read
+        column_sum(dz, w.cs2);  // its barrier: the FP32 tile has been read
 #pragma unroll
         for (int q = 0; q < GRAD_ROWS / 8; ++q)
 #pragma unroll

@@ -239,3 +239,31 @@ def test_activation_values(env, lo, hi):
     # s (1 + z (1 - s)): the terms by themselves, for they cancel
     assert (np.abs(dz - s * (1.0 + z * (1.0 - s)))[ok] <= (rel * s * (1.0 + np.abs(z)))[ok]).all()
     assert (y[1:] == 0.0).all() and abs(y[0] - h.sum()) <= 256 * 2.0**-23 * np.abs(h).sum()
+
+
+def _chain(v, axis=0):
+    """FP32 sums in order."""
+    return np.add.accumulate(v.astype(np.float32), axis=axis, dtype=np.float32).take(-1, axis=axis)
+
+
+@pytest.mark.parametrize("batch", [1, 33, 64, 65, 200, 1000])
+def test_bias_sums_in_row_order(env, batch):
+    """The bias gradients are sums in the order of the rows, 64 at a time, then
+    the partial sums in order.  With b = 0 and W2 = W3 = 1 every activation is
+    0, silu' = 1/2, and W4 = (1, ..) on one output gives dz3 = dy / 2 and
+    dz2 = bf16(dz3) / 2, exactly: the sums can be formed again bit by bit."""
+    rt, torch, tr = env
+    say("bias sums batch=%d" % batch)
+    w4 = np.zeros((6, 256))
+    w4[np.arange(256) % 6, np.arange(256)] = 1.0
+    pt, pb = _plain_net(torch, W2=np.eye(256), W3=np.eye(256), W4=w4)
+    rng = np.random.default_rng(batch)
+    dy = (rng.normal(size=(1, batch, 6)) * 2.0 ** rng.integers(-12, 12, (1, batch, 6))).astype(np.float32)
+    work = tr.mlp_work(1, batch)
+    tr.mlp_fwd(pb, pt, torch.zeros((1, batch, 6), device="cuda"), work)
+    parts = mlp.split(tr.mlp_bwd(pb, pt, torch.tensor(dy, device="cuda"), work).cpu().numpy()[0])
+    dz3 = 0.5 * dy[0][:, np.arange(256) % 6]
+    dz2 = 0.5 * mlp.bf16_round(dz3).astype(np.float32)
+    for got, dz in ((parts[5], dz3), (parts[3], dz2)):
+        ref = _chain(np.stack([_chain(dz[r:r + 64]) for r in range(0, batch, 64)]))
+        assert np.array_equal(got, ref)
