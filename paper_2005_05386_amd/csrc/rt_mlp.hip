@@ -596,21 +596,33 @@ __global__ __launch_bounds__(NT, 4) void k_mlp_bwd(const float *__restrict__ par
 // Weight gradients of both 256x256 layers: dW[o][i] = sum_b dz[b][o] h[b][i],
 // with dz and h as [256][64] tiles, so that a lane's eight consecutive b of
 // an operand are one 16-byte load and nothing is transposed here.  A 64x64
-// tile of one layer of one network per block; the four waves split the batch
-// in contiguous quarters, each accumulating the whole tile (4x4 16x16x32 MFMA
-// tiles) straight from L2, and the partial tiles are added in a fixed order,
-// (w0 + w2) + (w1 + w3).  Bound by the 256 KB a tile reads through L2.
+// tile of one layer of one network per block; bound by the 256 KB that the tile
+// of a batch of 1024 reads through L2.
+struct WgradTile {
+    const __bf16 *A, *B;  // this lane's first element of the tile's dz and h columns
+    float *C;
+};
+__device__ __forceinline__ bool wgrad_tile(int n, int tiles, const rti::MlpWork &w, float *grad, WgradTile &t) {
+    int tx, ty, gl;
+    if (!xcd_tile(4, 4, 2 * n, tx, ty, gl)) return false;
+    const int g = gl >> 1, l = gl & 1, m0 = ty * 64, n0 = tx * 64, lane = threadIdx.x & 63;
+    const int64_t base = ((int64_t)g * tiles * H + (lane & 15)) * TM + (lane >> 4) * 8;
+    t.A = (l ? w.dz3t : w.dz2t) + base + m0 * TM;
+    t.B = (l ? w.h2t : w.h1t) + base + n0 * TM;
+    t.C = grad + g * rti::MLP_P + (l ? rti::OFF_W3 : rti::OFF_W2) + (int64_t)m0 * H + n0;
+    return true;
+}
+
+// Batches of whole 128 rows: the four waves split the batch in contiguous
+// quarters, each accumulating the whole tile (4x4 16x16x32 MFMA tiles) straight
+// from L2, and the partial tiles are added in a fixed order,
+// (w0 + w2) + (w1 + w3).
 __global__ __launch_bounds__(256, 4) void k_mlp_wgrad(int n, int tiles, rti::MlpWork w, float *__restrict__ grad) {
     __shared__ __attribute__((aligned(16))) float R[2][64][64];
-    int tx, ty, gl;
-    if (!xcd_tile(4, 4, 2 * n, tx, ty, gl)) return;
-    const int g = gl >> 1, l = gl & 1;
-    const int m0 = ty * 64, n0 = tx * 64;
+    WgradTile t;
+    if (!wgrad_tile(n, tiles, w, grad, t)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 15, grp = lane >> 4;
-    const int64_t base = ((int64_t)g * tiles * H + col) * TM + grp * 8;
-    const __bf16 *__restrict__ A = (l ? w.dz3t : w.dz2t) + base + m0 * TM;
-    const __bf16 *__restrict__ Bm = (l ? w.h2t : w.h1t) + base + n0 * TM;
     const int ns = 2 * tiles, s0 = ns * wave / 4, s1 = ns * (wave + 1) / 4;
     f32x4 acc[4][4];
 #pragma unroll
@@ -622,11 +634,11 @@ __global__ __launch_bounds__(256, 4) void k_mlp_wgrad(int n, int tiles, rti::Mlp
         const int64_t o = (int64_t)(s >> 1) * TM * H + (s & 1) * 32;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            a[i] = *(const bf16x8 *)(A + o + 16 * i * TM);
-            b[i] = *(const bf16x8 *)(Bm + o + 16 * i * TM);
+            a[i] = *(const bf16x8 *)(t.A + o + 16 * i * TM);
+            b[i] = *(const bf16x8 *)(t.B + o + 16 * i * TM);
         }
     };
-    if (s0 < s1) load(s0);
+    load(s0);
 #pragma unroll 2
     for (int s = s0; s < s1; ++s) {
         bf16x8 ca[4], cb[4];
@@ -655,13 +667,74 @@ __global__ __launch_bounds__(256, 4) void k_mlp_wgrad(int n, int tiles, rti::Mlp
     __syncthreads();
     if (wave < 2) each([](float &r, float v) { r = v + r; });
     __syncthreads();
-    float *__restrict__ C = grad + g * rti::MLP_P + (l ? rti::OFF_W3 : rti::OFF_W2);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int r = q * 16 + (tid >> 4), c = (tid & 15) * 4;
         const f32x4 v0 = *(const f32x4 *)&R[0][r][c], v1 = *(const f32x4 *)&R[1][r][c];
-        *(f32x4u *)(C + (int64_t)(m0 + r) * H + n0 + c) = v0 + v1;
+        *(f32x4u *)(t.C + (int64_t)r * H + c) = v0 + v1;
     }
+}
+
+// Other batches: one chain of sums through the whole batch in order, each wave a
+// 32x32 corner of the tile.  The waves share the operands through LDS, whole
+// fragments as the lanes loaded them, the next 64 rows on their way while the
+// current ones are multiplied (37 networks x 1329 rows: 109 us with every wave
+// loading its own operands, 74 with these; the four quarters, which would
+// round differently, 68).
+__global__ __launch_bounds__(256, 4) void k_mlp_wgrad_rows(int n, int tiles, rti::MlpWork w, float *__restrict__ grad) {
+    __shared__ bf16x8 S[2][2][2][4][64];  // [buffer][slice of 32 rows][A or B][16 columns][lane]
+    WgradTile t;
+    if (!wgrad_tile(n, tiles, w, grad, t)) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wm = (wave >> 1) * 2, wn = (wave & 1) * 2;  // in tiles of 16
+    f32x4 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // wave: slice wave >> 1 of operand wave & 1
+    const __bf16 *__restrict__ src = (wave & 1 ? t.B : t.A) + (wave >> 1) * 32;
+    bf16x8 v[4];
+    auto load = [&](int q) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = *(const bf16x8 *)(src + (int64_t)q * TM * H + 16 * i * TM);
+    };
+    auto store = [&](int q) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) S[q & 1][wave >> 1][wave & 1][i][lane] = v[i];
+    };
+    load(0);
+    store(0);
+    load(min(1, tiles - 1));
+    __syncthreads();
+    for (int q = 0; q < tiles; ++q) {
+        bf16x8 a[2][2], b[2][2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                a[s][i] = S[q & 1][s][0][wm + i][lane];
+                b[s][i] = S[q & 1][s][1][wn + i][lane];
+            }
+        // the other buffer was read before the last barrier
+        store(q + 1);
+        load(min(q + 2, tiles - 1));
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s][i], b[s][j], acc[i][j], 0, 0, 0);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                t.C[(int64_t)((wm + i) * 16 + 4 * (lane >> 4) + e) * H + (wn + j) * 16 + (lane & 15)] = acc[i][j][e];
 }
 
 // Sums of the row partials in order: block (q, g) takes one of the 16 sums of
@@ -805,7 +878,10 @@ hipError_t mlp_backward(int n, int B, const __bf16 *wb, const float *params, con
     const int tiles = (B + TM - 1) / TM;
     hipLaunchKernelGGL(k_mlp_wfrag, dim3(8, n), dim3(256), 0, s, wb, w.wt);
     hipLaunchKernelGGL(k_mlp_bwd, dim3(xcd_grid(tiles, 1, n)), dim3(NT), 0, s, params, dy, n, B, w);
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3(xcd_grid(4, 4, 2 * n)), dim3(256), 0, s, n, tiles, w, grad);
+    if (B % 128 == 0)
+        hipLaunchKernelGGL(k_mlp_wgrad, dim3(xcd_grid(4, 4, 2 * n)), dim3(256), 0, s, n, tiles, w, grad);
+    else
+        hipLaunchKernelGGL(k_mlp_wgrad_rows, dim3(xcd_grid(4, 4, 2 * n)), dim3(256), 0, s, n, tiles, w, grad);
     hipLaunchKernelGGL(k_mlp_sums, dim3(16, n), dim3(256), 0, s, B, w, grad);
     return hipGetLastError();
 }

@@ -267,3 +267,30 @@ def test_bias_sums_in_row_order(env, batch):
     for got, dz in ((parts[5], dz3), (parts[3], dz2)):
         ref = _chain(np.stack([_chain(dz[r:r + 64]) for r in range(0, batch, 64)]))
         assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("batch", [193, 256, 264, 1000, 1024])
+def test_weight_gradient_order(env, batch):
+    """The weight gradients of the 256x256 layers run through the batch in one
+    chain of 32-row products, or, for batches of whole 128 rows, in four
+    quarters added as (q0 + q2) + (q1 + q3).  One row of each 32 carries a power
+    of two (h2 = 64 where b2 = 64), among them a large one and its negative, next
+    to which the others vanish: every sum is exact or keeps the large one."""
+    rt, torch, tr = env
+    say("weight gradient order batch=%d" % batch)
+    pt, pb = _plain_net(torch, b2=64.0, W4=np.eye(6, 1) * np.ones(256))
+    ns = (batch + 31) // 32
+    ones = np.ones(ns, np.float32)
+    ones[[ns // 4, ns // 2]] = 2.0**40, -2.0**40
+    dy = np.zeros((1, batch, 6), np.float32)
+    dy[0, ::32, 0] = ones
+    work = tr.mlp_work(1, batch)
+    tr.mlp_fwd(pb, pt, torch.zeros((1, batch, 6), device="cuda"), work)
+    g = mlp.split(tr.mlp_bwd(pb, pt, torch.tensor(dy, device="cuda"), work).cpu().numpy()[0])[4]
+    v = 32.0 * ones  # dz3 h2 = (dy / 2) 64
+    if batch % 128 == 0:
+        q = [_chain(v[ns * k // 4:ns * (k + 1) // 4]) for k in range(4)]
+        ref = np.float32(q[0] + q[2]) + np.float32(q[1] + q[3])
+    else:
+        ref = _chain(v)
+    assert (g == ref).all(), (g[0, 0], ref)
