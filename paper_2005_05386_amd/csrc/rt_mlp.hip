@@ -781,22 +781,47 @@ __global__ void k_adamw(float *__restrict__ p, __bf16 *__restrict__ pb, float *_
     }
 }
 
-// dy = 2 (y - t) / batch and per-block squared-error sums (fixed order).
+// dy = 2 (y - t) / batch and per-block squared-error sums in a fixed order: 256
+// chains, each adding its elements in order, then a tree.  A chain's elements
+// are loaded by four threads, MSE_LOADS each at once, and pass through LDS (64
+// networks x 1024 rows: 13.6 us with the chain's thread loading them, 6.2
+// with these).
+constexpr int MSE_LOADS = 6;
 __global__ __launch_bounds__(1024) void k_mse_grad(const float *__restrict__ y, const float *__restrict__ t,
                                                   float *__restrict__ dy, int64_t n, float inv_batch,
                                                   float *__restrict__ part) {
-    __shared__ float sh[1024];
-    float acc = 0.f;
-    // part[b]: the elements whose index / 256 is b modulo the grid
+    __shared__ float D[4 * MSE_LOADS][256], sh[256];
+    const int lane = threadIdx.x & 255, q = threadIdx.x >> 8;
     const int64_t stride = (int64_t)gridDim.x * 256;
-    for (int64_t i = blockIdx.x * 256 + (threadIdx.x & 255) + (threadIdx.x >> 8) * stride; i < n; i += 4 * stride) {
-        float d = y[i] - t[i];
-        dy[i] = 2.f * d * inv_batch;
-        acc += d * d;
+    float acc = 0.f;
+    for (int64_t i0 = blockIdx.x * 256; i0 < n; i0 += 4 * MSE_LOADS * stride) {
+        const int64_t i = i0 + lane + q * stride;
+        float a[MSE_LOADS], b[MSE_LOADS];
+#pragma unroll
+        for (int u = 0; u < MSE_LOADS; ++u) {
+            const int64_t k = min(i + 4 * u * stride, n - 1);
+            a[u] = y[k];
+            b[u] = t[k];
+        }
+#pragma unroll
+        for (int u = 0; u < MSE_LOADS; ++u) {
+            const float d = a[u] - b[u];
+            D[4 * u + q][lane] = d;
+            if (i + 4 * u * stride < n) dy[i + 4 * u * stride] = 2.f * d * inv_batch;
+        }
+        __syncthreads();
+        if (q == 0) {
+#pragma unroll
+            for (int u = 0; u < 4 * MSE_LOADS; ++u) {
+                const float d = D[u][lane];
+                if (i + u * stride < n) acc += d * d;
+            }
+        }
+        __syncthreads();
     }
-    sh[threadIdx.x] = acc;
+    if (q == 0) sh[lane] = acc;
     __syncthreads();
-    for (int o = 512; o >= 1; o >>= 1) {
+    for (int o = 128; o >= 1; o >>= 1) {
         if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
         __syncthreads();
     }

@@ -294,3 +294,49 @@ def test_weight_gradient_order(env, batch):
     else:
         ref = _chain(v)
     assert (g == ref).all(), (g[0, 0], ref)
+
+
+@pytest.mark.parametrize("n,batch", [(3, 100), (2, 128)])
+def test_training_loop_equals_its_steps(env, n, batch):
+    """The training loop across a border of its groups of 16 steps, against the
+    same steps made one by one: the same bits."""
+    rt, torch, tr = env
+    say("training loop n_nets=%d batch=%d" % (n, batch))
+    kappa, scale = np.linspace(0.4, 2.5, n).astype(np.float32), np.full(n, 0.3, np.float32)
+    steps, lr, warmup, seed = 18, 2e-3, 200, 5
+    state = []
+    for _ in range(2):
+        p, pt, pb = _params(torch, n)
+        state.append([pt, pb, torch.zeros_like(pt), torch.zeros_like(pt)])
+    log, _ = tr.surrogate_train(kappa, scale, *state[0], batch, steps, seed=seed, lr=lr, warmup=warmup, log_every=1)
+    pt, pb, m, v = state[1]
+    work = tr.mlp_work(n, batch)
+    for step in range(1, steps + 1):
+        if step % 16 == 1:
+            X, Y, _ = tr.surrogate_gen(kappa, scale, 16 * batch, 0.01, mode=4, seed=seed + 1000003 * ((step - 1) // 16 + 1))
+        j = (step - 1) % 16
+        x, t = X[:, j::16].contiguous(), Y[:, j::16].contiguous()
+        dy, part = tr.mse_grad(tr.mlp_fwd(pb, pt, x, work), t, batch)
+        g = tr.mlp_bwd(pb, pt, dy, work)
+        tr.adamw(pt, pb, m, v, g, float(np.float32(lr) * np.float32(step) / np.float32(warmup)), step)
+        assert torch.equal(log[step - 1], part), step
+    for a, b in zip(*state):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n", [100, 16384, 16385, 400000])
+def test_mse_summation_order(env, n):
+    """Each of a block's 256 chains adds its squares in order, then the chains
+    are added in halves.  With 12-bit differences the squares are exact, and the
+    partial sums can be formed again bit by bit."""
+    rt, torch, tr = env
+    say("mse summation order n=%d" % n)
+    rng = np.random.default_rng(n)
+    d = (rng.integers(-4095, 4096, n) * 2.0 ** rng.integers(-20, 0, n)).astype(np.float32)
+    _, part = tr.mse_grad(torch.tensor(d, device="cuda"), torch.zeros(n, device="cuda"), 7)
+    sq = np.zeros(-(-n // 16384) * 16384, np.float32)
+    sq[:n] = d * d
+    s = _chain(sq.reshape(-1, 64, 256))
+    while s.shape[1] > 1:
+        s = s[:, :s.shape[1] // 2] + s[:, s.shape[1] // 2:]
+    assert np.array_equal(part.cpu().numpy(), s[:, 0])
