@@ -572,19 +572,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LAT ? RT_LA
                         if constexpr (FREE) {
                             // Nothing in reach of this window: the steps are free flight,
                             // and so are those of the further windows that end before the
-                            // nearest cut region or object.  There a g-unit velocity has
-                            // Euclidean speed 1 (2% margin), the step's stages included.
+                            // nearest cut region or object.  The velocity is constant in
+                            // flight, so that end follows from the wave's largest Euclidean
+                            // speed (not from 1, the speed of a g-unit velocity there, which
+                            // coarse steps do not keep: Euler steps through a sharp bump
+                            // leave it up to a third faster).
                             // The twist is free only beyond its ball, and only if no
                             // velocity component is too small to absorb its acceleration.
                             const bool empty = ((FLAT && KIND != KIND_EUCLID ? bmask : 0ull) | sm[0] | sm[1] | sm[2] | sm[3] | omask) == 0;
                             if (empty && (FLAT || ballot(act && !(fminf(fabsf(y.x), fabsf(y.y)) >= TWIST_MIN_V)) == 0)) {
                                 const float D = free_distance<KIND>(A, Bs, SPH, PLN, TOR, lane, pmn, pmx);
-                                const float q = fminf((D - 2e-4f) * rcp_((FLAT ? 1.02f : 1.08f) * A.h_max), 1e6f);
-                                n_free = (int)q - 2;
+                                const float v = sqrt_(wave_max(act ? dot(y, y) : 0.f)) * 1.0001f;
+                                const float q = (D - 2e-4f) * rcp_(fmaxf(v, 1e-3f) * A.h_max) - 2.0f;
+                                n_free = (int)fminf(fmaxf(q, 0.f), 1e6f);
+                                // (an empty window was found empty by its own bound)
                                 if constexpr (FLAT) n_free = max(n_free, A.K);
                                 // (adaptive steps cull at multiples of the window)
                                 if constexpr (!TIGHT) n_free = n_free / A.K * A.K;
-                                n_free = max(n_free, 0);
                             }
                         }
                     }

@@ -142,3 +142,35 @@ def test_taped_trace_equals_plain(rt):
             assert np.array_equal(out[k], ref[k]), k
         tapes.append(tape.cpu().numpy())
     assert np.array_equal(tapes[0], tapes[1], equal_nan=True) and np.array_equal(tapes[0], tapes[2], equal_nan=True)
+
+
+def fast_rays(bump):
+    """A sharp bump filling a narrow view, in the middle of a box of planes with
+    a broad bump and two spheres in it."""
+    wl = few(0)
+    wl["metric"] = W.metric(W.GRAPH_GAUSS, bumps=np.array([bump, (0.4, 0.3, -0.2, 4.0, 0.4)]))
+    wl["scene"] = W.scene(spheres=[(0.1, 0.1, 3.0, 0.05), (-0.3, 0.2, 6.0, 0.2)],
+                          planes=[(s * e[0], s * e[1], s * e[2], 7.0) for e in np.eye(3) for s in (1.0, -1.0)])
+    wl["camera"] = W.camera(384, 256, eye=(0.0, 0.0, -10.0 * bump[4]), forward=(0.0, 0.0, 1.0), vfov_deg=35.0)
+    return wl
+
+
+# Steps too coarse for the bump: the integrator loses the unit speed, and in FP64
+# the fastest rays leave it at about 1.07 (Euler, h = 0.01), 1.3 (Euler, h = 0.005)
+# and 1.09 (RK45).  The bound of a culling window of K steps holds up to
+# 1.02 (K + 1) / K: 1.08 for 16 steps, and 2.04 for one.
+@pytest.mark.parametrize("rule,bump", [
+    (dict(kind=W.EULER, h=0.01), (2.0, 0.0, 0.0, 0.0, 0.15)),
+    (dict(kind=W.EULER, h=0.01, pass_steps=300, cull_every=1), (2.0, 0.0, 0.0, 0.0, 0.15)),
+    (dict(kind=W.EULER, h=0.005, cull_every=1), (0.6, 0.0, 0.0, 0.0, 0.05)),
+    (dict(kind=W.RK45, h=0.02, rtol=1e-2, atol=1e-2, h_max=0.05, cull_every=1), (2.0, 0.0, 0.0, 0.0, 0.15)),
+])
+def test_flight_of_rays_off_unit_speed(rt, rule, bump):
+    """Rays that leave a bump faster than 1 fly as far as their own speed
+    allows: nothing behind the bump is passed over."""
+    print("[gpu-case] rays off unit speed", rule, bump, flush=True)
+    wl = fast_rays(bump)
+    g = same(rt, wl, dict(wl["rule"], **rule))
+    far = g["id"] >= 2  # a plane: its distance from the bump over the time from there
+    speed = np.linalg.norm(g["hit"][far], axis=1) / (g["t"][far] - 10.0 * bump[4])
+    assert (speed > 1.025).any()
