@@ -84,11 +84,18 @@ __device__ __forceinline__ uint64_t bump_window(const float4 *__restrict__ Bs, i
     return mask;
 }
 
-// Steps of length h that every lane with `on` can take from p before it can
-// reach a cut region (an anisotropic one taken as a ball), by the speed bound
-// |y| <= 1 with a 2% margin; called by the whole wave.
+// Steps of length h that every lane of the wave can take at constant velocity
+// before the first lane's gap (1e6: none) is used up by the fastest lane (the
+// shots' own speed, which coarse steps take away from that of a g-unit velocity).
+__device__ __forceinline__ int steps_within(float gap, V3<float> y, bool on, float h) {
+    const float v = sqrt_(wave_max(on ? dot(y, y) : 0.f)) * 1.0001f;
+    const float q = (wave_min(on ? gap : 1e6f) * 0.999f - 2e-4f) * rcp_(fmaxf(v, 1e-3f) * h) - 2.0f;
+    return (int)fminf(fmaxf(q, 0.f), 1e6f);
+}
+// The same from p to the next cut region (an anisotropic one taken as a ball),
+// for the lanes with `on`; called by the whole wave.
 template <int KIND>
-__device__ __forceinline__ int free_steps(const float4 *__restrict__ Bs, int n, V3<float> p, bool on, float h) {
+__device__ __forceinline__ int free_steps(const float4 *__restrict__ Bs, int n, V3<float> p, V3<float> y, bool on, float h) {
     float gap = 1e6f;
     for (int b = 0; b < n; ++b) {
         const float4 b0 = Bs[2 * b], b1 = Bs[2 * b + 1];
@@ -98,8 +105,7 @@ __device__ __forceinline__ int free_steps(const float4 *__restrict__ Bs, int n, 
         else R = sqrt_(b1.w) * rsqrt_(fminf(fminf(b1.x, b1.y), b1.z));
         gap = fminf(gap, sqrt_(dot(d, d)) - R * 1.0001f);
     }
-    const float q = (wave_min(on ? gap : 1e6f) * 0.999f - 2e-4f) * rcp_(1.02f * h);
-    return max((int)fminf(q, 1e6f) - 2, 0);
+    return steps_within(gap, y, on, h);
 }
 
 // Integrate the geodesic from (q, v) over arc length T: n = ceil(T / h)
@@ -131,7 +137,7 @@ __device__ __forceinline__ bool shoot(IAcc<KIND> &acc, const rti::IllumArgs &A, 
                            ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mask >> 32), src) << 32);
                 if (acc.mask == 0) {
                     const V3<float> dx = free_step<STEP_RK4>(y, h);
-                    const int m = free_steps<KIND>(acc.B, A.n_bumps, xh + xl, on, h);
+                    const int m = free_steps<KIND>(acc.B, A.n_bumps, xh + xl, y, on, h);
                     if (m > 0 && ballot(on && !finite6(dx, mk(0.f, 0.f, 0.f))) == 0) {
                         if (on) {
                             y = y + mk(0.f, 0.f, 0.f);
@@ -301,8 +307,7 @@ __device__ __forceinline__ bool shoot_rows(const float4 (&b0)[NB], const float4 
                 const V3<float> d = mk(p.x - b0[k].x, p.y - b0[k].y, p.z - b0[k].z);
                 gap = fminf(gap, sqrt_(dot(d, d)) - R[k]);
             }
-            const float f = (wave_min(ok ? gap : 1e6f) * 0.999f - 2e-4f) * rcp_(1.02f * h);
-            const int m = uniform_i(min((int)fminf(f, 1e6f) - 2, n - 1 - i));
+            const int m = uniform_i(min(steps_within(gap, y, ok, h), n - 1 - i));
             fly = i + 4;
             if (m > 0) {
                 const V3<float> dx1 = free_step<STEP_RK4>(y, h);

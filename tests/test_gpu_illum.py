@@ -242,3 +242,46 @@ def test_spread_bumps_equal_the_walk(rt, n, w, h):
     assert np.array_equal(ta["hit"], tb["hit"]) and (ta["id"] >= 0).any()
     for k in sa:
         assert np.array_equal(sa[k], sb[k], equal_nan=True), k
+
+
+@pytest.mark.parametrize("n", [4, 33])
+def test_shot_off_unit_speed(rt, n):
+    """A shot that leaves a bump faster than 1 (RK4 with h = 0.03 through the tip
+    of a = 0.6, sigma = 0.1, the distance to it searched with the oracle)
+    flies as far as its own speed allows, here to a sharp bump 25 units on
+    (the last flight starts half way, where the tip is no nearer).  The
+    same pixel with one more bump, of amplitude zero and a cut that holds the
+    scene, flies nowhere: equal bit for bit, for bumps spread over the lanes and
+    walked.  (The light is 280 units off, so that the first target of the
+    continuation, an eighth of the way, lies behind that bump too.)"""
+    say("illumination, shot off unit speed, %d bumps" % n)
+    wl = W.with_size(W.get("bumps16_1080p"), 1, 1)
+    wl["scene"] = W.scene(planes=[(0.0, 1.0, 0.0, -1.0)])
+    wl["camera"] = W.camera(1, 1, eye=(0.0, 0.5, -4.0), forward=(0.0, -0.75, 1.0))
+    light = dict(LIGHT, pos=(27.0, 280.0, 15.0), h=0.03, max_steps=20000)
+
+    def run(bumps):
+        b = np.concatenate([bumps, np.tile([[0.0, 40.0, -40.0, 40.0, 0.1]], (n - len(bumps), 1))])
+        out = []
+        for sigma in (0.1, 1000.0):
+            b[-1, 4] = sigma
+            out.append(_run(rt, dict(wl, metric=dict(wl["metric"], bumps=b[None].astype(np.float32))), light=light))
+        return out
+    q = run(np.zeros((0, 5)) + 0.1)[0][0]["hit"][0].astype(np.float64)
+    e = np.array(light["pos"]) - q
+    e /= np.linalg.norm(e)
+    best = None
+    for d in np.arange(0.75, 0.78, 0.001):
+        tip = np.array([[0.6, *(q + d * e), 0.1]]).astype(np.float32)
+        z, ok = oracle.Oracle(W.metric(W.GRAPH_GAUSS, bumps=tip), wl["scene"]).shoot(q, e, 3.0, light["h"])
+        speed = np.linalg.norm(z[3:])
+        if ok and speed < 1.075 and (best is None or speed > best[0]):
+            best = speed, tip, z
+    speed, tip, z = best
+    say("speed", speed, "after the tip at", tip[0, 1:4] - q)
+    assert speed > 1.04
+    far = np.array([[0.5, *(z[:3] + 24.0 * z[3:] / speed), 0.1]])
+    (ta, sa), (tb, sb) = run(np.concatenate([tip, far]))
+    assert np.array_equal(ta["hit"], tb["hit"]) and np.abs(ta["hit"][0] - q).max() < 1e-6
+    for k in sa:
+        assert np.array_equal(sa[k], sb[k], equal_nan=True), (k, sa[k], sb[k])
