@@ -682,8 +682,9 @@ __global__ __launch_bounds__(256) void k_illum_solve(rti::IllumArgs A, const flo
         const V3<float> Xb = mk(__shfl(X.x, s2), __shfl(X.y, s2), __shfl(X.z, s2));
         const int oka = __shfl((int)ok, s1), okb = __shfl((int)ok, s2);
         int next = 0;  // iterations done if the pixel goes on, else 0
-        if (live && role == 0 && ok) {
-            next = advance<KIND>(A, P, L, it, oka && okb, X, Y, Xa, Xb, al, be, T, last, cont, code, A.status + pix);
+        if (live && role == 0) {
+            if (ok) next = advance<KIND>(A, P, L, it, oka && okb, X, Y, Xa, Xb, al, be, T, last, cont, code, A.status + pix);
+            // a pixel that ends, also by a failed shot, leaves the state of its last step
             if (next == 0) {
                 A.w_al[pix] = al;
                 A.w_be[pix] = be;

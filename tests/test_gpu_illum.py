@@ -285,3 +285,22 @@ def test_shot_off_unit_speed(rt, n):
     assert np.array_equal(ta["hit"], tb["hit"]) and np.abs(ta["hit"][0] - q).max() < 1e-6
     for k in sa:
         assert np.array_equal(sa[k], sb[k], equal_nan=True), (k, sa[k], sb[k])
+
+
+@pytest.mark.parametrize("max_steps", [40, 300, 600, 900])
+@pytest.mark.parametrize("w,h", [(24, 16), (160, 104)])
+def test_shots_over_the_step_budget(rt, w, h, max_steps):
+    """A pixel whose shot fails after some Newton steps (here: longer than
+    max_steps) keeps the state of its last step, whichever launch it ends in: the
+    same direction and length from two runs, and from the table padded to 33
+    bumps, whose pixels end in another launch."""
+    say("illumination", w, h, "max_steps", max_steps)
+    wl = W.with_size(W.get("bumps16_1080p"), w, h)
+    b = wl["metric"]["bumps"][0]
+    pad = np.tile(np.array([[0.0, 3.0, 3.0, 3.0, 0.3]], np.float32), (33 - len(b), 1))
+    res = [_run(rt, dict(wl, metric=dict(wl["metric"], bumps=m[None])), light=dict(LIGHT, max_steps=max_steps))[1]
+           for m in (b, b, np.concatenate([b, pad]))]
+    assert (res[0]["status"] == -1).any()
+    for other in res[1:]:
+        for k in other:
+            assert np.array_equal(res[0][k], other[k], equal_nan=True), k
