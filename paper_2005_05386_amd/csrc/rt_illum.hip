@@ -587,10 +587,27 @@ __device__ __forceinline__ bool newton(const rti::IllumArgs &A, const Pixel<KIND
 // Angle displacement of the finite-difference shots.
 constexpr float ILLUM_EPS = 1e-3f;
 
-// Waves that a short list is spread over: two per SIMD.  The line is flat: a
-// 1080p frame takes 283, 281, 280, 272, 272 and 278 ms at 512, 768, 1024, 1536,
-// 2048 and 4096 (before k_illum_rows), for its time is the longest chain.
+// Kinds whose shots walk no list of bumps: a step is one instruction stream, and
+// waves that share a SIMD slow each other.
+template <int KIND> constexpr bool cheap_steps = !bump_cull<KIND> && !is_deform(KIND);
+
+// Waves that a short list is spread over: two per SIMD, one for the kinds of cheap
+// steps.  With a bump walk the line is flat: a 1080p frame takes 283, 281, 280,
+// 272, 272 and 278 ms at 512, 768, 1024, 1536, 2048 and 4096 (before
+// k_illum_rows), for its time is the longest chain.  The 160x104 quadric takes 58,
+// 65 and 95 ms at 1024, 2048 and 4096, the twist 10.1, 12.3 and 17.7.
 constexpr int SOLVE_WAVES = 2048;
+template <int KIND> constexpr int solve_waves = cheap_steps<KIND> ? SOLVE_WAVES / 2 : SOLVE_WAVES;
+
+// Lists of the kinds of cheap steps longer than this are bound by issue, not by
+// their longest chain: k_illum_solve then takes one iteration and packs the pixels
+// that go on into the next list, and the continuation stops at each target, so
+// that waves stay full (the 420x405 quadric: 81 ms, and 94 with each pixel solved
+// to its end; 77 before there was such a launch).  Kinds with a bump walk are
+// faster solved to the end at any length (431x401: 16 anisotropic bumps 143 ms, 189
+// packed; 16 isotropic ones 56 and 75; 16 deformations 53 and 66).
+constexpr int PACK_ABOVE = 16384;
+template <int KIND> __device__ __host__ __forceinline__ bool packs(int64_t n) { return cheap_steps<KIND> && n > PACK_ABOVE; }
 
 // Pixels that k_illum_rows takes, one per wave: four waves per SIMD.  1080p with
 // 16 bumps takes 245, 240, 235 and 248 ms at 1024, 2048, 4096 and 8192; frames
@@ -604,17 +621,18 @@ inline int solve_blocks(int64_t n) {
 }
 
 // What the shots of iteration it of a pixel lead to: the iterations done if it
-// goes on (-1: none, at the next target of the continuation), else 0.
+// goes on (-1: none, at the next target of the continuation), else 0.  through:
+// a pixel that converges at a target of the continuation goes on to the next.
 template <int KIND>
 __device__ __forceinline__ int advance(const rti::IllumArgs &A, const Pixel<KIND> &P, V3<float> L, int it, bool okab,
                                        V3<float> X, V3<float> Y, V3<float> Xa, V3<float> Xb, float &al, float &be,
-                                       float &T, float &last, float &cont, int &code, int *status) {
+                                       float &T, float &last, float &cont, int &code, int *status, bool through = true) {
     const V3<float> Lp = target(cont, P, L);
     const V3<float> F = X - Lp;
     const int j = assess(A, it, F, last);
     if (j == J_STEP) {
         if (okab && newton<KIND>(A, P, Lp, ILLUM_EPS, al, be, T, F, X, Y, Xa, Xb) && it + 1 < A.max_iters) return it + 1;
-    } else if (j == J_CONV && code == ST_CONT) {
+    } else if (j == J_CONV && code == ST_CONT && through) {
         // the next stage of the continuation starts from here
         const int st = (int)(cont * rti::ILLUM_CONT_STAGES + 0.5f);
         const float lam0 = (float)st / rti::ILLUM_CONT_STAGES, lam1 = (float)(st + 1) / rti::ILLUM_CONT_STAGES;
@@ -630,7 +648,8 @@ __device__ __forceinline__ int advance(const rti::IllumArgs &A, const Pixel<KIND
 }
 
 // A short list[it & 1]: the pixels' remaining iterations, each pixel on its
-// own; the launches that follow find their lists empty.  Lanes 3j, 3j+1, 3j+2
+// own (one iteration where packs(n_in)); the launches that follow find their lists
+// empty.  Lanes 3j, 3j+1, 3j+2
 // of a wave shoot the base and the two displaced directions of pixel j side by
 // side; lane 3j tests the residual, takes the Newton step and hands the new state to its
 // neighbours.  During the continuation a pixel that converges goes on to the
@@ -651,7 +670,8 @@ __global__ __launch_bounds__(256) void k_illum_solve(rti::IllumArgs A, const flo
     const V3<float> L = mk(A.light[0], A.light[1], A.light[2]);
     const float eps = ILLUM_EPS;
     const int lane = lane_id(), role = lane % 3, src = lane - role;
-    const int per_wave = min(PAR_PIX, max(1, (n_in + SOLVE_WAVES - 1) / SOLVE_WAVES));
+    const int per_wave = min(PAR_PIX, max(1, (n_in + solve_waves<KIND> - 1) / solve_waves<KIND>));
+    const bool through = !packs<KIND>((int64_t)A.n_sets * A.width * A.height);
     const int base = (blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6)) * per_wave;
     if (base >= n_in) return;
     const int k = base + lane / 3;
@@ -683,7 +703,7 @@ __global__ __launch_bounds__(256) void k_illum_solve(rti::IllumArgs A, const flo
         const int oka = __shfl((int)ok, s1), okb = __shfl((int)ok, s2);
         int next = 0;  // iterations done if the pixel goes on, else 0
         if (live && role == 0) {
-            if (ok) next = advance<KIND>(A, P, L, it, oka && okb, X, Y, Xa, Xb, al, be, T, last, cont, code, A.status + pix);
+            if (ok) next = advance<KIND>(A, P, L, it, oka && okb, X, Y, Xa, Xb, al, be, T, last, cont, code, A.status + pix, through);
             // a pixel that ends, also by a failed shot, leaves the state of its last step
             if (next == 0) {
                 A.w_al[pix] = al;
@@ -698,6 +718,16 @@ __global__ __launch_bounds__(256) void k_illum_solve(rti::IllumArgs A, const flo
         T = __shfl(T, src);
         const int ended = __popcll(ballot(live && role == 0 && next == 0));
         live = live && next != 0;
+        if (packs<KIND>(n_in)) {
+            if (live && role == 0) {
+                A.w_al[pix] = al;
+                A.w_be[pix] = be;
+                A.w_T[pix] = T;
+                A.w_F[pix] = last;
+            }
+            append(A.list[(it + 1) & 1], A.ctr + it + 1, pix, live && role == 0);
+            return;
+        }
         it = max(next, 0);
         if (rows) {
             int left = 0;
@@ -1035,6 +1065,7 @@ void illum_rounds(const rti::IllumArgs &a, const rti::DeviceData &d, int grid, h
     const int sgrid = solve_blocks((int64_t)a.n_sets * a.width * a.height);
     const int rgrid = (int)std::min<int64_t>((int64_t)a.n_sets * a.width * a.height, ROWS_MAX);
     const bool rows = KIND == KIND_GRAPH && a.n_bumps > 0 && a.n_bumps <= 32;
+    const bool packed = packs<KIND>((int64_t)a.n_sets * a.width * a.height);
     // one iteration's launches; solve: the pixels of a short list go to their end
     auto iteration = [&](const rti::IllumArgs &q, int it, bool solve) {
         if (solve) hipLaunchKernelGGL((k_illum_solve<KIND, ONE>), dim3(sgrid), dim3(256), 0, s, q, d.bump_f, it, rows);
@@ -1057,7 +1088,7 @@ void illum_rounds(const rti::IllumArgs &a, const rti::DeviceData &d, int grid, h
     for (int round = 1; round <= rti::ILLUM_RETRY_ROUNDS; ++round) {
         r.ctr = a.ctr + round * rti::illum_ctr_words(a.max_iters);
         hipLaunchKernelGGL((k_illum_seed<KIND, ONE>), dim3(grid), dim3(256), 0, s, r, d.bump_f, r.ctr);
-        for (int it = 0; it < r.max_iters; ++it) iteration(r, it, it == 0);
+        for (int it = 0; it < r.max_iters; ++it) iteration(r, it, it == 0 || packed);
     }
     // continuation in the light position for the pixels still unsolved, half
     // the iterations per stage (a quarter loses 15% of the quadric's hits)
@@ -1068,7 +1099,7 @@ void illum_rounds(const rti::IllumArgs &a, const rti::DeviceData &d, int grid, h
         r.cont = lam1;
         r.conv_code = st + 1 < rti::ILLUM_CONT_STAGES ? ST_CONT : ST_CONV;
         hipLaunchKernelGGL((k_illum_cont<KIND, ONE>), dim3(grid), dim3(256), 0, s, r, d.bump_f, r.ctr, lam0, lam1);
-        for (int it = 0; it < r.max_iters; ++it) iteration(r, it, it == 0);
+        for (int it = 0; it < r.max_iters; ++it) iteration(r, it, it == 0 || packed);
     }
     hipLaunchKernelGGL((k_illum_finish<KIND, ONE>), dim3(grid), dim3(256), 0, s, a, d.bump_f, d.sph_f, d.pln_f,
                        d.tor_f);

@@ -304,3 +304,12 @@ def test_shots_over_the_step_budget(rt, w, h, max_steps):
     for other in res[1:]:
         for k in other:
             assert np.array_equal(res[0][k], other[k], equal_nan=True), k
+
+
+def test_packed_lists(rt):
+    """The quadric's lists above the line where the iterations are packed again
+    after each shot (16384 pixels): the geodesics found reach the light."""
+    say("illumination, quadric 200x160, packed lists")
+    wl = W.with_size(W.get("quadric_1080p"), 200, 160)
+    tra, sh = _run(rt, wl)
+    _check_found(wl, tra, sh, 0.9, sample=400)
