@@ -1027,6 +1027,7 @@ rt_status rt_illuminate(rt_ctx *c, const rt_camera *cam, const rt_outputs *trace
     a.n_tori = (int)c->tor.size();
     a.width = cam->width;
     a.height = cam->height;
+    a.n_cu = c->n_cu;
     a.hit = traced->hit;
     a.id = traced->id;
     for (int k = 0; k < 3; ++k) a.light[k] = L->pos[k];

@@ -492,19 +492,20 @@ template <class P> __device__ __forceinline__ V3<float> target(float cont, const
 
 // Pixels per wave when the three shots of an iteration run on three lanes.
 constexpr int PAR_PIX = 21;
-// A list is short while 8192 waves (one pass of the GPU) hold it at three
-// lanes per pixel.
-constexpr int SHORT_LIST = 8192 * PAR_PIX;
+// The lines below count waves of the whole device, here per CU (sizes quoted are
+// those of 256 CUs).  A list is short while 32 waves per CU hold it at three lanes
+// per pixel (172032 pixels).
+__device__ __host__ __forceinline__ int short_list(const rti::IllumArgs &A) { return A.n_cu * 32 * PAR_PIX; }
 
 // Pixel t of the frames, in the order of the lists, and the count of such t.
-// Frames of more than SHORT_LIST pixels go in 8x8 tiles, one per wave (-1
+// Frames of more than short_list pixels go in 8x8 tiles, one per wave (-1
 // beyond the edge): the windows of the full-grid launches then cover a tile
 // instead of a strip of 64 pixels and reach fewer bumps (1080p with 16 bumps
 // 236 ms in strips, 224 in tiles; 818x557 with 4 bumps 18.5 and 18.3).  Smaller
 // frames, whose lists are solved pixel by pixel, keep the strips (127x75 with 3
 // bumps 3.97 ms, in tiles 4.45: the finish reaches more objects at once).
 __device__ __forceinline__ bool in_tiles(const rti::IllumArgs &A) {
-    return (int64_t)A.n_sets * A.width * A.height > SHORT_LIST;
+    return (int64_t)A.n_sets * A.width * A.height > short_list(A);
 }
 __device__ __forceinline__ int64_t pixel_count(const rti::IllumArgs &A) {
     return in_tiles(A) ? (int64_t)A.n_sets * ((A.width + 7) / 8) * ((A.height + 7) / 8) * 64
@@ -591,13 +592,15 @@ constexpr float ILLUM_EPS = 1e-3f;
 // waves that share a SIMD slow each other.
 template <int KIND> constexpr bool cheap_steps = !bump_cull<KIND> && !is_deform(KIND);
 
-// Waves that a short list is spread over: two per SIMD, one for the kinds of cheap
+// Waves per CU that a short list is spread over: two per SIMD, one for the kinds of cheap
 // steps.  With a bump walk the line is flat: a 1080p frame takes 283, 281, 280,
 // 272, 272 and 278 ms at 512, 768, 1024, 1536, 2048 and 4096 (before
 // k_illum_rows), for its time is the longest chain.  The 160x104 quadric takes 58,
 // 65 and 95 ms at 1024, 2048 and 4096, the twist 10.1, 12.3 and 17.7.
-constexpr int SOLVE_WAVES = 2048;
-template <int KIND> constexpr int solve_waves = cheap_steps<KIND> ? SOLVE_WAVES / 2 : SOLVE_WAVES;
+constexpr int SOLVE_WAVES = 8;
+template <int KIND> __device__ __forceinline__ int solve_waves(const rti::IllumArgs &A) {
+    return A.n_cu * (cheap_steps<KIND> ? SOLVE_WAVES / 2 : SOLVE_WAVES);
+}
 
 // Lists of the kinds of cheap steps longer than this are bound by issue, not by
 // their longest chain: k_illum_solve then takes one iteration and packs the pixels
@@ -606,18 +609,22 @@ template <int KIND> constexpr int solve_waves = cheap_steps<KIND> ? SOLVE_WAVES 
 // to its end; 77 before there was such a launch).  Kinds with a bump walk are
 // faster solved to the end at any length (431x401: 16 anisotropic bumps 143 ms, 189
 // packed; 16 isotropic ones 56 and 75; 16 deformations 53 and 66).
-constexpr int PACK_ABOVE = 16384;
-template <int KIND> __device__ __host__ __forceinline__ bool packs(int64_t n) { return cheap_steps<KIND> && n > PACK_ABOVE; }
+constexpr int PACK_ABOVE = 64;
+template <int KIND> __device__ __host__ __forceinline__ bool packs(const rti::IllumArgs &A, int64_t n) {
+    return cheap_steps<KIND> && n > A.n_cu * PACK_ABOVE;
+}
 
-// Pixels that k_illum_rows takes, one per wave: four waves per SIMD.  1080p with
+// Pixels per CU that k_illum_rows takes, one per wave: four waves per SIMD.  1080p with
 // 16 bumps takes 245, 240, 235 and 248 ms at 1024, 2048, 4096 and 8192; frames
 // of 3 to 90 thousand pixels change by 1% to 15% in the same order.
-constexpr int ROWS_MAX = 4096;
+constexpr int ROWS_MAX = 16;
+__device__ __host__ __forceinline__ int rows_max(const rti::IllumArgs &A) { return A.n_cu * ROWS_MAX; }
 
 // Blocks of four waves that hold any short list of a frame of n pixels, and
-// SOLVE_WAVES waves.
-inline int solve_blocks(int64_t n) {
-    return (int)std::max<int64_t>(SOLVE_WAVES / 4, (std::min<int64_t>(n, SHORT_LIST) + 4 * PAR_PIX - 1) / (4 * PAR_PIX));
+// SOLVE_WAVES waves per CU.
+inline int solve_blocks(const rti::IllumArgs &A, int64_t n) {
+    return (int)std::max<int64_t>(A.n_cu * SOLVE_WAVES / 4,
+                                  (std::min<int64_t>(n, short_list(A)) + 4 * PAR_PIX - 1) / (4 * PAR_PIX));
 }
 
 // What the shots of iteration it of a pixel lead to: the iterations done if it
@@ -657,21 +664,21 @@ __device__ __forceinline__ int advance(const rti::IllumArgs &A, const Pixel<KIND
 // steps, so a launch per iteration lasted as long as its longest shot, and the
 // sum of those maxima was most of the time; here a pixel's time is the sum of
 // its own shots.  Same values as the launches one by one.
-// rows: k_illum_rows follows; lists of up to ROWS_MAX pixels are left to it
-// whole, and of a longer list the last ROWS_MAX pixels to be solved (their
+// rows: k_illum_rows follows; lists of up to rows_max pixels are left to it
+// whole, and of a longer list the last rows_max pixels to be solved (their
 // state in w_X and the arrays of the state).
 template <int KIND, bool ONE>
 __global__ __launch_bounds__(256) void k_illum_solve(rti::IllumArgs A, const float4 *__restrict__ BF, int it, bool rows) {
     const int *in = A.list[it & 1];
     const int n_in = A.ctr[it];
-    if (n_in > SHORT_LIST || (rows && n_in <= ROWS_MAX)) return;
+    if (n_in > short_list(A) || (rows && n_in <= rows_max(A))) return;
     int *done = A.ctr + 2 * (A.max_iters + 1) + it, *handed = A.ctr + 3 * (A.max_iters + 1) + it;
     const uint64_t all = all_bumps(A.n_bumps);
     const V3<float> L = mk(A.light[0], A.light[1], A.light[2]);
     const float eps = ILLUM_EPS;
     const int lane = lane_id(), role = lane % 3, src = lane - role;
-    const int per_wave = min(PAR_PIX, max(1, (n_in + solve_waves<KIND> - 1) / solve_waves<KIND>));
-    const bool through = !packs<KIND>((int64_t)A.n_sets * A.width * A.height);
+    const int per_wave = min(PAR_PIX, max(1, (n_in + solve_waves<KIND>(A) - 1) / solve_waves<KIND>(A)));
+    const bool through = !packs<KIND>(A, (int64_t)A.n_sets * A.width * A.height);
     const int base = (blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6)) * per_wave;
     if (base >= n_in) return;
     const int k = base + lane / 3;
@@ -718,7 +725,7 @@ __global__ __launch_bounds__(256) void k_illum_solve(rti::IllumArgs A, const flo
         T = __shfl(T, src);
         const int ended = __popcll(ballot(live && role == 0 && next == 0));
         live = live && next != 0;
-        if (packs<KIND>(n_in)) {
+        if (packs<KIND>(A, n_in)) {
             if (live && role == 0) {
                 A.w_al[pix] = al;
                 A.w_be[pix] = be;
@@ -735,7 +742,7 @@ __global__ __launch_bounds__(256) void k_illum_solve(rti::IllumArgs A, const flo
                 left = n_in - ended -
                        (ended ? atomicAdd(done, ended) : __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
             }
-            if (uniform_i(left) <= ROWS_MAX) {
+            if (uniform_i(left) <= rows_max(A)) {
                 if (live && role == 0) {
                     A.w_al[pix] = al;
                     A.w_be[pix] = be;
@@ -752,7 +759,7 @@ __global__ __launch_bounds__(256) void k_illum_solve(rti::IllumArgs A, const flo
     }
 }
 
-// The pixels of a list of up to ROWS_MAX, or those that k_illum_solve handed
+// The pixels of a list of up to rows_max, or those that k_illum_solve handed
 // over, to their end: one wave per pixel, its three shots on three rows of 16
 // lanes (the fourth repeats the base), the bumps spread over the lanes of each
 // row.  What is left there are serial chains of up to 50 shots of hundreds of
@@ -763,9 +770,9 @@ __global__ __launch_bounds__(256) void k_illum_solve(rti::IllumArgs A, const flo
 template <int NB, bool ONE>
 __global__ __launch_bounds__(64) void k_illum_rows(rti::IllumArgs A, const float4 *__restrict__ BF, int it) {
     const int n_in = A.ctr[it];
-    if (n_in > SHORT_LIST) return;
-    const bool whole = n_in <= ROWS_MAX;
-    const int n = whole ? n_in : min(A.ctr[3 * (A.max_iters + 1) + it], ROWS_MAX);
+    if (n_in > short_list(A)) return;
+    const bool whole = n_in <= rows_max(A);
+    const int n = whole ? n_in : min(A.ctr[3 * (A.max_iters + 1) + it], rows_max(A));
     const int k = blockIdx.x;
     if (k >= n) return;
     const int lane = lane_id(), role = lane >> 4;
@@ -825,7 +832,7 @@ __global__ __launch_bounds__(256) void k_illum_iter(rti::IllumArgs A, const floa
     const int n_in = A.ctr[it];
     const uint64_t all = all_bumps(A.n_bumps);
     const V3<float> L = mk(A.light[0], A.light[1], A.light[2]);
-    if (solved && n_in <= SHORT_LIST) return;
+    if (solved && n_in <= short_list(A)) return;
     int *steps = A.list[2];
     for (int base = blockIdx.x * blockDim.x; base < n_in; base += gridDim.x * blockDim.x) {
         const int k = base + threadIdx.x;
@@ -1062,10 +1069,10 @@ __global__ __launch_bounds__(256) void k_illum_cont(rti::IllumArgs A, const floa
 
 template <int KIND, bool ONE>
 void illum_rounds(const rti::IllumArgs &a, const rti::DeviceData &d, int grid, hipStream_t s) {
-    const int sgrid = solve_blocks((int64_t)a.n_sets * a.width * a.height);
-    const int rgrid = (int)std::min<int64_t>((int64_t)a.n_sets * a.width * a.height, ROWS_MAX);
+    const int sgrid = solve_blocks(a, (int64_t)a.n_sets * a.width * a.height);
+    const int rgrid = (int)std::min<int64_t>((int64_t)a.n_sets * a.width * a.height, rows_max(a));
     const bool rows = KIND == KIND_GRAPH && a.n_bumps > 0 && a.n_bumps <= 32;
-    const bool packed = packs<KIND>((int64_t)a.n_sets * a.width * a.height);
+    const bool packed = packs<KIND>(a, (int64_t)a.n_sets * a.width * a.height);
     // one iteration's launches; solve: the pixels of a short list go to their end
     auto iteration = [&](const rti::IllumArgs &q, int it, bool solve) {
         if (solve) hipLaunchKernelGGL((k_illum_solve<KIND, ONE>), dim3(sgrid), dim3(256), 0, s, q, d.bump_f, it, rows);

@@ -184,6 +184,7 @@ struct IllumArgs {
     float twist_amp, twist_theta0;
     int n_spheres, n_planes, n_tori;
     int width, height;
+    int n_cu;          // compute units: the lines between the launches count waves
     const float *hit;  // traced hit points [n_sets * H * W][3]
     const int *id;     // traced object ids
     float light[3];
