@@ -461,7 +461,8 @@ rt_status rt_mlp_fwd(rt_ctx *ctx, int n_nets, int batch, const uint16_t *w_bf16,
  * runs on its crossings): network g maps rows [off_g, off_g + rows[g]) of
  * x [sum rows][6] to y [sum rows][6], off_g = rows[0] + ... + rows[g-1].
  * rows is a host array [n_nets], n_nets <= 64; same rounding points as
- * rt_mlp_fwd. */
+ * rt_mlp_fwd.  Uses a buffer of the context, which a call on another stream
+ * waits for; a stream that is being captured is refused (RT_EUNSUPPORTED). */
 rt_status rt_mlp_fwd_grouped(rt_ctx *ctx, int n_nets, const int32_t *rows, const uint16_t *w_bf16,
                              const float *params, const float *x, float *y, void *hip_stream);
 

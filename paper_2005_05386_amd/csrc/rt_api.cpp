@@ -83,6 +83,8 @@ struct rt_ctx {
     int surr_eligible = 0;
     void *d_grp_ws = nullptr;          // split weights of rt_mlp_fwd_grouped
     size_t grp_ws_bytes = 0;
+    hipStream_t grp_stream = nullptr;  // the stream of the call that used it last
+    bool grp_used = false;
     void *d_xbuf = nullptr;            // crossing queues, sized for xbuf_cap rays
     int64_t xbuf_cap = 0;
     void *d_ibuf = nullptr;            // illumination workspace, sized for ibuf_cap pixels
@@ -1239,12 +1241,25 @@ rt_status rt_mlp_fwd_grouped(rt_ctx *c, int n_nets, const int32_t *rows, const u
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return hip_fail(c, e, "hipSetDevice");
     if (tiles == 0) return RT_OK;
+    if (stream) {
+        // a replay would use the context's buffer whatever calls came between
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if ((e = hipStreamIsCapturing((hipStream_t)stream, &cs)) != hipSuccess)
+            return hip_fail(c, e, "hipStreamIsCapturing");
+        if (cs != hipStreamCaptureStatusNone)
+            return fail(c, RT_EUNSUPPORTED, "rt_mlp_fwd_grouped: the stream is being captured");
+    }
     // the context's buffer for the split weights: calls on one stream take
-    // turns on it, a call on another stream waits for the last one
+    // turns on it; a call on another stream, or one that frees it to take a
+    // larger one, waits for the call that used it last (whatever the context
+    // did on other streams since)
     const size_t need = (size_t)n_nets * rti::MLP_WSPLIT * 2;
-    if (c->last_stream != (hipStream_t)stream || c->grp_ws_bytes < need) {
-        rt_status st = sync_last(c);
-        if (st != RT_OK) return st;
+    if (c->grp_used && (c->grp_stream != (hipStream_t)stream || c->grp_ws_bytes < need)) {
+        if (hipStreamSynchronize(c->grp_stream) != hipSuccess) {  // (a stream destroyed since)
+            (void)hipGetLastError();
+            if ((e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(c, e, "hipDeviceSynchronize (grouped mlp)");
+        }
+        c->grp_used = false;
     }
     if (c->grp_ws_bytes < need) {
         (void)hipFree(c->d_grp_ws);
@@ -1262,6 +1277,8 @@ rt_status rt_mlp_fwd_grouped(rt_ctx *c, int n_nets, const int32_t *rows, const u
     S.xout = y;
     int blocks = (int)std::min<int64_t>(tiles, 2 * (int64_t)c->n_cu);
     e = rti::launch_mlp_rows(ctl, S, blocks, (hipStream_t)stream);
+    c->grp_stream = (hipStream_t)stream;
+    c->grp_used = true;
     if (e != hipSuccess) return hip_fail(c, e, "kernel launch (grouped mlp)");
     c->last_stream = (hipStream_t)stream;
     c->traced = true;

@@ -340,3 +340,42 @@ def test_mse_summation_order(env, n):
     while s.shape[1] > 1:
         s = s[:, :s.shape[1] // 2] + s[:, s.shape[1] // 2:]
     assert np.array_equal(part.cpu().numpy(), s[:, 0])
+
+
+def test_grouped_forward_after_other_calls(env):
+    """A long grouped call on one stream, another entry point and then a grouped
+    call with other networks on a second stream: the second call waits for the
+    first, whose networks it would overwrite."""
+    rt, torch, tr = env
+    say("grouped forward, other calls between")
+    rng = np.random.default_rng(9)
+    (_, pa, wa), (_, pb, wb) = _params(torch, 8), _params(torch, 8, scale=0.5)
+    xa = torch.tensor(rng.normal(size=(800000, 6)).astype(np.float32), device="cuda")
+    xb = xa[:640].contiguous()
+    ra, rb = [100000] * 8, [80] * 8
+    alone = tr.mlp_fwd_grouped(wa, pa, xa, ra).clone(), tr.mlp_fwd_grouped(wb, pb, xb, rb).clone()
+    torch.cuda.synchronize()
+    s0, s1 = torch.cuda.Stream(), torch.cuda.Stream()
+    for _ in range(3):
+        with torch.cuda.stream(s0):
+            ya = tr.mlp_fwd_grouped(wa, pa, xa, ra)
+        with torch.cuda.stream(s1):
+            tr.surrogate_gen([1.0], [0.3], 64, 0.01)
+            yb = tr.mlp_fwd_grouped(wb, pb, xb, rb)
+        torch.cuda.synchronize()
+        assert torch.equal(ya, alone[0]) and torch.equal(yb, alone[1])
+
+
+def test_grouped_forward_refuses_capture(env):
+    """A graph would keep the address of the context's buffer."""
+    rt, torch, tr = env
+    say("grouped forward under capture")
+    _, pt, pb = _params(torch, 2)
+    x = torch.zeros((100, 6), device="cuda")
+    ref = tr.mlp_fwd_grouped(pb, pt, x, [50, 50]).clone()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(torch.cuda.CUDAGraph()):
+        x + 1.0
+        with pytest.raises(rt.RtError, match="captured"):
+            tr.mlp_fwd_grouped(pb, pt, x, [50, 50])
+    assert torch.equal(tr.mlp_fwd_grouped(pb, pt, x, [50, 50]), ref)
