@@ -449,7 +449,9 @@ rt_status rt_trace_bwd(rt_ctx *ctx, const void *tape, const float *grad_hit, flo
  * batch rows: x [n_nets][batch][6]. */
 #define RT_MLP_PARAMS 134918
 
-/* Bytes of device workspace for rt_mlp_fwd/rt_mlp_bwd at this size. */
+/* Bytes of device workspace for rt_mlp_fwd/rt_mlp_bwd at this size: about 4 KB
+ * for every row (each network's rows rounded up to 64) and 0.5 MB for every
+ * network up to 256. */
 size_t rt_mlp_work_bytes(int n_nets, int batch);
 
 /* y = MLP(x) per network; the workspace keeps the activations for a
@@ -467,7 +469,8 @@ rt_status rt_mlp_fwd_grouped(rt_ctx *ctx, int n_nets, const int32_t *rows, const
                              const float *params, const float *x, float *y, void *hip_stream);
 
 /* grad [n_nets][RT_MLP_PARAMS] = d/dparams of sum_rows dy . y, for the
- * activations stored in work by the last rt_mlp_fwd with the same weights.
+ * activations stored in work by the last rt_mlp_fwd with the same weights
+ * (the first layer's are formed again from params).
  * Reductions over rows run in a fixed order. */
 rt_status rt_mlp_bwd(rt_ctx *ctx, int n_nets, int batch, const uint16_t *w_bf16, const float *params, const float *dy,
                      float *grad, void *work, size_t work_bytes, void *hip_stream);

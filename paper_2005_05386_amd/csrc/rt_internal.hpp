@@ -131,7 +131,7 @@ struct TraceArgs {
 // Learned crossing stage run between passes.
 struct SurrArgs {
     int n_nets, n_tab, n_bins;
-    int64_t stride;       // parameters per network in wb / params (multiple of 8)
+    int64_t stride;       // parameters per network in params (RT_MLP_PARAMS: rows at 4-byte alignment)
     float tol;
     const __bf16 *wsplit; // [n_nets][MLP_WSPLIT] W2, W3 in two bf16 parts
     const float *params;  // [n_nets][stride]
@@ -227,15 +227,15 @@ constexpr int MLP_WSPLIT = 4 * 256 * 256;
 // Fill them (ws [n][MLP_WSPLIT], 16-byte aligned) from FP32 masters `stride` apart.
 void launch_wsplit(const float *params, int64_t stride, int n, __bf16 *ws, hipStream_t s);
 // Workspace of a forward pass kept for the backward: rows in whole tiles of
-// 64, T = tiles per network, Bp = 64 T.
+// 64, T = tiles per network, Bp = 64 T.  ws and wt hold the networks of one turn.
 struct MlpWork {
     float *xf;             // [n][Bp][6] inputs
     float *z2;             // [n][T] tiles of pre-activations of layer 2, accumulator order
     float *z3;             // [n][Bp][256] pre-activations of layer 3
     __bf16 *h1t, *h2t;     // [n][T][256][64] activations (bf16, high part)
     __bf16 *dz2t, *dz3t;   // [n][T][256][64] back-propagated signals
-    __bf16 *ws;            // [n] W2, W3 as two bf16 parts in the forward products' fragment order
-    __bf16 *wt;            // [n][2][256 * 256] W2, W3 in the backward products' fragment order
+    __bf16 *ws;            // W2, W3 as two bf16 parts in the forward products' fragment order
+    __bf16 *wt;            // [2][256 * 256] W2, W3 in the backward products' fragment order, in the room of ws
     float *part1, *part4;  // [n][ceil(B/32)][7][256] partial gradients of the FP32 layers
     float *cs2, *cs3;      // [n][T][256] partial bias gradients
 };
@@ -260,7 +260,7 @@ hipError_t launch_cross_cal(const float *X, const float *P, const float *Y, cons
 // Crossing stage after pass `pass`: group by network, fused MLP forward,
 // decode, probe, and jump or fall back.
 // Fused grouped MLP forward: ctl holds per-network row offsets at XC_ROW
-// and tile offsets at XC_TILE; uses S.wb, S.params, S.stride, S.n_nets,
+// and tile offsets at XC_TILE; uses S.wsplit, S.params, S.stride, S.n_nets,
 // S.xin, S.xout.
 // launch_mlp_rows fills S.wsplit from S.params first.
 struct GroupCtl {

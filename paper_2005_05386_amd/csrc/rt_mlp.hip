@@ -846,8 +846,13 @@ hipError_t launch_mse_grad(const float *y, const float *t, float *dy, int64_t n,
     return hipGetLastError();
 }
 
+// Networks whose re-laid weights the workspace holds at once (0.5 MB each; larger
+// calls take their networks in turns of this many).
+constexpr int MLP_TURN = 256;
+
 // Workspace of n networks of batch rows: the tiles are whole, their rows past
-// the batch hold the forward of zero inputs and zero signals.
+// the batch hold the forward of zero inputs and zero signals.  The forward's and
+// the backward's weights share their room: each pass lays them out first.
 template <class F> static void mlp_layout(int n, int batch, MlpWork &w, F take) {
     const size_t tiles = ((size_t)batch + TM - 1) / TM, nch = ((size_t)batch + GRAD_ROWS - 1) / GRAD_ROWS;
     const size_t rows = (size_t)n * tiles * TM;
@@ -858,8 +863,7 @@ template <class F> static void mlp_layout(int n, int batch, MlpWork &w, F take) 
     w.h2t = (__bf16 *)take(rows * MLP_H * 2);
     w.dz2t = (__bf16 *)take(rows * MLP_H * 2);
     w.dz3t = (__bf16 *)take(rows * MLP_H * 2);
-    w.ws = (__bf16 *)take((size_t)n * MLP_WSPLIT * 2);
-    w.wt = (__bf16 *)take((size_t)n * 2 * MLP_H * MLP_H * 2);
+    w.ws = w.wt = (__bf16 *)take((size_t)std::min(n, MLP_TURN) * MLP_WSPLIT * 2);
     w.part1 = (float *)take(n * nch * 7 * MLP_H * 4);
     w.part4 = (float *)take(n * nch * 7 * MLP_H * 4);
     w.cs2 = (float *)take(n * tiles * MLP_H * 4);
@@ -885,29 +889,58 @@ void mlp_work_carve(void *base, int n_nets, int batch, MlpWork &w) {
     });
 }
 
+// The workspace from network g on.
+static MlpWork from_net(MlpWork w, int64_t g, int B) {
+    const int64_t tiles = (B + TM - 1) / TM, nch = (B + GRAD_ROWS - 1) / GRAD_ROWS, e = g * tiles * TM * MLP_H;
+    w.xf += g * tiles * TM * MLP_IN;
+    w.z2 += e;
+    w.z3 += e;
+    w.h1t += e;
+    w.h2t += e;
+    w.dz2t += e;
+    w.dz3t += e;
+    w.part1 += g * nch * 7 * MLP_H;
+    w.part4 += g * nch * 7 * MLP_H;
+    w.cs2 += g * tiles * MLP_H;
+    w.cs3 += g * tiles * MLP_H;
+    return w;
+}
+
 void launch_wsplit(const float *params, int64_t stride, int n, __bf16 *ws, hipStream_t s) {
     hipLaunchKernelGGL(k_mlp_wsplit, dim3(64, n), dim3(256), 0, s, params, stride, ws);
 }
 
 // y = MLP(x) for n_nets networks of batch rows each, keeping what a backward
 // pass needs in the workspace.
-hipError_t mlp_forward(int n, int B, const float *params, const float *x, float *y, const MlpWork &w, hipStream_t s) {
-    launch_wsplit(params, MLP_P, n, w.ws, s);
-    hipLaunchKernelGGL(k_mlp_fwd, dim3(xcd_grid((B + TM - 1) / TM, 1, n)), dim3(NT), 0, s, params, x, y, n, B, w);
+hipError_t mlp_forward(int n, int B, const float *params, const float *x, float *y, const MlpWork &work, hipStream_t s) {
+    for (int64_t g = 0; g < n; g += MLP_TURN) {
+        const int m = (int)std::min<int64_t>(MLP_TURN, n - g);
+        const MlpWork w = from_net(work, g, B);
+        const float *p = params + g * MLP_P;
+        launch_wsplit(p, MLP_P, m, w.ws, s);
+        hipLaunchKernelGGL(k_mlp_fwd, dim3(xcd_grid((B + TM - 1) / TM, 1, m)), dim3(NT), 0, s, p, x + g * B * MLP_IN,
+                           y + g * B * MLP_OUT, m, B, w);
+    }
     return hipGetLastError();
 }
 
 // grad = dL/dparams given dy = dL/dy, using the workspace of the last forward.
 hipError_t mlp_backward(int n, int B, const __bf16 *wb, const float *params, const float *dy, float *grad,
-                        const MlpWork &w, hipStream_t s) {
+                        const MlpWork &work, hipStream_t s) {
     const int tiles = (B + TM - 1) / TM;
-    hipLaunchKernelGGL(k_mlp_wfrag, dim3(8, n), dim3(256), 0, s, wb, w.wt);
-    hipLaunchKernelGGL(k_mlp_bwd, dim3(xcd_grid(tiles, 1, n)), dim3(NT), 0, s, params, dy, n, B, w);
-    if (B % 128 == 0)
-        hipLaunchKernelGGL(k_mlp_wgrad, dim3(xcd_grid(4, 4, 2 * n)), dim3(256), 0, s, n, tiles, w, grad);
-    else
-        hipLaunchKernelGGL(k_mlp_wgrad_rows, dim3(xcd_grid(4, 4, 2 * n)), dim3(256), 0, s, n, tiles, w, grad);
-    hipLaunchKernelGGL(k_mlp_sums, dim3(16, n), dim3(256), 0, s, B, w, grad);
+    for (int64_t g = 0; g < n; g += MLP_TURN) {
+        const int m = (int)std::min<int64_t>(MLP_TURN, n - g);
+        const MlpWork w = from_net(work, g, B);
+        float *G = grad + g * MLP_P;
+        hipLaunchKernelGGL(k_mlp_wfrag, dim3(8, m), dim3(256), 0, s, wb + g * MLP_P, w.wt);
+        hipLaunchKernelGGL(k_mlp_bwd, dim3(xcd_grid(tiles, 1, m)), dim3(NT), 0, s, params + g * MLP_P,
+                           dy + g * B * MLP_OUT, m, B, w);
+        if (B % 128 == 0)
+            hipLaunchKernelGGL(k_mlp_wgrad, dim3(xcd_grid(4, 4, 2 * m)), dim3(256), 0, s, m, tiles, w, G);
+        else
+            hipLaunchKernelGGL(k_mlp_wgrad_rows, dim3(xcd_grid(4, 4, 2 * m)), dim3(256), 0, s, m, tiles, w, G);
+        hipLaunchKernelGGL(k_mlp_sums, dim3(16, m), dim3(256), 0, s, B, w, G);
+    }
     return hipGetLastError();
 }
 

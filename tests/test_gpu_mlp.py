@@ -379,3 +379,25 @@ def test_grouped_forward_refuses_capture(env):
         with pytest.raises(rt.RtError, match="captured"):
             tr.mlp_fwd_grouped(pb, pt, x, [50, 50])
     assert torch.equal(tr.mlp_fwd_grouped(pb, pt, x, [50, 50]), ref)
+
+
+def test_many_small_networks(env):
+    """More networks than the workspace holds re-laid weights for: the same as
+    the networks by themselves, at a few hundred KB a network."""
+    rt, torch, tr = env
+    n, batch = 515, 3
+    say("mlp n_nets=%d batch=%d" % (n, batch))
+    assert tr.mlp_work(1, 1).numel() * 4 < 1.0e6
+    assert rt._lib.rt_mlp_work_bytes(4096, 1) < 1.3e9
+    rng = np.random.default_rng(3)
+    pt = torch.tensor(rng.normal(0.0, 0.06, (n, mlp.N_PARAMS)).astype(np.float32), device="cuda")
+    pb = pt.to(torch.bfloat16)
+    x = torch.tensor(rng.normal(size=(n, batch, 6)).astype(np.float32), device="cuda")
+    dy = torch.tensor(rng.normal(size=(n, batch, 6)).astype(np.float32), device="cuda")
+    work = tr.mlp_work(n, batch)
+    y = tr.mlp_fwd(pb, pt, x, work)
+    g = tr.mlp_bwd(pb, pt, dy, work)
+    for a, b in ((0, 3), (254, 259), (510, 515)):
+        w1 = tr.mlp_work(b - a, batch)
+        assert torch.equal(tr.mlp_fwd(pb[a:b], pt[a:b], x[a:b], w1), y[a:b])
+        assert torch.equal(tr.mlp_bwd(pb[a:b], pt[a:b], dy[a:b], w1), g[a:b])
