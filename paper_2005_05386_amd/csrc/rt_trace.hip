@@ -871,14 +871,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LAT ? RT_LA
                             const float rem = t_lim - ((float)steps * A.h + (th + tl));
                             hstep = rem < A.h * (1.0f - 1e-5f) ? fmaxf(rem, 0.f) : A.h;
                         }
-                        if (FREE && KIND != KIND_EUCLID && bmask == 0) {
-                            // objects but no bump in the window: the same free step
-                            dx = free_step<STEP>(y, A.h);
-                            dv = mk(0.f, 0.f, 0.f);
-                            ok = true;
-                        } else {
-                            ok = step_rk4<float>(acc, p, y, hstep, dx, dv);
-                        }
+                        ok = step_rk4<float>(acc, p, y, hstep, dx, dv);
                     } else {
                         ok = step_euler<float>(acc, p, y, A.h, dx, dv);
                     }
