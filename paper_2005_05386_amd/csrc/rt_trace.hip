@@ -263,8 +263,20 @@ __device__ __forceinline__ void chord_scan(const uint64_t sm[4], uint64_t om, in
 // A lane that ends by a miss or a failure while marching writes its output
 // only once its box is cleared.  Windows and object lists only bound the
 // work, so the outputs equal the plain kernel's bit for bit.
-template <int KIND, int STEP, bool COUNT, bool SURR = false, bool TAPE = false, bool BATCH = false, bool LAT = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LAT ? RT_LAT_WAVES : STEP == STEP_RK45 || KIND == KIND_DEFORM_ROT ? 6 : (BATCH ? RT_BATCH_WAVES : (KIND == KIND_GRAPH && !SURR ? RT_GRAPH_WAVES : (KIND == KIND_TWIST ? RT_TWIST_WAVES : RT_PASS_WAVES))), 8))) void k_trace_pass(TraceArgs A, int pass, const float4 *__restrict__ BF,
+// FLY: free flight.  Adaptive traces of more than FLY_DEFORMS deformations do
+// without: there its block keeps some 35 more scalars alive, which spill to vector
+// registers inside the step loop, and few windows are empty (1280x720, RK45, with and
+// without: 16 deformations 14.6-19.5 and 13.5-18.0 ms, 12 7.3-12.8 and 7.3-11.5, 8
+// 5.1-6.5 and 5.9-6.8, 2 2.5-3.0 and 4.6-4.9).
+constexpr int FLY_DEFORMS = 8;
+constexpr bool few_fly(int kind, int step) { return is_deform(kind) && step == STEP_RK45; }
+// Waves per SIMD a pass kernel is compiled for (adaptive steps: 6; flying between
+// deformations 7.2 and 7.6 ms at 5 and 6 for nine of them, rotating ones 8.3 and 9.0
+// flying, 15.7 and 17.4 for sixteen not flying).
+constexpr int rk45_waves(int kind, bool fly) { return few_fly(kind, STEP_RK45) && (fly || kind == KIND_DEFORM_ROT) ? 5 : 6; }
+template <int KIND, int STEP, bool COUNT, bool SURR = false, bool TAPE = false, bool BATCH = false, bool LAT = false,
+          bool FLY = true>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LAT ? RT_LAT_WAVES : STEP == STEP_RK45 ? rk45_waves(KIND, FLY && !COUNT) : KIND == KIND_DEFORM_ROT ? 6 : (BATCH ? RT_BATCH_WAVES : (KIND == KIND_GRAPH && !SURR ? RT_GRAPH_WAVES : (KIND == KIND_TWIST ? RT_TWIST_WAVES : RT_PASS_WAVES))), 8))) void k_trace_pass(TraceArgs A, int pass, const float4 *__restrict__ BF,
                                                     const float4 *__restrict__ SPH,
                                                     const float4 *__restrict__ PLN,
                                                     const float *__restrict__ TOR) {
@@ -284,7 +296,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LAT ? RT_LA
     }
     int groups = 0;  // LIST: its groups
     constexpr bool TIGHT = STEP != STEP_RK45 && !COUNT && !SURR && !BATCH;
-    constexpr bool FLAT = flat_outside(KIND) && !COUNT && !SURR && !BATCH;
+    constexpr bool FLAT = FLY && flat_outside(KIND) && !COUNT && !SURR && !BATCH;
     constexpr bool FREE = FLAT || (KIND == KIND_TWIST && STEP != STEP_RK45 && !COUNT && !SURR && !BATCH);
     const int lane = lane_id();
     const int xcd0 = blockIdx.x % N_XCD;
@@ -1421,6 +1433,13 @@ hipError_t launch_pass(const TraceArgs &a, const rti::DeviceData &d, int p, int 
                                d.pln_f, d.tor_f);
         if (!a.count && a.lat_chunks > 0 && chunks <= a.lat_chunks) return hipGetLastError();
     }
+    if constexpr (few_fly(KIND, STEP) && !SURR && !TAPE) {
+        if (!a.count && a.n_bumps > FLY_DEFORMS) {
+            hipLaunchKernelGGL((k_trace_pass<KIND, STEP, false, false, false, false, false, false>), dim3(grid), dim3(256),
+                               0, s, a, p, d.bump_f, d.sph_f, d.pln_f, d.tor_f);
+            return hipGetLastError();
+        }
+    }
     if (a.count)
         hipLaunchKernelGGL((k_trace_pass<KIND, STEP, true, SURR, TAPE>), dim3(grid), dim3(256), 0, s, a, p,
                            d.bump_f, d.sph_f, d.pln_f, d.tor_f);
@@ -1479,7 +1498,10 @@ hipError_t launch_kind_step(const TraceArgs &a, const rti::DeviceData &d, int n_
 
 template <int KIND, int STEP> int occ() {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_trace_pass<KIND, STEP, false>, 256, 0) != hipSuccess)
+    // (of the flying and the other variant, the one that more blocks fit)
+    constexpr bool fly = !few_fly(KIND, STEP);
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &n, k_trace_pass<KIND, STEP, false, false, false, false, false, fly>, 256, 0) != hipSuccess)
         return 1;
     return n > 0 ? n : 1;
 }

@@ -174,3 +174,13 @@ def test_flight_of_rays_off_unit_speed(rt, rule, bump):
     far = g["id"] >= 2  # a plane: its distance from the bump over the time from there
     speed = np.linalg.norm(g["hit"][far], axis=1) / (g["t"][far] - 10.0 * bump[4])
     assert (speed > 1.025).any()
+
+
+@pytest.mark.parametrize("name", ["deform16_1080p", "rdeform16_1080p"])
+@pytest.mark.parametrize("n", [1, 8, 9, 16])
+def test_adaptive_trace_of_deformations(rt, name, n):
+    """Up to eight deformations fly free under adaptive steps, more do not."""
+    print("[gpu-case] adaptive steps", name, n, flush=True)
+    wl = W.with_size(W.get(name), 200, 113)
+    wl["metric"] = dict(wl["metric"], deforms=wl["metric"]["deforms"][:, :n])
+    same(rt, wl, dict(wl["rule"], kind=W.RK45, h_max=0.02, pass_steps=128))
