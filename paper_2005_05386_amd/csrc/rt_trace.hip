@@ -592,7 +592,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LAT ? RT_LA
                             // The twist is free only beyond its ball, and only if no
                             // velocity component is too small to absorb its acceleration.
                             const bool empty = ((FLAT && KIND != KIND_EUCLID ? bmask : 0ull) | sm[0] | sm[1] | sm[2] | sm[3] | omask) == 0;
-                            if (empty && (FLAT || ballot(act && !(fminf(fabsf(y.x), fabsf(y.y)) >= TWIST_MIN_V)) == 0)) {
+                            if (empty && (FLAT || (box_dist2(0.f, 0.f, 0.f, pmn, pmx) > TWIST_FREE * TWIST_FREE &&
+                                                   ballot(act && !(fminf(fabsf(y.x), fabsf(y.y)) >= TWIST_MIN_V)) == 0))) {
                                 const float D = free_distance<KIND>(A, Bs, SPH, PLN, TOR, lane, pmn, pmx);
                                 const float v = sqrt_(wave_max(act ? dot(y, y) : 0.f)) * 1.0001f;
                                 const float q = (D - 2e-4f) * rcp_(fmaxf(v, 1e-3f) * A.h_max) - 2.0f;
