@@ -595,8 +595,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LAT ? RT_LA
                             if (empty && (FLAT || (box_dist2(0.f, 0.f, 0.f, pmn, pmx) > TWIST_FREE * TWIST_FREE &&
                                                    ballot(act && !(fminf(fabsf(y.x), fabsf(y.y)) >= TWIST_MIN_V)) == 0))) {
                                 const float D = free_distance<KIND>(A, Bs, SPH, PLN, TOR, lane, pmn, pmx);
-                                const float v = sqrt_(wave_max(act ? dot(y, y) : 0.f)) * 1.0001f;
-                                const float q = (D - 2e-4f) * rcp_(fmaxf(v, 1e-3f) * A.h_max) - 2.0f;
+                                const float v2 = act ? dot(y, y) : 0.f;
+                                float v = 1.001f;
+                                if (ballot(v2 > 1.0f)) v = sqrt_(wave_max(v2)) * 1.0001f;
+                                const float q = (D - 2e-4f) * rcp_(v * A.h_max) - 2.0f;
                                 n_free = (int)fminf(fmaxf(q, 0.f), 1e6f);
                                 // (an empty window was found empty by its own bound)
                                 if constexpr (FLAT) n_free = max(n_free, A.K);
