@@ -965,12 +965,20 @@ static rt_status trace_impl(rt_ctx *c, const rt_camera *cam, const rt_step_rule 
         int v = std::atoi(g);
         if (v >= 1) grid = v;
     }
-    // Passes of at most three waves per SIMD run the small-launch variant: its
-    // registers allow four, and the variants meet between two and four (with
-    // the line at 0 / 2 / 4: 721x403 anisotropic bumps 19.2 / 18.1 / 18.4 ms,
-    // 473x458 twist 6.7 / 6.0 / 6.1, 679x676 quadric 3.02 / 3.04 / 2.95).
+    // Passes of few waves per SIMD run the small-launch variant.  Its registers
+    // allow four at a time; up to ten, in two or three rounds, its shorter steps
+    // still win where a step is long (in ms, the other variant first: 25 bumps
+    // 640x480 7.4-9.1 and 5.8-7.2, 900x600 8.0-10.1 and 7.5-8.2; 48 bumps 900x600
+    // 14.9-17.4 and 12.0-15.0; 14 deformations 4.5-4.8 and 4.1-4.4; twist 6.2 and
+    // 5.7), beyond that the other one (25 bumps 1000x700 6.4-9.6 and 7.7-9.3).  With
+    // fewer than 20 bumps the variants meet between two and four (721x403, 12
+    // anisotropic bumps, the line at 0 / 2 / 4: 19.2 / 18.1 / 18.4 ms; 640x480 1.9-2.2
+    // and 2.1-2.4, 16 bumps 2.2-3.4 and 2.4-3.1).
     a.lat_chunks = 0;
-    if (rti::has_small_variant(a.kind, r->kind) && !a.count && !a.batch && !use_surr) a.lat_chunks = c->n_cu * 4 * 3;
+    if (rti::has_small_variant(a.kind, r->kind) && !a.count && !a.batch && !use_surr) {
+        const bool bumps = c->kind == RT_METRIC_GRAPH_GAUSS || c->kind == RT_METRIC_GRAPH_ANISO;
+        a.lat_chunks = c->n_cu * 4 * (bumps && c->n_bumps <= 19 ? 3 : 10);
+    }
     hipStream_t s = (hipStream_t)stream;
     bool timed = (r->flags & RT_FLAG_TIMING) != 0;
     if (timed) {

@@ -241,7 +241,7 @@ __device__ __forceinline__ void chord_scan(const uint64_t sm[4], uint64_t om, in
 #define RT_LAT_WAVES 4  // the same for the small-launch variant
 #endif
 // LAT: the variant for passes of few chunks (fixed steps; at most
-// lat_chunks, three waves per SIMD).  A wave alone on its SIMD
+// lat_chunks, see the line's rule where it is set).  A wave alone on its SIMD
 // issues a vector instruction every 5 to 6 cycles and waits out every scalar
 // load, so what counts is the length of its own instruction stream: one or two
 // listed bumps stay in registers for the whole window, more are read from the
@@ -274,8 +274,16 @@ constexpr bool few_fly(int kind, int step) { return is_deform(kind) && step == S
 // deformations 7.2 and 7.6 ms at 5 and 6 for nine of them, rotating ones 8.3 and 9.0
 // flying, 15.7 and 17.4 for sixteen not flying).
 constexpr int rk45_waves(int kind, bool fly) { return few_fly(kind, STEP_RK45) && (fly || kind == KIND_DEFORM_ROT) ? 5 : 6; }
+// DENSE: isotropic tables of more than SPARSE_BUMPS.  Their windows list many
+// bumps, of which few hold the window in their cut: the walk that tests every cut
+// without asking (a select, no branch) is then faster from DENSE_WALK listed bumps
+// on (48 bumps 1280x720 16.8-20.5 and 15.6-18.8 ms, 25 bumps 9.1-10.4 and 8.2-9.4, 20
+// bumps 1000x700 4.1-8.3 and 4.1-7.6), while tables that seldom list so many pay for
+// two loops (16 bumps 1920x1080 6.2-6.6 and 6.6-6.8, 17 bumps 7.2-8.8 and 7.5-8.8).
+constexpr int SPARSE_BUMPS = 19, DENSE_WALK = 8;
+constexpr bool has_dense(int kind, int step) { return kind == KIND_GRAPH && step != STEP_RK45; }
 template <int KIND, int STEP, bool COUNT, bool SURR = false, bool TAPE = false, bool BATCH = false, bool LAT = false,
-          bool FLY = true>
+          bool FLY = true, bool DENSE = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LAT ? RT_LAT_WAVES : STEP == STEP_RK45 ? rk45_waves(KIND, FLY && !COUNT) : KIND == KIND_DEFORM_ROT ? 6 : (BATCH ? RT_BATCH_WAVES : (KIND == KIND_GRAPH && !SURR ? RT_GRAPH_WAVES : (KIND == KIND_TWIST ? RT_TWIST_WAVES : RT_PASS_WAVES))), 8))) void k_trace_pass(TraceArgs A, int pass, const float4 *__restrict__ BF,
                                                     const float4 *__restrict__ SPH,
                                                     const float4 *__restrict__ PLN,
@@ -789,9 +797,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LAT ? RT_LA
                             if (nb == 1) march(HeldAcc<AN, 1>(Bs, bmask));
                             else if (nb == 2) march(HeldAcc<AN, 2>(Bs, bmask));
                             else march(ListAcc<AN>{list, groups});
-                        } else if constexpr (KIND == KIND_GRAPH) {
+                        } else if (KIND == KIND_GRAPH && !(DENSE && __popcll(bmask) > DENSE_WALK)) {
                             march(GraphWalk{Bs, bmask, cutm});
-                        } else {
+                        } else if (KIND != KIND_GRAPH || DENSE) {
                             march(Acc32<KIND, false, true>{Bs, bmask, A.twist_amp, A.twist_theta0, nullptr, nullptr});
                         }
                         steps += j;
@@ -1440,6 +1448,13 @@ hipError_t launch_pass(const TraceArgs &a, const rti::DeviceData &d, int p, int 
         if (!a.count && a.n_bumps > FLY_DEFORMS) {
             hipLaunchKernelGGL((k_trace_pass<KIND, STEP, false, false, false, false, false, false>), dim3(grid), dim3(256),
                                0, s, a, p, d.bump_f, d.sph_f, d.pln_f, d.tor_f);
+            return hipGetLastError();
+        }
+    }
+    if constexpr (has_dense(KIND, STEP) && !SURR && !TAPE) {
+        if (!a.count && a.n_bumps > SPARSE_BUMPS) {
+            hipLaunchKernelGGL((k_trace_pass<KIND, STEP, false, false, false, false, false, true, true>), dim3(grid),
+                               dim3(256), 0, s, a, p, d.bump_f, d.sph_f, d.pln_f, d.tor_f);
             return hipGetLastError();
         }
     }

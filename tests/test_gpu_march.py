@@ -184,3 +184,15 @@ def test_adaptive_trace_of_deformations(rt, name, n):
     wl = W.with_size(W.get(name), 200, 113)
     wl["metric"] = dict(wl["metric"], deforms=wl["metric"]["deforms"][:, :n])
     same(rt, wl, dict(wl["rule"], kind=W.RK45, h_max=0.02, pass_steps=128))
+
+
+@pytest.mark.parametrize("n,size", [(19, (512, 384)), (19, (520, 384)), (20, (520, 384)), (20, (1024, 640)),
+                                    (20, (1032, 640)), (64, (1032, 640))])
+def test_lines_by_table_size(rt, n, size):
+    """On 256 CUs tables of up to 19 bumps run the small-launch variant up to 3072
+    chunks, longer ones up to 10240 and beyond that the walk for dense tables."""
+    print("[gpu-case] lines by table size", n, size, flush=True)
+    wl = W.with_size(W.get("bumps16_1080p"), *size)
+    wl["metric"] = W.metric(W.GRAPH_GAUSS, bumps=W.random_bumps(n, 40 + n))
+    for kind in (W.RK4, W.EULER):
+        same(rt, wl, dict(wl["rule"], kind=kind, pass_steps=200, h=0.02, max_steps=600))
