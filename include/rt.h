@@ -450,8 +450,8 @@ rt_status rt_trace_bwd(rt_ctx *ctx, const void *tape, const float *grad_hit, flo
 #define RT_MLP_PARAMS 134918
 
 /* Bytes of device workspace for rt_mlp_fwd/rt_mlp_bwd at this size: about 4 KB
- * for every row (each network's rows rounded up to 64) and 0.5 MB for every
- * network up to 256. */
+ * for every row (each network's rows rounded up to 64) and, for batches of more
+ * than 64 rows, 0.5 MB for every network up to 256. */
 size_t rt_mlp_work_bytes(int n_nets, int batch);
 
 /* y = MLP(x) per network; the workspace keeps the activations for a

@@ -124,6 +124,14 @@ template <int N, class Z> __device__ __forceinline__ void times_dsilu(const Z &z
 // once per call instead of by every tile, and a fragment is one contiguous
 // kilobyte; rows of the master are a kilobyte apart, which spreads a load of
 // sixteen of them over four of L2's sixteen channels.
+__device__ __forceinline__ void split8(f32x4 u0, f32x4 u1, bf16x8 &hi, bf16x8 &lo) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float v = e < 4 ? u0[e & 3] : u1[e & 3];
+        hi[e] = (__bf16)v;
+        lo[e] = (__bf16)(v - (float)hi[e]);
+    }
+}
 constexpr int WSPLIT = rti::MLP_WSPLIT;
 __global__ __launch_bounds__(256) void k_mlp_wsplit(const float *__restrict__ params, int64_t stride,
                                                     __bf16 *__restrict__ ws) {
@@ -131,14 +139,8 @@ __global__ __launch_bounds__(256) void k_mlp_wsplit(const float *__restrict__ pa
     const int l = t >> 13, f = t & 8191, lane = f & 63;
     const int n = (f >> 9) * 16 + (lane & 15), k = ((f >> 6) & 7) * 32 + (lane >> 4) * 8;
     const float *src = params + (int64_t)g * stride + (l == 0 ? rti::OFF_W2 : rti::OFF_W3) + n * H + k;
-    const f32x4u u0 = *(const f32x4u *)src, u1 = *(const f32x4u *)(src + 4);
     bf16x8 hi, lo;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const float v = e < 4 ? u0[e & 3] : u1[e & 3];
-        hi[e] = (__bf16)v;
-        lo[e] = (__bf16)(v - (float)hi[e]);
-    }
+    split8(*(const f32x4u *)src, *(const f32x4u *)(src + 4), hi, lo);
     __bf16 *dst = ws + (int64_t)g * WSPLIT + (int64_t)l * 2 * H * H + f * 8;
     *(bf16x8 *)dst = hi;
     *(bf16x8 *)(dst + H * H) = lo;
@@ -182,7 +184,9 @@ struct KeepTile {
 // a CU, so one's vector work runs under the other's products (64 networks x
 // 1024 rows: 110 us; with four waves of 64 columns, two per SIMD, 125 against
 // 112 with these before the weights were split once and the quotients exact).
-template <bool KEEP>
+// DIRECT: the weights are read from the FP32 master and split by the tile, for
+// networks of a single tile, whose split would be written and read back once.
+template <bool KEEP, bool DIRECT = false>
 __device__ __forceinline__ void forward_tile(char *smem, float (*Xs)[6], const float *__restrict__ Pg,
                                              const __bf16 *__restrict__ Wg, const float *__restrict__ X, float *__restrict__ Y, int M,
                                              const KeepTile &K) {
@@ -232,6 +236,7 @@ __device__ __forceinline__ void forward_tile(char *smem, float (*Xs)[6], const f
 #pragma unroll 1
     for (int l = 0; l < 2; ++l) {
         const __bf16 *__restrict__ W = Wg + l * 2 * H * H + (wave * 2 * 8 * 64 + lane) * 8;
+        const float *__restrict__ Wf = Pg + (l == 0 ? rti::OFF_W2 : rti::OFF_W3) + (wave * 32 + col) * H + kq;
         const float *__restrict__ bias = Pg + (l == 0 ? rti::OFF_B2 : rti::OFF_B3) + wave * 32 + col;
         f32x4 acc[4][2];
 #pragma unroll
@@ -239,11 +244,18 @@ __device__ __forceinline__ void forward_tile(char *smem, float (*Xs)[6], const f
 #pragma unroll
             for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         bf16x8 nh[2], nl[2];
+        f32x4 nf[2][2];
         auto load = [&](int k) {
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                nh[j] = *(const bf16x8 *)(W + (j * 8 + k) * 64 * 8);
-                nl[j] = *(const bf16x8 *)(W + (j * 8 + k) * 64 * 8 + H * H);
+                if constexpr (DIRECT) {
+                    const float *src = Wf + 16 * j * H + 32 * k;
+                    nf[j][0] = *(const f32x4u *)src;
+                    nf[j][1] = *(const f32x4u *)(src + 4);
+                } else {
+                    nh[j] = *(const bf16x8 *)(W + (j * 8 + k) * 64 * 8);
+                    nl[j] = *(const bf16x8 *)(W + (j * 8 + k) * 64 * 8 + H * H);
+                }
             }
         };
         load(0);
@@ -252,8 +264,12 @@ __device__ __forceinline__ void forward_tile(char *smem, float (*Xs)[6], const f
             bf16x8 bh[2], bl[2];
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                bh[j] = nh[j];
-                bl[j] = nl[j];
+                if constexpr (DIRECT) {
+                    split8(nf[j][0], nf[j][1], bh[j], bl[j]);
+                } else {
+                    bh[j] = nh[j];
+                    bl[j] = nl[j];
+                }
             }
             load(min(k0 / 32 + 1, 7));
 #pragma unroll
@@ -337,6 +353,7 @@ constexpr int TILE_LDS = 2 * TM * AROW * 2;  // both bf16 parts, or one FP32 til
 static_assert(TILE_LDS >= TM * FROW * 4, "FP32 tile exceeds the LDS block");
 
 // y = MLP(x) for n networks of B rows each, keeping what the backward needs.
+template <bool DIRECT>
 __global__ __launch_bounds__(NT, 4) void k_mlp_fwd(const float *__restrict__ params, const float *__restrict__ X,
                                                     float *__restrict__ Y, int n, int B, rti::MlpWork w) {
     __shared__ __attribute__((aligned(16))) char smem[TILE_LDS];
@@ -347,7 +364,7 @@ __global__ __launch_bounds__(NT, 4) void k_mlp_fwd(const float *__restrict__ par
     const int m0 = t * TM;
     const int64_t T = (int64_t)g * tiles + t;
     const KeepTile K{w.xf + T * TM * 6, w.z2 + T * TM * H, w.z3 + T * TM * H, w.h1t + T * TM * H, w.h2t + T * TM * H};
-    forward_tile<true>(smem, Xs, params + g * rti::MLP_P, w.ws + (int64_t)g * WSPLIT, X + ((int64_t)g * B + m0) * 6, Y + ((int64_t)g * B + m0) * 6,
+    forward_tile<true, DIRECT>(smem, Xs, params + g * rti::MLP_P, w.ws + (int64_t)g * WSPLIT, X + ((int64_t)g * B + m0) * 6, Y + ((int64_t)g * B + m0) * 6,
                        min(TM, B - m0), K);
 }
 
@@ -400,20 +417,29 @@ __global__ __launch_bounds__(256) void k_mlp_wfrag(const __bf16 *__restrict__ wb
     }
 }
 
-// acc = A W for the 64 rows of A in LDS and this wave's 32 columns.
-__device__ __forceinline__ void signal_product(const __bf16 (*A)[AROW], const __bf16 *__restrict__ frag, int wave,
+// acc = A W for the 64 rows of A in LDS and this wave's 32 columns; W as
+// fragments, or (DIRECT, for networks of a single tile) row by row as it is.
+template <bool DIRECT>
+__device__ __forceinline__ void signal_product(const __bf16 (*A)[AROW], const __bf16 *__restrict__ w, int wave,
                                                int lane, f32x4 acc[4][2]) {
     const int col = lane & 15, kq = (lane >> 4) * 8;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const __bf16 *__restrict__ W = frag + ((wave * 2) * 8 * 64 + lane) * 8;
+    const __bf16 *__restrict__ W = DIRECT ? w + kq * H + wave * 32 + col : w + ((wave * 2) * 8 * 64 + lane) * 8;
 #pragma unroll 2
     for (int k = 0; k < 8; ++k) {
         bf16x8 b[2];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) b[j] = *(const bf16x8 *)(W + (j * 8 + k) * 64 * 8);
+        for (int j = 0; j < 2; ++j) {
+            if constexpr (DIRECT) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) b[j][e] = W[(32 * k + e) * H + 16 * j];
+            } else {
+                b[j] = *(const bf16x8 *)(W + (j * 8 + k) * 64 * 8);
+            }
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const bf16x8 a = *(const bf16x8 *)&A[16 * i + col][32 * k + kq];
@@ -431,8 +457,9 @@ __device__ __forceinline__ void signal_product(const __bf16 (*A)[AROW], const __
 // the FP32 layers' weight-gradient partials in row order, and the column's
 // bf16 values, which are contiguous in the transposed signal matrices.
 // Bound by the 0.3 MB that a tile reads and writes and by the column walks.
-__global__ __launch_bounds__(NT, 4) void k_mlp_bwd(const float *__restrict__ params, const float *__restrict__ DY, int n,
-                                                   int B, rti::MlpWork w) {
+template <bool DIRECT>
+__global__ __launch_bounds__(NT, 4) void k_mlp_bwd(const float *__restrict__ params, const __bf16 *__restrict__ wb,
+                                                   const float *__restrict__ DY, int n, int B, rti::MlpWork w) {
     __shared__ __attribute__((aligned(16))) char smem[TILE_LDS];
     __shared__ float Xs[TM][6], Ds[TM][6], S0[H];
     __bf16(*A)[AROW] = reinterpret_cast<__bf16(*)[AROW]>(smem);
@@ -518,7 +545,8 @@ __global__ __launch_bounds__(NT, 4) void k_mlp_bwd(const float *__restrict__ par
     }
     // (column_sum's barrier: the tile of signals is complete)
     f32x4 acc[4][2];
-    signal_product(A, w.wt + ((int64_t)g * 2 + 1) * H * H, wave, lane, acc);
+    const __bf16 *__restrict__ wg = wb + g * rti::MLP_P;
+    signal_product<DIRECT>(A, DIRECT ? wg + rti::OFF_W3 : w.wt + ((int64_t)g * 2 + 1) * H * H, wave, lane, acc);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -553,7 +581,7 @@ __global__ __launch_bounds__(NT, 4) void k_mlp_bwd(const float *__restrict__ par
             for (int u = 0; u < 8; ++u) A[rh + 8 * q + u][c] = pk[q][u];
     }
     __syncthreads();
-    signal_product(A, w.wt + ((int64_t)g * 2) * H * H, wave, lane, acc);
+    signal_product<DIRECT>(A, DIRECT ? wg + rti::OFF_W2 : w.wt + ((int64_t)g * 2) * H * H, wave, lane, acc);
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
@@ -681,7 +709,7 @@ __global__ __launch_bounds__(256, 4) void k_mlp_wgrad(int n, int tiles, rti::Mlp
 // current ones are multiplied (37 networks x 1329 rows: 109 us with every wave
 // loading its own operands, 74 with these; the four quarters, which would
 // round differently, 68).
-__global__ __launch_bounds__(256, 4) void k_mlp_wgrad_rows(int n, int tiles, rti::MlpWork w, float *__restrict__ grad) {
+__global__ __launch_bounds__(256, 4) void k_mlp_wgrad_rows(int n, int tiles, int slices, rti::MlpWork w, float *__restrict__ grad) {
     __shared__ bf16x8 S[2][2][2][4][64];  // [buffer][slice of 32 rows][A or B][16 columns][lane]
     WgradTile t;
     if (!wgrad_tile(n, tiles, w, grad, t)) return;
@@ -694,8 +722,9 @@ __global__ __launch_bounds__(256, 4) void k_mlp_wgrad_rows(int n, int tiles, rti
         for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     // wave: slice wave >> 1 of operand wave & 1
     const __bf16 *__restrict__ src = (wave & 1 ? t.B : t.A) + (wave >> 1) * 32;
-    bf16x8 v[4];
+    bf16x8 v[4] = {};
     auto load = [&](int q) {
+        if (2 * q + (wave >> 1) >= slices) return;  // (padding rows alone: not multiplied)
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = *(const bf16x8 *)(src + (int64_t)q * TM * H + 16 * i * TM);
     };
@@ -720,21 +749,31 @@ __global__ __launch_bounds__(256, 4) void k_mlp_wgrad_rows(int n, int tiles, rti
         store(q + 1);
         load(min(q + 2, tiles - 1));
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int s = 0; s < 2; ++s) {
+            if (2 * q + s >= slices) break;
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s][i], b[s][j], acc[i][j], 0, 0, 0);
+        }
         __syncthreads();
     }
+    // the tile through LDS (free after the last barrier) to whole rows
+    float(*R)[68] = reinterpret_cast<float(*)[68]>(&S[0][0][0][0][0]);
+    static_assert(sizeof(S) >= 64 * 68 * sizeof(float), "output tile exceeds the staging block");
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                t.C[(int64_t)((wm + i) * 16 + 4 * (lane >> 4) + e) * H + (wn + j) * 16 + (lane & 15)] = acc[i][j][e];
+            for (int e = 0; e < 4; ++e) R[(wm + i) * 16 + 4 * (lane >> 4) + e][(wn + j) * 16 + (lane & 15)] = acc[i][j][e];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int r = q * 16 + (threadIdx.x >> 4), c = (threadIdx.x & 15) * 4;
+        *(f32x4u *)(t.C + (int64_t)r * H + c) = *(const f32x4 *)&R[r][c];
+    }
 }
 
 // Sums of the row partials in order: block (q, g) takes one of the 16 sums of
@@ -847,8 +886,12 @@ hipError_t launch_mse_grad(const float *y, const float *t, float *dy, int64_t n,
 }
 
 // Networks whose re-laid weights the workspace holds at once (0.5 MB each; larger
-// calls take their networks in turns of this many).
+// calls take their networks in turns of this many).  Networks of a single tile
+// need none, and go in one turn: their tiles read the weights as they are (forward
+// and backward of 2048 networks of 4 rows 0.75 + 1.19 ms with re-laid weights,
+// 0.41 + 0.67 as they are; 64 of 16 rows 0.054 + 0.070, and 0.047 + 0.059).
 constexpr int MLP_TURN = 256;
+static int networks_a_turn(int n, int batch) { return batch <= TM ? n : std::min(n, MLP_TURN); }
 
 // Workspace of n networks of batch rows: the tiles are whole, their rows past
 // the batch hold the forward of zero inputs and zero signals.  The forward's and
@@ -863,7 +906,7 @@ template <class F> static void mlp_layout(int n, int batch, MlpWork &w, F take) 
     w.h2t = (__bf16 *)take(rows * MLP_H * 2);
     w.dz2t = (__bf16 *)take(rows * MLP_H * 2);
     w.dz3t = (__bf16 *)take(rows * MLP_H * 2);
-    w.ws = w.wt = (__bf16 *)take((size_t)std::min(n, MLP_TURN) * MLP_WSPLIT * 2);
+    w.ws = w.wt = (__bf16 *)take(batch <= TM ? 0 : (size_t)networks_a_turn(n, batch) * MLP_WSPLIT * 2);
     w.part1 = (float *)take(n * nch * 7 * MLP_H * 4);
     w.part4 = (float *)take(n * nch * 7 * MLP_H * 4);
     w.cs2 = (float *)take(n * tiles * MLP_H * 4);
@@ -913,13 +956,20 @@ void launch_wsplit(const float *params, int64_t stride, int n, __bf16 *ws, hipSt
 // y = MLP(x) for n_nets networks of batch rows each, keeping what a backward
 // pass needs in the workspace.
 hipError_t mlp_forward(int n, int B, const float *params, const float *x, float *y, const MlpWork &work, hipStream_t s) {
-    for (int64_t g = 0; g < n; g += MLP_TURN) {
-        const int m = (int)std::min<int64_t>(MLP_TURN, n - g);
+    const int turn = networks_a_turn(n, B);
+    for (int64_t g = 0; g < n; g += turn) {
+        const int m = (int)std::min<int64_t>(turn, n - g);
         const MlpWork w = from_net(work, g, B);
         const float *p = params + g * MLP_P;
-        launch_wsplit(p, MLP_P, m, w.ws, s);
-        hipLaunchKernelGGL(k_mlp_fwd, dim3(xcd_grid((B + TM - 1) / TM, 1, m)), dim3(NT), 0, s, p, x + g * B * MLP_IN,
-                           y + g * B * MLP_OUT, m, B, w);
+        const float *xg = x + g * B * MLP_IN;
+        float *yg = y + g * B * MLP_OUT;
+        const dim3 grid(xcd_grid((B + TM - 1) / TM, 1, m));
+        if (B <= TM) {
+            hipLaunchKernelGGL(k_mlp_fwd<true>, grid, dim3(NT), 0, s, p, xg, yg, m, B, w);
+        } else {
+            launch_wsplit(p, MLP_P, m, w.ws, s);
+            hipLaunchKernelGGL(k_mlp_fwd<false>, grid, dim3(NT), 0, s, p, xg, yg, m, B, w);
+        }
     }
     return hipGetLastError();
 }
@@ -928,17 +978,24 @@ hipError_t mlp_forward(int n, int B, const float *params, const float *x, float 
 hipError_t mlp_backward(int n, int B, const __bf16 *wb, const float *params, const float *dy, float *grad,
                         const MlpWork &work, hipStream_t s) {
     const int tiles = (B + TM - 1) / TM;
-    for (int64_t g = 0; g < n; g += MLP_TURN) {
-        const int m = (int)std::min<int64_t>(MLP_TURN, n - g);
+    const int turn = networks_a_turn(n, B);
+    for (int64_t g = 0; g < n; g += turn) {
+        const int m = (int)std::min<int64_t>(turn, n - g);
         const MlpWork w = from_net(work, g, B);
         float *G = grad + g * MLP_P;
-        hipLaunchKernelGGL(k_mlp_wfrag, dim3(8, m), dim3(256), 0, s, wb + g * MLP_P, w.wt);
-        hipLaunchKernelGGL(k_mlp_bwd, dim3(xcd_grid(tiles, 1, m)), dim3(NT), 0, s, params + g * MLP_P,
-                           dy + g * B * MLP_OUT, m, B, w);
+        const float *p = params + g * MLP_P, *d = dy + g * B * MLP_OUT;
+        const __bf16 *b = wb + g * MLP_P;
+        const dim3 grid(xcd_grid(tiles, 1, m));
+        if (tiles == 1) {
+            hipLaunchKernelGGL(k_mlp_bwd<true>, grid, dim3(NT), 0, s, p, b, d, m, B, w);
+        } else {
+            hipLaunchKernelGGL(k_mlp_wfrag, dim3(8, m), dim3(256), 0, s, b, w.wt);
+            hipLaunchKernelGGL(k_mlp_bwd<false>, grid, dim3(NT), 0, s, p, b, d, m, B, w);
+        }
         if (B % 128 == 0)
             hipLaunchKernelGGL(k_mlp_wgrad, dim3(xcd_grid(4, 4, 2 * m)), dim3(256), 0, s, m, tiles, w, G);
         else
-            hipLaunchKernelGGL(k_mlp_wgrad_rows, dim3(xcd_grid(4, 4, 2 * m)), dim3(256), 0, s, m, tiles, w, G);
+            hipLaunchKernelGGL(k_mlp_wgrad_rows, dim3(xcd_grid(4, 4, 2 * m)), dim3(256), 0, s, m, tiles, (B + 31) / 32, w, G);
         hipLaunchKernelGGL(k_mlp_sums, dim3(16, m), dim3(256), 0, s, B, w, G);
     }
     return hipGetLastError();

@@ -381,13 +381,15 @@ def test_grouped_forward_refuses_capture(env):
     assert torch.equal(tr.mlp_fwd_grouped(pb, pt, x, [50, 50]), ref)
 
 
-def test_many_small_networks(env):
-    """More networks than the workspace holds re-laid weights for: the same as
-    the networks by themselves, at a few hundred KB a network."""
+@pytest.mark.parametrize("batch", [3, 64, 66])
+def test_many_small_networks(env, batch):
+    """More networks than the workspace holds re-laid weights for, of one tile
+    (which need none) and of two: the same as the networks by themselves, at a few
+    hundred KB a network."""
     rt, torch, tr = env
-    n, batch = 515, 3
+    n = 515
     say("mlp n_nets=%d batch=%d" % (n, batch))
-    assert tr.mlp_work(1, 1).numel() * 4 < 1.0e6
+    assert rt._lib.rt_mlp_work_bytes(1, 1) < 1.0e6
     assert rt._lib.rt_mlp_work_bytes(4096, 1) < 1.3e9
     rng = np.random.default_rng(3)
     pt = torch.tensor(rng.normal(0.0, 0.06, (n, mlp.N_PARAMS)).astype(np.float32), device="cuda")
