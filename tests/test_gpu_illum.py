@@ -313,3 +313,19 @@ def test_packed_lists(rt):
     wl = W.with_size(W.get("quadric_1080p"), 200, 160)
     tra, sh = _run(rt, wl)
     _check_found(wl, tra, sh, 0.9, sample=400)
+
+
+def test_tiled_lists_equal_strips(rt):
+    """Frames of more than 172032 pixels list them in 8x8 tiles, smaller ones in
+    strips: three parameter sets of a frame with ragged sides, 177870 pixels in
+    one call, against the sets one by one."""
+    w, h = 245, 242
+    say("illumination, 3 sets of %dx%d in tiles vs one by one" % (w, h))
+    wl = W.with_size(W.get("adjoint_64x512", n_sets=3), w, h)
+    _, sh = _run(rt, wl)
+    n = w * h
+    for s in range(3):
+        one = dict(wl, metric=dict(wl["metric"], bumps=wl["metric"]["bumps"][s:s + 1]))
+        _, shs = _run(rt, one)
+        for k in ("status", "shade", "dir", "len"):
+            assert np.array_equal(sh[k][s * n:(s + 1) * n], shs[k]), (s, k)
